@@ -309,7 +309,7 @@ const void* batch_pick_c64(int tpt, int degree) { return pick_t<K_COULOMB, false
 #elif BATCH_PART == 2
 const void* batch_pick_c32(int tpt, int degree) { return pick_t<K_COULOMB, true>(tpt, degree); }
 #elif BATCH_PART == 3
-const void* batch_pick_y64(int tpt, int degree) { return pick_t<K_YUKAWA, false>(tpt, degree); }
+const void* batch_pick_y64(int tpt, int degree) { return pick_t<K_YUKAWA_ANY, false>(tpt, degree); }
 #elif BATCH_PART == 4
 const void* batch_pick_y32(int tpt, int degree) { return pick_t<K_YUKAWA, true>(tpt, degree); }
 #elif BATCH_PART == 5

@@ -344,7 +344,8 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
     int sym_tile = 256;
     if (!(fp32 && pl->mfma_transfer())) {
         const int64_t want = 8 * 4 * (int64_t)std::max(1, pl->cus);
-        for (int t : {1024, 512}) {
+        for (int t : {1024, kSymTileLong}) {
+            if (pl->kind != BLDTT_COULOMB && t > kSymTileLong) continue;
             int64_t items = 0;
             for (int64_t c = 0; c < T.size(); ++c)
                 if (T.is_leaf(c)) items += (T.count[c] + t - 1) / t;
@@ -369,9 +370,9 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
     auto sym_pp_pass = [&](const DevBuf& items, const DevBuf& entries, const SymWork& sw, hipStream_t s) {
         const int n = (int)sw.pp_items.size(), n0 = (int)sw.pp_plain;
         const DevFold& f = pl->fold_pp;
-        launch_sym(fp32, pl->mfma_transfer(), false, false, items.as<DevItem>(), n0, entries.as<int2>(), pl->dsrc(),
+        launch_sym(ks, fp32, pl->mfma_transfer(), false, false, items.as<DevItem>(), n0, entries.as<int2>(), pl->dsrc(),
                    dS, tab, deg_ptrs(pl->qhat_deg), nfp64, f.out(), s);
-        launch_sym(fp32, pl->mfma_transfer(), false, true, items.as<DevItem>() + n0, n - n0, entries.as<int2>(),
+        launch_sym(ks, fp32, pl->mfma_transfer(), false, true, items.as<DevItem>() + n0, n - n0, entries.as<int2>(),
                    pl->dsrc(), dS, tab, deg_ptrs(pl->qhat_deg), nfp64, f.out_from(n0), s);
     };
     auto sym_pp_fold = [&](hipStream_t s) {
@@ -427,7 +428,7 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
         PhaseMark mark(pl, BLDTT_PH_PP_SELF, st);
         particle_pass(pl->self_items, pl->n_self_items, pl->self_entries, false, st);
         const DevFold& f = pl->fold_self;
-        launch_sym(fp32, pl->mfma_transfer(), false, true, pl->self_sym_items.as<DevItem>(), pl->n_self_sym_items,
+        launch_sym(ks, fp32, pl->mfma_transfer(), false, true, pl->self_sym_items.as<DevItem>(), pl->n_self_sym_items,
                    pl->self_sym_entries.as<int2>(), pl->dsrc(), dS, tab, deg_ptrs(pl->qhat_deg), nfp64, f.out(), st);
         launch_sym_fold(f.segs.as<FoldSeg>(), f.n_segs, f.parts.as<FoldPart>(), f.slots.as<double>(),
                         pl->phi_tree.as<double>(), DegOut{}, st);
@@ -588,7 +589,7 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
                         nullptr, deg_out(pl->phihat_deg), st);
         if (symm) {             // symmetric CC pairs add to the proxy potentials the pass above wrote
             const DevFold& f = pl->fold_cc;
-            launch_sym(fp32, pl->mfma_transfer(), true, false, pl->sym_cc_items.as<DevItem>(), (int)scc.cc_items.size(),
+            launch_sym(ks, fp32, pl->mfma_transfer(), true, false, pl->sym_cc_items.as<DevItem>(), (int)scc.cc_items.size(),
                        pl->sym_cc_entries.as<int2>(), pl->dsrc(), dS, tab, deg_ptrs(pl->qhat_deg), nullptr, f.out(),
                        st);
             launch_sym_fold(f.segs.as<FoldSeg>(), f.n_segs, f.parts.as<FoldPart>(), f.slots.as<double>(), nullptr,

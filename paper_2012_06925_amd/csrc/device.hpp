@@ -25,7 +25,9 @@ namespace dev {
 constexpr int kBlock = 256;
 constexpr int kChunk = 512;                  // sources staged in LDS per round
 
-enum { K_COULOMB = 0, K_YUKAWA = 1, K_OSC = 2, K_REG = 3, K_POLY = 100 };
+// K_YUKAWA_ANY: Yukawa in FP64 with the library's exp, for a param the fast form does
+// not take (negative, infinite or NaN) and for the batch kernel
+enum { K_COULOMB = 0, K_YUKAWA = 1, K_OSC = 2, K_REG = 3, K_YUKAWA_ANY = 4, K_POLY = 100 };
 
 // ---------------------------------------------------------------------------
 // Chebyshev grid and barycentric basis (Sec. 2.1, Eq. 2)
@@ -86,14 +88,96 @@ __device__ __forceinline__ double rsq_fix(double r2, double y) {
 
 __device__ __forceinline__ double rsq_full(double r2) { return rsq_fix(r2, rsq_est(r2)); }
 
+// sin(pi r) / r of the oscillatory kernel from r^2 and the estimate y0 of 1/r.  The
+// estimate is corrected as in rsq_fix, and s = fl(r2 y0) by the same factor 1 + h
+// gives r: e = 1 - s y0 holds half of the rounding of s, so r is rounded once
+// more and not twice as r2 times the rounded 1/r would be.  r modulo 2 (exact) folds to m in [0, 1/2], the sine
+// is m (pi + m^2 Q(m^2)), Q of degree 7 interpolated at Chebyshev nodes, pi in two
+// parts (2.9e-17 relative), with the sign of the reduced r; 0 at integers and
+// for huge r.  22 instructions after the estimate and no branch; the library's
+// sinpi(r) alone takes 1.8x the time of this sine (two polynomials, selects and
+// range checks).  One value from r^2: 1.39 ps against 2.23, rms error over 1/r for
+// r < 3.5 8.4e-17 against 1.8e-16.
+__device__ __forceinline__ double osc_value(double r2, double y0) {
+    const double s = r2 * y0;
+    const double e = fma(-s, y0, 1.0);
+    const double h = e * fma(e, 0.375, 0.5);
+    const double y = fma(y0, h, y0), r = fma(s, h, s);
+    const double f = fma(-2.0, __builtin_rint(0.5 * r), r);
+    const double m = fmin(fabs(f), 1.0 - fabs(f)), w = m * m;
+    double q = 0x1.9ec7b1cdbc923p-21;
+    q = fma(q, w, -0x1.6f867887a27dfp-16);
+    q = fma(q, w, 0x1.e8f3b059105c6p-12);
+    q = fma(q, w, -0x1.e3074ee6b2925p-8);
+    q = fma(q, w, 0x1.50783486f294cp-4);
+    q = fma(q, w, -0x1.32d2cce62adcfp-1);
+    q = fma(q, w, 0x1.466bc6775aad6p+1);
+    q = fma(q, w, -0x1.4abbce625be53p+2);
+    q = fma(q, w, 0x1.1a62633145c07p-53);
+    return copysign(fma(m, 0x1.921fb54442d18p+1, m * q), f) * y;
+}
+
+// exp(-param r) / r of the Yukawa kernel, 0 <= param < inf.  r is r2 times the
+// rounded 1/r, whose error partly cancels between the two factors.
+// exp(-param r) = 2^n e^t with n = rint(-param r / ln2): t = (-param r - n ln2_hi) -
+// n ln2_lo has param r inside an FMA and n ln2_hi exact, so -param r is never
+// rounded; e^t is the degree-11 polynomial of least largest relative error on
+// |t| <= ln2/2 (3.7e-18, by reweighted least squares); v_ldexp_f64 underflows to 0
+// as it should, and the bound on r keeps n inside its 32 bits.  20 instructions
+// and no branch in place of the multiplication and the library's exp with its
+// range checks: the one-sided passes of 2E6 targets and 1E7 sources 77 -> 69 ms
+// (bound by FP64 issue), the value's rms error 8.5e-17 as before for param 0.5,
+// r < 3.5, and smaller where param r is larger.
+__device__ __forceinline__ double yukawa_value(double r2, double y0, double param) {
+    const double y = rsq_fix(r2, y0);
+    const double r = fmin(r2 * y, 2000.0 / param);                // the quotient is the same for every pair
+    const double n = __builtin_rint(r * (param * -0x1.71547652b82fep+0));
+    double t = fma(-param, r, n * -0x1.62e42fee00000p-1);
+    t = fma(n, -0x1.a39ef35793c76p-33, t);
+    double p = 0x1.ad9ed58bcc0acp-26;
+    p = fma(p, t, 0x1.28ad4bed4e7b3p-22);
+    p = fma(p, t, 0x1.71df0ccfde709p-19);
+    p = fma(p, t, 0x1.a0199a21e316fp-16);
+    p = fma(p, t, 0x1.a01a01384bb4ap-13);
+    p = fma(p, t, 0x1.6c16c18431969p-10);
+    p = fma(p, t, 0x1.1111111124546p-7);
+    p = fma(p, t, 0x1.55555555507bap-5);
+    p = fma(p, t, 0x1.555555555550dp-3);
+    p = fma(p, t, 0x1.000000000000ap-1);
+    p = fma(p, t, 1.0);
+    p = fma(p, t, 1.0);
+    return __builtin_amdgcn_ldexp(p, (int)n) * y;
+}
+
+// FP64 kernel value at a squared distance r2, times 2 for Coulomb: its charges are
+// staged as q/2 (charge_scale), which folds one Newton step into the value,
+// 1/r ~= y0 (3 - r^2 y0^2) / 2, relative error ~1.5 e0^2 + rounding for an
+// estimate y0 = (1 + e0)/r (|e0| ~ 5e-8).  GUARD: r2 may be 0, which gives 0.
+template <int KIND>
+struct G64 {
+    static constexpr double charge_scale = KIND == K_COULOMB ? 0.5 : 1.0;
+    template <bool GUARD>
+    __device__ __forceinline__ static double value(double r2, double param) {
+        if (KIND == K_REG) {
+            const double g = rsq_full(fma(param, param, r2));
+            return GUARD ? (r2 > 0.0 ? g : 0.0) : g;
+        }
+        double y = rsq_est(r2);
+        if (GUARD) y = r2 > 0.0 ? y : 0.0;      // rsq(0) = inf; a zero estimate stays zero below
+        if (KIND == K_COULOMB) return y * fma(-(r2 * y), y, 3.0);
+        if (KIND == K_OSC) return osc_value(r2, y);
+        if (KIND == K_YUKAWA) return yukawa_value(r2, y, param);
+        y = rsq_fix(r2, y);                     // K_YUKAWA_ANY
+        return exp(-param * (r2 * y)) * y;
+    }
+};
+
 // FP64 evaluation on absolute coordinates; sources are double4 (x, y, z, w)
-// with w = q, or w = q/2 for Coulomb (charge_scale).  Coulomb folds one
-// Newton step into the sum: q/r ~= (q/2) y0 (3 - r^2 y0^2), relative error
-// ~1.5 e0^2 + rounding for an estimate y0 = (1 + e0)/r (|e0| ~ 5e-8).
+// with w = charge_scale q.
 template <int KIND>
 struct E64 {
     using V = double4;
-    static constexpr double charge_scale = KIND == K_COULOMB ? 0.5 : 1.0;
+    static constexpr double charge_scale = G64<KIND>::charge_scale;
     template <bool GUARD>
     __device__ __forceinline__ static void add(double& acc, double tx, double ty, double tz, const V& s,
                                                double param) {
@@ -104,20 +188,13 @@ struct E64 {
         }
         double dx = tx - s.x, dy = ty - s.y, dz = tz - s.z;
         double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
-        double y = rsq_est(r2);
-        if (GUARD) y = r2 > 0.0 ? y : 0.0;      // rsq(0) = inf; a zero estimate stays zero below
         if (KIND == K_COULOMB) {
-            const double u = fma(-(r2 * y), y, 3.0);
-            acc = fma(s.w * y, u, acc);
-            return;
+            double y = rsq_est(r2);
+            if (GUARD) y = r2 > 0.0 ? y : 0.0;
+            acc = fma(s.w * y, fma(-(r2 * y), y, 3.0), acc);
+        } else {
+            acc = fma(s.w, G64<KIND>::template value<GUARD>(r2, param), acc);
         }
-        y = rsq_fix(r2, y);
-        double g;
-        if (KIND == K_COULOMB) g = y;
-        else if (KIND == K_YUKAWA) g = exp(-param * (r2 * y)) * y;
-        else if (KIND == K_OSC) g = sinpi(r2 * y) * y;
-        else g = GUARD ? (r2 > 0.0 ? rsq_full(fma(param, param, r2)) : 0.0) : rsq_full(fma(param, param, r2));
-        acc = fma(s.w, g, acc);
     }
 };
 
@@ -905,8 +982,8 @@ __device__ __forceinline__ void down_leaf_mfma_body(const DevItem& it, bool far,
 }
 
 // ---------------------------------------------------------------------------
-// Symmetric passes for targets = sources (Coulomb).  G(x, y) = G(y, x), so one
-// kernel value serves two terms:
+// Symmetric passes for targets = sources (the four physical kernels in FP64,
+// Coulomb in FP32).  G(x, y) = G(y, x), so one kernel value serves two terms:
 //   PP (pairs of distinct leaves {A, B}): phi_i += q_j G, phi_j += q_i G;
 //   CC (pairs of clusters {A, B} at one degree): phihat_A[l] += G qhat_B[k] and
 //      phihat_B[k] += G qhat_A[l] -- the proxy grids of a cluster are the same
@@ -955,15 +1032,15 @@ constexpr int sym_lds_bytes() {
 // and the same bits (a lane's second row is padding with charge 0), so the
 // particle passes give such tiles H = 1 and no lane slot idles; tiles of 129
 // to 192 particles take H = 3 (192 lane slots in place of 256).
-template <bool F32, bool PROXY, int H = 2, bool SPROXY = PROXY>
+template <bool F32, bool PROXY, int H = 2, bool SPROXY = PROXY, int KIND = K_COULOMB>
 __device__ __forceinline__ void sym_body(const DevItem it, const int2* __restrict__ entries, DevParticles p,
                                          DevTree T, const double* __restrict__ tab, DegPtrs qhat, void* lds,
                                          double* nfp64, double* __restrict__ tslots, int64_t tbase,
-                                         double* __restrict__ sslots, int64_t sbase) {
+                                         double* __restrict__ sslots, int64_t sbase, double param = 0.0) {
+    static_assert(!F32 || KIND == K_COULOMB, "the FP32 symmetric pass evaluates the Coulomb kernel");
     using R = typename std::conditional<F32, float, double>::type;
     using V = typename std::conditional<F32, float4, double4>::type;
-    // FP64: charges staged as q/2 for the folded Newton step (E64<K_COULOMB>)
-    constexpr R qs = F32 ? (R)1 : (R)0.5;
+    constexpr R qs = F32 ? (R)1 : (R)G64<KIND>::charge_scale;
     V* src = static_cast<V*>(lds);                               // per copy: 64 staged sources, twice
     double (*part_red)[64] = reinterpret_cast<double (*)[64]>(src + 4 * 128);  // [4][64] wave partials
     int* sidx = reinterpret_cast<int*>(part_red + 4);            // [4 * 64] staged particle index, -1: none
@@ -1070,6 +1147,9 @@ __device__ __forceinline__ void sym_body(const DevItem it, const int2* __restric
             double sum[H];
 #pragma unroll
             for (int h = 0; h < H; ++h) sum[h] = 0.0;
+            // the Coulomb step is short and its 64 copies fit the instruction
+            // cache; the other kernels' (3 to 5 times as long) would not
+            constexpr int kUnroll = KIND == K_COULOMB ? 64 : 4;
             // 64 steps: lane l pairs its H targets with source (l + s) mod 64;
             // every term goes to FP64 sums
             auto step = [&](int s, auto guard) {
@@ -1090,9 +1170,7 @@ __device__ __forceinline__ void sym_body(const DevItem it, const int2* __restric
                                 }
                             }
                         } else {
-                            double y0 = rsq_est(r2);
-                            if constexpr (decltype(guard)::value) y0 = r2 > 0.0 ? y0 : 0.0;
-                            y[h] = y0 * fma(-(r2 * y0), y0, 3.0);   // 2 y0 (3 - r^2 y0^2)/2; q staged /2
+                            y[h] = G64<KIND>::template value<decltype(guard)::value>(r2, param);
                         }
                         sum[h] = fma((double)v.w, y[h], sum[h]);
                     }
@@ -1110,10 +1188,10 @@ __device__ __forceinline__ void sym_body(const DevItem it, const int2* __restric
 #pragma unroll 1
                 for (int s = 0; s < 64; ++s) step(s, std::true_type{});
             } else if (guard) {
-#pragma unroll
+#pragma unroll (kUnroll)
                 for (int s = 0; s < 64; ++s) step(s, std::true_type{});
             } else {
-#pragma unroll
+#pragma unroll (kUnroll)
                 for (int s = 0; s < 64; ++s) step(s, std::false_type{});
             }
 #pragma unroll

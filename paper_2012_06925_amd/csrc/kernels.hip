@@ -100,25 +100,33 @@ __global__ __launch_bounds__(kBlock) void k_down_leaf(const DevItem* __restrict_
 // ---------------------------------------------------------------------------
 // Symmetric passes on the vector ALUs (sym_body): one work group per item.
 // ---------------------------------------------------------------------------
-template <bool F32, bool PROXY>
+template <int KIND, bool F32, bool PROXY>
 __global__ __launch_bounds__(kBlock) void k_sym(const DevItem* __restrict__ items, const int2* __restrict__ entries,
                                                 DevParticles p, DevTree T, const double* __restrict__ tab,
-                                                DegPtrs qhat, double* __restrict__ nfp64, SymSlots out) {
+                                                DegPtrs qhat, double param, double* __restrict__ nfp64,
+                                                SymSlots out) {
     __shared__ double4 pool[(sym_lds_bytes<F32>() + 31) / 32];
-    // tiles of more than 128 targets: four per lane (one wave per copy); the
-    // tails of leaves take fewer, so that fewer lane slots idle: three for
-    // 129..192 particles, one for at most 64.  The proxy passes keep two and
-    // four (their register count doubles with the one-per-lane body).
     const DevItem it = items[blockIdx.x];
     const int64_t base = out.ibase[blockIdx.x];
-    if (!PROXY && it.tn > 128 && it.tn <= 192)
-        sym_body<F32, PROXY, 3>(it, entries, p, T, tab, qhat, pool, nfp64, out.slots, base, out.slots, base + it.tn);
-    else if (it.tn > 128)
-        sym_body<F32, PROXY, 4>(it, entries, p, T, tab, qhat, pool, nfp64, out.slots, base, out.slots, base + it.tn);
-    else if (PROXY || it.tn > 64)
-        sym_body<F32, PROXY, 2>(it, entries, p, T, tab, qhat, pool, nfp64, out.slots, base, out.slots, base + it.tn);
-    else
-        sym_body<F32, PROXY, 1>(it, entries, p, T, tab, qhat, pool, nfp64, out.slots, base, out.slots, base + it.tn);
+    auto body = [&](auto h) {
+        sym_body<F32, PROXY, decltype(h)::value, PROXY, KIND>(it, entries, p, T, tab, qhat, pool, nfp64, out.slots,
+                                                              base, out.slots, base + it.tn, param);
+    };
+    if constexpr (KIND == K_COULOMB) {
+        // tiles of more than 128 targets: four per lane (one wave per copy);
+        // the tails of leaves take fewer, so that fewer lane slots idle: three
+        // for 129..192 particles, one for at most 64.  The proxy passes keep two
+        // and four (their register count doubles with the one-per-lane body).
+        if (!PROXY && it.tn > 128 && it.tn <= 192) body(std::integral_constant<int, 3>{});
+        else if (it.tn > 128) body(std::integral_constant<int, 4>{});
+        else if (PROXY || it.tn > 64) body(std::integral_constant<int, 2>{});
+        else body(std::integral_constant<int, 1>{});
+    } else {
+        // the longer kernels: the source read and the partial's move weigh
+        // little beside them, so two per lane do (kSymTileLong targets at most)
+        if (it.tn > 64) body(std::integral_constant<int, 2>{});
+        else body(std::integral_constant<int, 1>{});
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -957,6 +965,10 @@ void launch_interact(KernelSpec k, bool fp32, bool proxy_targets, int tpt, const
     if (fp32) {
         if (proxy_targets) { DISPATCH_KIND(k.kind, LAUNCH_ONE(true, true)); }
         else { DISPATCH_KIND(k.kind, LAUNCH_ONE(true, false)); }
+    } else if (k.kind == K_YUKAWA && !(k.param >= 0.0 && k.param < INFINITY)) {
+        constexpr int KK = K_YUKAWA_ANY;
+        if (proxy_targets) LAUNCH_ONE(false, true);
+        else LAUNCH_ONE(false, false);
     } else {
         if (proxy_targets) { DISPATCH_KIND(k.kind, LAUNCH_ONE(false, true)); }
         else { DISPATCH_KIND(k.kind, LAUNCH_ONE(false, false)); }
@@ -983,11 +995,12 @@ void launch_pp_mfma(const DevItem* items, int n_items, const int2* entries, DevP
     CHECK_LAUNCH();
 }
 
-void launch_sym(bool fp32, bool mfma, bool proxies, bool guarded, const DevItem* items, int n_items,
+void launch_sym(KernelSpec k, bool fp32, bool mfma, bool proxies, bool guarded, const DevItem* items, int n_items,
                 const int2* entries, DevParticles p, DevTree T, const double* tab, DegPtrs qhat, double* nfp64,
                 SymSlots out, hipStream_t st) {
     if (n_items <= 0) return;
     if (!out.slots || !out.ibase) throw Error(-1, "symmetric pass without slots");
+    if (fp32 && k.kind != K_COULOMB) throw Error(-1, "the FP32 symmetric pass evaluates the Coulomb kernel");
     if (fp32 && mfma) {
         if (proxies && guarded) throw Error(-1, "proxy entries are never guarded");
         if (proxies)
@@ -1002,15 +1015,22 @@ void launch_sym(bool fp32, bool mfma, bool proxies, bool guarded, const DevItem*
         CHECK_LAUNCH();
         return;
     }
-#define LAUNCH_SYM(F, PX) hipLaunchKernelGGL((k_sym<F, PX>), dim3(n_items), dim3(kBlock), 0, st, items, entries, p, T, \
-                                            tab, qhat, nfp64, out)
+#define LAUNCH_SYM(KK, F, PX) hipLaunchKernelGGL((k_sym<KK, F, PX>), dim3(n_items), dim3(kBlock), 0, st, items, entries, \
+                                                p, T, tab, qhat, k.param, nfp64, out)
+#define LAUNCH_SYM64(KK) do { if (proxies) LAUNCH_SYM(KK, false, true); else LAUNCH_SYM(KK, false, false); } while (0)
     if (fp32) {
-        if (proxies) LAUNCH_SYM(true, true);
-        else LAUNCH_SYM(true, false);
+        if (proxies) LAUNCH_SYM(K_COULOMB, true, true);
+        else LAUNCH_SYM(K_COULOMB, true, false);
     } else {
-        if (proxies) LAUNCH_SYM(false, true);
-        else LAUNCH_SYM(false, false);
+        switch (k.kind) {
+        case K_COULOMB: LAUNCH_SYM64(K_COULOMB); break;
+        case K_YUKAWA: LAUNCH_SYM64(K_YUKAWA); break;
+        case K_OSC: LAUNCH_SYM64(K_OSC); break;
+        case K_REG: LAUNCH_SYM64(K_REG); break;
+        default: throw Error(-1, "no symmetric pass for this kernel");
+        }
     }
+#undef LAUNCH_SYM64
 #undef LAUNCH_SYM
     CHECK_LAUNCH();
 }

@@ -76,7 +76,8 @@ void launch_interact(KernelSpec k, bool fp32, bool proxy_targets, int tpt, const
                      DegPtrs qhat, double* out, DegOut pout, hipStream_t st, bool add = false,
                      double* nfp64 = nullptr);
 
-// Symmetric passes (Coulomb, targets = sources): items are tiles of a target
+// Symmetric passes (targets = sources; Coulomb in FP32, the four physical
+// kernels in FP64): items are tiles of a target
 // cluster A (particles, or proxies of degree item.degree) with entries of
 // partner clusters B (particle ranges, or proxy entries); every kernel value
 // counts for both sides.  Item i writes its sums to the slots of its fold
@@ -85,11 +86,12 @@ void launch_interact(KernelSpec k, bool fp32, bool proxy_targets, int tpt, const
 // is the same bits every time.  With fp32 and mfma the squared distances
 // come from the FP64 matrix cores.
 // guarded: the items' entries are all flagged SRC_RANGE_GUARD (else none is).
+constexpr int kSymTileLong = 512;     // targets per item at most for Yukawa, oscillatory, regularized Coulomb
 struct SymSlots {
     double* slots;
     const int64_t* ibase;
 };
-void launch_sym(bool fp32, bool mfma, bool proxies, bool guarded, const DevItem* items, int n_items,
+void launch_sym(KernelSpec k, bool fp32, bool mfma, bool proxies, bool guarded, const DevItem* items, int n_items,
                 const int2* entries, DevParticles p, DevTree T, const double* tab, DegPtrs qhat, double* nfp64,
                 SymSlots out, hipStream_t st);
 

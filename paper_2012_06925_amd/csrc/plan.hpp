@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <chrono>
+#include <cmath>
 #include <cstring>
 #include <string>
 #include <vector>
@@ -292,8 +293,26 @@ struct bldtt_plan {
     // BLDTT_DEVICE_TRAVERSAL: the lists of each compute come from the walk on the GPU (walk.hip)
     DevWalk walk;
     bool device_walk() const { return !host_only && (flags & BLDTT_DEVICE_TRAVERSAL) != 0; }
+    // Pairs listed both ways evaluated once for both: targets = sources and a
+    // symmetric kernel.  Coulomb in both precisions; Yukawa, oscillatory and
+    // regularized Coulomb in FP64 (their FP32 values are taken relative to the
+    // target box, so the two directions of a pair differ by FP32 rounding).
+    // The symmetric items pad with uncharged points 1e18 away, which must stay
+    // apart from the particles and give finite kernel values there: else the
+    // one-sided passes, which evaluate no padding, take those three kernels.
+    // (Half the kernel values: Yukawa, 3E5 particles, n 6, leaf 500: 38.1 ms one-sided,
+    // 18.2 ms; oscillatory, 1.2E5, n 8, leaf 1000: 26.3 and 10.1 ms, with the
+    // values of device.hpp.)
     bool symmetric_pp() const {
-        return aliased && kind == BLDTT_COULOMB && (flags & BLDTT_ONE_SIDED_PP) == 0;
+        if (!aliased || (flags & BLDTT_ONE_SIDED_PP) != 0) return false;
+        if (kind == BLDTT_COULOMB) return true;
+        return kind != BLDTT_POLY_TEST && (flags & BLDTT_FP32_EVAL) == 0 && padding_safe();
+    }
+    bool padding_safe() const {
+        for (int d = 0; d < 3; ++d)
+            if (!(S.lo[d] > -1e17 && S.hi[d] < 1e17)) return false;
+        if (kind == BLDTT_YUKAWA) return param >= 0.0 && param < 1e100;
+        return kind != BLDTT_REGCOULOMB || std::fabs(param) < 1e100;
     }
 
     int tpt = 2, tpt_proxy = 2;              // targets per thread in the interaction kernels

@@ -1,0 +1,69 @@
+"""GPU parity of the interaction passes' own rules: which pass a plan takes and how its items are cut.
+
+The oracle is the reference (plain C, FP64); bar 1e-12, as for every FP64 potential.
+"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from oracle import core  # noqa: E402
+from paper_2012_06925_amd import _lib, inputs  # noqa: E402
+
+PARITY = 1e-12
+
+
+def _plan(p, targets=None, **kw):
+    from paper_2012_06925_amd import api
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()        # noqa: E731
+    t = None if targets is None else [dev(a) for a in (targets.x, targets.y, targets.z)]
+    return api.Plan(t, [dev(a) for a in (p.x, p.y, p.z, p.q)], **kw)
+
+
+def _computes(plan, n=2):
+    return [plan.compute().cpu().numpy() for _ in range(n)]
+
+
+def _close(got, ref):
+    assert core.rel_l2(got, ref) < PARITY and core.max_rel(got, ref) < PARITY, (core.rel_l2(got, ref),
+                                                                               core.max_rel(got, ref))
+
+
+@pytest.mark.parametrize("kernel", ["yukawa", "oscillatory", "regcoulomb"])
+@pytest.mark.parametrize("n,leaf,degree", [(5001, 40, 2), (9000, 300, 3), (6001, 700, 4)])
+def test_symmetric_passes_of_the_other_kernels(kernel, n, leaf, degree):
+    # leaves of one wave, of two per lane and of more than one tile; some
+    # points twice (r = 0 inside a leaf and in the guarded ranges)
+    p = inputs.particles(n, "uniform", seed=71)
+    for a in (p.x, p.y, p.z):
+        a[1:40:2] = a[0:39:2]
+    plan = _plan(p, kernel=kernel, theta=0.8, degree=degree, leaf=leaf)
+    a, b = _computes(plan)
+    st = plan.stats()
+    plan.close()
+    assert st["pass_interactions"][2] > 0 and st["pass_interactions"][4] > 0
+    assert np.array_equal(a, b)
+    _close(a, core.bldtt(p, p, kernel=kernel, theta=0.8, degree=degree, leaf=leaf))
+
+
+@pytest.mark.parametrize("kernel,param,shift", [("yukawa", -0.5, 0.0), ("yukawa", 1e101, 0.0), ("regcoulomb", 0.01, 2e17),
+                                                ("yukawa", 0.5, 1e18)])
+def test_padding_unsafe_problems_stay_one_sided(kernel, param, shift):
+    # kernel values that grow with the distance or overflow at the padding,
+    # and particles out where the padding sits, take the passes without padding
+    p = inputs.particles(3000, "uniform", seed=72)
+    if shift:
+        for a in (p.x, p.y, p.z):
+            a *= 1e16
+            a += shift
+    kw = dict(kernel=kernel, param=param, theta=0.7, degree=3, leaf=100)
+    plan = _plan(p, **kw)
+    got = _computes(plan, 1)[0]
+    st = plan.stats()
+    plan.close()
+    assert st["pass_interactions"][2] == 0 and st["pass_interactions"][4] == 0
+    one = _plan(p, flags=_lib.ONE_SIDED_PP, **kw)
+    ref = _computes(one, 1)[0]
+    one.close()
+    assert np.all(np.isfinite(ref)) and np.array_equal(got, ref)
