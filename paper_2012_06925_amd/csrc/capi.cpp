@@ -296,7 +296,7 @@ void ensure_self_work(bldtt_plan* pl) {
     upload(f.ibase, fold.ibase);
     upload(f.segs, fold.segs);
     upload(f.parts, fold.parts);
-    f.n_segs = (int)fold.segs.size();
+    f.set_segments(fold);
     pl->n_self_items = (int)di.size();
     pl->n_self_sym_items = (int)sym.size();
     pl->self_evaluations = evals;
@@ -355,6 +355,12 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
             }
         }
     }
+    // symmetric items: about four per resident work group (four of those per
+    // CU), of at least one round of 256 sources.  A leaf of a small problem has few
+    // tiles and many partners, and one item per tile left the GPU idle: the pass of
+    // 1E4 particles (leaf 500) 345 us with 62 items, 37 us with 1023; 1E5 Gaussian
+    // particles 2.85 -> 1.7 ms; at 1E6 and more one item per tile is as good.
+    const ItemCut sym_cut{16 * (int64_t)std::max(1, pl->cus), 256};
     auto particle_pass = [&](const DevBuf& items, int n, const DevBuf& entries, bool add, hipStream_t s) {
         if (mfma_pp)
             launch_pp_mfma(items.as<DevItem>(), n, entries.as<int2>(), pl->dtgt(), dT, pl->dsrc(), dS, tab,
@@ -377,7 +383,7 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
     };
     auto sym_pp_fold = [&](hipStream_t s) {
         const DevFold& f = pl->fold_pp;
-        launch_sym_fold(f.segs.as<FoldSeg>(), f.n_segs, f.parts.as<FoldPart>(), f.slots.as<double>(),
+        launch_sym_fold(f.segs.as<FoldSeg>(), f.n_segs, f.max_n, f.parts.as<FoldPart>(), f.slots.as<double>(),
                         pl->phi_tree.as<double>(), DegOut{}, s);
     };
     auto add_bases = [](Upload& u, DevFold& d, const SymFold& f) {
@@ -385,7 +391,7 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
         u.add(d.ibase, f.ibase);
     };
     auto add_parts = [](Upload& u, DevFold& d, const SymFold& f) {
-        d.n_segs = (int)f.segs.size();
+        d.set_segments(f);
         u.add(d.segs, f.segs).add(d.parts, f.parts);
     };
 
@@ -430,7 +436,7 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
         const DevFold& f = pl->fold_self;
         launch_sym(ks, fp32, pl->mfma_transfer(), false, true, pl->self_sym_items.as<DevItem>(), pl->n_self_sym_items,
                    pl->self_sym_entries.as<int2>(), pl->dsrc(), dS, tab, deg_ptrs(pl->qhat_deg), nfp64, f.out(), st);
-        launch_sym_fold(f.segs.as<FoldSeg>(), f.n_segs, f.parts.as<FoldPart>(), f.slots.as<double>(),
+        launch_sym_fold(f.segs.as<FoldSeg>(), f.n_segs, f.max_n, f.parts.as<FoldPart>(), f.slots.as<double>(),
                         pl->phi_tree.as<double>(), DegOut{}, st);
     }
 
@@ -476,7 +482,7 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
                 PhaseMark mark(pl, BLDTT_PH_PP_SYM, pl->side);
                 sym_pp_pass(pl->sym_items, pl->sym_entries, pl->sym, pl->side);
                 mark_host(2);
-            }, sep_guard, false, sym_tile);
+            }, sep_guard, false, sym_tile, sym_cut);
             drop_self_pairs(near_rest);
         }
         pack_work(T, S, symm ? near_rest : pl->lists, pl->degree, tile, ptile, pl->work_near);
@@ -521,11 +527,11 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
             PhaseMark mark(pl, BLDTT_PH_PP_SYM, st);
             sym_pp_pass(pl->sym_items, pl->sym_entries, pl->sym, st);
             mark_host(2);
-        }, sep_guard, false, sym_tile);
+        }, sep_guard, false, sym_tile, sym_cut);
         fold_parts(T, pl->sym.pp_items, pl->sym.pp_entries, false, pl->sym.pp_fold);
         drop_self_pairs(rest);
     }
-    if (symm && varied) split_symmetric(T, sep, pl->degree, false, true, rest, pl->sym_sep, {}, sep_guard, false, sym_tile);
+    if (symm && varied) split_symmetric(T, sep, pl->degree, false, true, rest, pl->sym_sep, {}, sep_guard, false, sym_tile, sym_cut);
     const SymWork& scc = varied ? pl->sym_sep : pl->sym;          // symmetric CC pairs
     std::vector<uint32_t> scc_deg;
     if (symm) scc_deg = sym_cc_degrees(T, scc);
@@ -592,7 +598,7 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
             launch_sym(ks, fp32, pl->mfma_transfer(), true, false, pl->sym_cc_items.as<DevItem>(), (int)scc.cc_items.size(),
                        pl->sym_cc_entries.as<int2>(), pl->dsrc(), dS, tab, deg_ptrs(pl->qhat_deg), nullptr, f.out(),
                        st);
-            launch_sym_fold(f.segs.as<FoldSeg>(), f.n_segs, f.parts.as<FoldPart>(), f.slots.as<double>(), nullptr,
+            launch_sym_fold(f.segs.as<FoldSeg>(), f.n_segs, f.max_n, f.parts.as<FoldPart>(), f.slots.as<double>(), nullptr,
                             deg_out(pl->phihat_deg), st);
         }
     }

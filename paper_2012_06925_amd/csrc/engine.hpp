@@ -176,6 +176,14 @@ void pack_work(const Tree& T, const Tree& S, const Lists& L, int degree, int til
                const std::vector<uint32_t>* extra = nullptr);
 
 
+// How finely a pass's work is cut into items: about `want` items of equal cost
+// (targets x sources), each with at least min_src sources (an item's loads,
+// barriers and last reduction are worth some hundred sources).  want 0: one
+// item per tile of targets, however many sources it has.
+struct ItemCut {
+    int64_t want = 0, min_src = 1;
+};
+
 // Symmetric pairs of a targets = sources plan (one tree): with `pp`, leaf
 // pairs (A, B), A != B, listed as PP in both directions; with `cc`, cluster
 // pairs listed as CC in both directions at one degree.  `rest` receives a copy
@@ -266,10 +274,12 @@ struct SymWork {
 // which are the same points as target and as source): pc_items are tiles of
 // A's particles with the proxy entries of such partners B, grouped by degree;
 // their folds are left to the caller (fold_group_*).  `tile`: targets per
-// item at most (the pass that runs the items must take that many).
+// item at most (the pass that runs the items must take that many).  `cut`: see
+// ItemCut; a tile then has several items, each over a part of its sources, with
+// target slots of its own that the fold adds.
 void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc, Lists& rest, SymWork& sw,
                      const std::function<void()>& pp_ready = {}, bool separate_guarded = false, bool pc = false,
-                     int tile = 256);
+                     int tile = 256, const ItemCut& cut = {});
 
 // Per-cluster degree masks of the proxy potentials the symmetric passes add
 // to: both clusters of each CC pair, the proxy side of each PC/CP pair.

@@ -22,6 +22,8 @@
 // every compute gives the same bits.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
 #include <cstdint>
 #include <type_traits>
 
@@ -130,16 +132,48 @@ __global__ __launch_bounds__(kBlock) void k_sym(const DevItem* __restrict__ item
 }
 
 // ---------------------------------------------------------------------------
-// Fold of a deterministic symmetric pass (fold.hpp): one work group per
-// segment; each output adds its parts in their stored order.
+// Fold of a deterministic symmetric pass (fold.hpp): a work group takes 64
+// outputs of a segment (blockIdx.x the segment, y the 64), each of its four
+// waves every fourth batch of eight parts, and the waves' sums are added in
+// wave order: the same order of the same terms every time.  A fold waits on
+// memory (each part is one load per output, slots written by other CUs), so the
+// loads in flight count: one group per segment with its threads across the
+// outputs left 140 us for 137 leaves, 0.24 ms for 582 and 0.94 ms for 8192.
 // ---------------------------------------------------------------------------
+constexpr int kFoldOutputs = 64;
+
 __global__ __launch_bounds__(kBlock) void k_sym_fold(const FoldSeg* __restrict__ segs,
                                                      const FoldPart* __restrict__ parts,
                                                      const double* __restrict__ slots, double* __restrict__ phi,
                                                      DegOut phihat) {
-    __shared__ FoldPart lp[kFoldLdsParts];
+    constexpr int U = 8;
+    __shared__ double red[3][kFoldOutputs];
     const FoldSeg sg = segs[blockIdx.x];
-    fold_body(sg, parts, slots, (sg.deg < 0 ? phi : phihat.p[sg.deg]) + sg.off, 0, sg.n, lp);
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (sg.pe == sg.pb) return;                                  // the whole group leaves together
+    double* out = (sg.deg < 0 ? phi : phihat.p[sg.deg]) + sg.off;
+    for (int k0 = kFoldOutputs * (int)blockIdx.y; k0 < sg.n; k0 += kFoldOutputs * (int)gridDim.y) {
+        const int k = k0 + lane;
+        double v = 0.0;
+        for (int q0 = sg.pb + U * wave; q0 < sg.pe; q0 += 4 * U) {
+            double s[U];
+            bool in[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const bool real = q0 + u < sg.pe;
+                const FoldPart pt = parts[real ? q0 + u : q0];   // uniform: scalar loads
+                const unsigned d = (unsigned)(k - pt.lo);
+                in[u] = real && d < (unsigned)pt.len;
+                s[u] = slots[pt.slot + (in[u] ? d : 0u)];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) v = in[u] ? v + s[u] : v;
+        }
+        if (wave > 0) red[wave - 1][lane] = v;
+        __syncthreads();
+        if (wave == 0 && k < sg.n) out[k] += ((v + red[0][lane]) + red[1][lane]) + red[2][lane];
+        __syncthreads();                                         // red is written again
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1035,10 +1069,11 @@ void launch_sym(KernelSpec k, bool fp32, bool mfma, bool proxies, bool guarded, 
     CHECK_LAUNCH();
 }
 
-void launch_sym_fold(const FoldSeg* segs, int n_segs, const FoldPart* parts, const double* slots, double* phi,
-                     DegOut phihat, hipStream_t st) {
-    if (n_segs <= 0) return;
-    hipLaunchKernelGGL(k_sym_fold, dim3(n_segs), dim3(kBlock), 0, st, segs, parts, slots, phi, phihat);
+void launch_sym_fold(const FoldSeg* segs, int n_segs, int max_n, const FoldPart* parts, const double* slots,
+                     double* phi, DegOut phihat, hipStream_t st) {
+    if (n_segs <= 0 || max_n <= 0) return;
+    const unsigned ny = (unsigned)std::min((max_n + kFoldOutputs - 1) / kFoldOutputs, 1024);
+    hipLaunchKernelGGL(k_sym_fold, dim3(n_segs, ny), dim3(kBlock), 0, st, segs, parts, slots, phi, phihat);
     CHECK_LAUNCH();
 }
 

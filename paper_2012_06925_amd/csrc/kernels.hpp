@@ -95,11 +95,11 @@ void launch_sym(KernelSpec k, bool fp32, bool mfma, bool proxies, bool guarded, 
                 const int2* entries, DevParticles p, DevTree T, const double* tab, DegPtrs qhat, double* nfp64,
                 SymSlots out, hipStream_t st);
 
-// out[k] += the parts of every segment (fold.hpp), one work group per segment:
+// out[k] += the parts of every segment (fold.hpp; max_n: the outputs of the largest):
 // phi (tree order) for particle segments, phihat.p[degree] for proxy ones,
 // which already hold the other terms.
-void launch_sym_fold(const FoldSeg* segs, int n_segs, const FoldPart* parts, const double* slots, double* phi,
-                     DegOut phihat, hipStream_t st);
+void launch_sym_fold(const FoldSeg* segs, int n_segs, int max_n, const FoldPart* parts, const double* slots,
+                     double* phi, DegOut phihat, hipStream_t st);
 
 // One-sided particle-target pass (PP ranges and PC proxies) in FP32 evaluation
 // with the squared distances from the FP64 matrix cores, Coulomb kernel only.

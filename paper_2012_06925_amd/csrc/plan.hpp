@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -148,7 +149,12 @@ void traverse_device(DevWalk& w, const DevTree& dT, const DevTree& dS,
 // item, segments and parts.
 struct DevFold {
     DevBuf slots, ibase, segs, parts;
-    int n_segs = 0;
+    int n_segs = 0, max_n = 0;               // segments, outputs of the largest
+    void set_segments(const SymFold& f) {
+        n_segs = (int)f.segs.size();
+        max_n = 0;
+        for (const FoldSeg& s : f.segs) max_n = std::max(max_n, s.n);
+    }
     SymSlots out() const { return SymSlots{slots.as<double>(), ibase.as<int64_t>()}; }
     SymSlots out_from(int item) const { return SymSlots{slots.as<double>(), ibase.as<int64_t>() + item}; }
 };

@@ -556,6 +556,40 @@ struct SymBlock {
     double evals = 0.0;
 };
 
+// The particle-range entries [at, end) of E cut at every multiple of `chunk`
+// sources (the order of the sources stays); first[c] is the entry chunk c
+// starts with, first.back() the end.
+void chunk_ranges(std::vector<Entry>& E, int64_t at, int64_t chunk, std::vector<int32_t>& first) {
+    static thread_local std::vector<Entry> in;
+    in.assign(E.begin() + at, E.end());
+    E.resize(at);
+    first.assign(1, (int32_t)at);
+    int64_t have = 0;                                      // sources in the open chunk
+    for (const Entry& e : in) {
+        const uint32_t kind = (uint32_t)e.b & ~(uint32_t)kCountMask;
+        for (int64_t a = e.a, n = e.b & kCountMask; n > 0;) {
+            if (have == chunk) {
+                first.push_back((int32_t)E.size());
+                have = 0;
+            }
+            const int64_t m = std::min(n, chunk - have);
+            E.push_back(Entry{(int32_t)a, (int32_t)(kind | (uint32_t)m)});
+            a += m;
+            n -= m;
+            have += m;
+        }
+    }
+    first.push_back((int32_t)E.size());
+}
+
+// Sources per chunk of items with up to `targets` targets that cost at most
+// about `cap` each, in whole rounds: the symmetric kernels stage 64, 128 or 256
+// sources at a time.
+int64_t chunk_sources(int64_t targets, double cap, int64_t min_src) {
+    const double by_cost = std::min(cap / (double)targets, 1e15);
+    return (std::max((int64_t)by_cost, min_src) + 255) / 256 * 256;
+}
+
 // The blocks' entries concatenated; their items sorted longest first, those
 // without guarded ranges ahead of those with (n_plain of them).
 void gather(std::vector<SymBlock>& blks, std::vector<Entry>& entries, std::vector<Item>& out, double& evals,
@@ -590,7 +624,8 @@ std::vector<uint32_t> sym_cc_degrees(const Tree& T, const SymWork& sw) {
 }
 
 void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc, Lists& rest, SymWork& sw,
-                     const std::function<void()>& pp_ready, bool separate_guarded, bool pc, int tile) {
+                     const std::function<void()>& pp_ready, bool separate_guarded, bool pc, int tile,
+                     const ItemCut& cut) {
     sw.clear();
     const int64_t nc = T.size();
     constexpr int64_t kBlk = 256;
@@ -618,12 +653,30 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
     }
     // PC (a, b) listed with its mirror CP (b, a) at degree d
     auto sym_pc = [&](int64_t a, int64_t b, int d) { return pc && ipc.has(a, b, d) && icp.has(b, a, d); };
+    // the most one item may cost, from the symmetric pairs' kernel values
+    auto cost_cap = [&](const std::vector<int64_t>& tc, const std::vector<int64_t>& sc, auto&& values) {
+        if (cut.want <= 0) return 1e300;
+        const int64_t n = (int64_t)tc.size();
+        const int64_t nch = std::max<int64_t>(1, std::min<int64_t>(4 * num_threads(), n / 16384 + 1));
+        const int64_t per = (n + nch - 1) / nch;
+        std::vector<double> part(nch, 0.0);
+        parallel_run(nch, [&](int64_t k) {
+            for (int64_t e = k * per; e < std::min(n, (k + 1) * per); ++e) part[k] += values(e, tc[e], sc[e]);
+        });
+        double v = 0.0;
+        for (double x : part) v += x;
+        return std::max(1.0, v / (double)cut.want);
+    };
     if (pp) {
+        const double cap = cost_cap(L.tc[PP], L.sc[PP], [&](int64_t, int64_t a, int64_t b) {
+            return a != b && T.is_leaf(a) && T.is_leaf(b) ? 0.5 * (double)T.count[a] * (double)T.count[b] : 0.0;
+        });
         // per leaf A: the partners B > A as merged particle ranges, tiles of A's particles
         std::vector<SymBlock> blks(nblk);
         parallel_run(nblk, [&](int64_t bi) {
             SymBlock& B = blks[bi];
             std::vector<std::pair<int64_t, int64_t>> rp, rg, none;
+            std::vector<int32_t> first, gfirst;
             for (int64_t a = bi * kBlk; a < std::min(nc, (bi + 1) * kBlk); ++a) {
                 if (!T.is_leaf(a)) continue;
                 double src = 0.0;
@@ -638,27 +691,43 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
                 if (rp.empty() && rg.empty()) continue;
                 double src_g = 0.0;
                 for (auto& r : rg) src_g += (double)r.second;
+                // the ranges, plain then guarded, cut into the chunks of a full tile
+                const int64_t full = std::min(kTile, T.count[a]);
+                const double src_all = separate_guarded ? src - src_g : src;
                 const int64_t eb = (int64_t)B.entries.size();
                 emit_ranges(rp, none, B.entries);
+                if (!separate_guarded) emit_ranges(none, rg, B.entries);
+                const int64_t chunk = chunk_sources(full, cap, cut.min_src);
+                if ((int64_t)src_all > chunk) chunk_ranges(B.entries, eb, chunk, first);
+                else first = {(int32_t)eb, (int32_t)B.entries.size()};
                 const int64_t em = (int64_t)B.entries.size();
-                emit_ranges(none, rg, B.entries);
-                const int64_t ee = (int64_t)B.entries.size();
+                if (separate_guarded) {
+                    emit_ranges(none, rg, B.entries);
+                    if ((int64_t)src_g > chunk) chunk_ranges(B.entries, em, chunk, gfirst);
+                    else gfirst = {(int32_t)em, (int32_t)B.entries.size()};
+                }
                 B.evals += 2.0 * (double)T.count[a] * src;
-                // tiles of A's particles: one item over every range, or one
-                // over the plain ranges and one over the guarded ranges
+                // items of one tile over the chunks first[0..]: a tile of few
+                // targets (whole waves of 64) takes several chunks, half as many
+                // as would make it cost what a full one does (its rounds of 256
+                // sources wait longer for their loads than they compute)
+                auto put = [&](std::vector<std::pair<double, Item>>& items, const std::vector<int32_t>& at, double sources,
+                               int64_t tb, int64_t tn) {
+                    const int64_t nch = (int64_t)at.size() - 1;
+                    const int64_t g = std::max<int64_t>(1, std::min(nch, full / (2 * ((tn + 63) / 64 * 64))));
+                    for (int64_t c = 0; c < nch; c += g) {
+                        const int64_t d = std::min(nch, c + g);
+                        if (at[d] == at[c]) continue;
+                        items.push_back({sources * (double)tn * (double)(d - c) / (double)nch,
+                                         Item{(int32_t)tb, (int32_t)tn, at[c], at[d], (int32_t)a, 0, (int32_t)tb}});
+                    }
+                };
+                // tiles of A's particles: items over every range, or over the
+                // plain ranges and over the guarded ranges apart
                 for (int64_t tb = T.begin[a]; tb < T.begin[a] + T.count[a]; tb += kTile) {
                     const int64_t tn = std::min<int64_t>(kTile, T.begin[a] + T.count[a] - tb);
-                    if (!separate_guarded) {
-                        B.items.push_back({src * (double)tn, Item{(int32_t)tb, (int32_t)tn, (int32_t)eb, (int32_t)ee,
-                                                                  (int32_t)a, 0, (int32_t)tb}});
-                        continue;
-                    }
-                    if (em > eb)
-                        B.items.push_back({(src - src_g) * (double)tn, Item{(int32_t)tb, (int32_t)tn, (int32_t)eb,
-                                                                         (int32_t)em, (int32_t)a, 0, (int32_t)tb}});
-                    if (ee > em)
-                        B.gitems.push_back({src_g * (double)tn, Item{(int32_t)tb, (int32_t)tn, (int32_t)em,
-                                                                   (int32_t)ee, (int32_t)a, 0, (int32_t)tb}});
+                    put(B.items, first, src_all, tb, tn);
+                    if (separate_guarded) put(B.gitems, gfirst, src_g, tb, tn);
                 }
             }
         });
@@ -711,7 +780,12 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
     rest.sep_tc.clear();
     rest.sep_sc.clear();
     if (cc) {
-        // per (cluster A, degree d): the partners B > A at d, tiles of A's proxies
+        const double cap = cost_cap(L.tc[CC], L.sc[CC], [&](int64_t e, int64_t a, int64_t b) {
+            const double np = (double)cube(L.deg[CC].empty() ? degree : (int)L.deg[CC][e]);
+            return a != b ? 0.5 * np * np : 0.0;
+        });
+        // per (cluster A, degree d): the partners B > A at d, tiles of A's
+        // proxies, as many partners per item as the cap allows
         std::vector<SymBlock> blks(nblk);
         parallel_run(nblk, [&](int64_t bi) {
             SymBlock& B = blks[bi];
@@ -732,9 +806,14 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
                     B.evals += 2.0 * (double)np * (double)np * (double)(ee - eb);
                     for (int64_t lb = 0; lb < np; lb += kTile) {
                         const int64_t ln = std::min<int64_t>(kTile, np - lb);
-                        B.items.push_back({(double)np * (double)(ee - eb) * (double)ln,
-                                           Item{(int32_t)lb, (int32_t)ln, (int32_t)eb, (int32_t)ee, (int32_t)a,
-                                                (int32_t)d, (int32_t)a}});
+                        const int64_t n = std::max<int64_t>(1, std::min<int64_t>(
+                            ee - eb, (int64_t)std::ceil(std::min((double)(np * (ee - eb) * ln) / cap, 1e9))));
+                        for (int64_t c = 0; c < n; ++c) {
+                            const int64_t e0 = eb + (ee - eb) * c / n, e1 = eb + (ee - eb) * (c + 1) / n;
+                            B.items.push_back({(double)np * (double)(e1 - e0) * (double)ln,
+                                               Item{(int32_t)lb, (int32_t)ln, (int32_t)e0, (int32_t)e1, (int32_t)a,
+                                                    (int32_t)d, (int32_t)a}});
+                        }
                     }
                 }
             }

@@ -1,0 +1,123 @@
+// Host check of how a pass's work is cut into items (ItemCut in engine.hpp), no
+// GPU: whatever the cut, every target must meet exactly the sources it met
+// before, through the items' own slots and the fold; no item may be empty; and
+// an item holds at most the sources the cut allows.  Exits non-zero on a failed
+// check.
+#include <cstdio>
+#include <map>
+#include <random>
+#include <vector>
+
+#include "../../paper_2012_06925_amd/csrc/engine.hpp"
+
+using namespace bldtt;
+
+namespace {
+
+int failures = 0;
+
+void check(bool ok, const char* what, long long a = 0, long long b = 0) {
+    if (!ok) {
+        std::fprintf(stderr, "FAILED: %s (%lld, %lld)\n", what, a, b);
+        ++failures;
+    }
+}
+
+int64_t cube3(int d) { return (int64_t)(d + 1) * (d + 1) * (d + 1); }
+
+// Sum over the sources each output meets of the source's weight (its position
+// + 1): equal sums for the same sources, and a missing or doubled one shows.
+double weight(int64_t pos) { return (double)(pos + 1); }
+
+struct Made {
+    std::vector<double> out;        // per particle, or per cluster and proxy
+    int64_t items = 0, most = 0;    // items, sources of the largest
+};
+
+Made apply(const Tree& T, const std::vector<Item>& items, const std::vector<Entry>& entries, bool proxies, int degree,
+           const SymFold& f) {
+    Made m;
+    const int64_t P = cube3(degree);
+    m.out.assign(proxies ? T.size() * P : T.n_particles, 0.0);
+    m.items = (int64_t)items.size();
+    std::vector<double> slots(f.nslots, 0.0);
+    std::vector<int> written(f.nslots, 0);
+    for (size_t i = 0; i < items.size(); ++i) {
+        const Item& it = items[i];
+        int64_t o = f.ibase[i];
+        double src = 0.0, tgt = 0.0;
+        int64_t n = 0;
+        for (int32_t e = it.eb; e < it.ee; ++e) {
+            const int64_t c = proxies ? P : (entries[e].b & kCountMask);
+            for (int64_t k = 0; k < c; ++k) src += weight(proxies ? entries[e].a * P + k : entries[e].a + k);
+            n += c;
+        }
+        check(n > 0 && it.tn > 0, "empty item", (long long)i, it.tn);
+        m.most = std::max(m.most, n);
+        for (int32_t r = 0; r < it.tn; ++r) tgt += weight(proxies ? (int64_t)it.cluster * P + it.t0 + r : it.t0 + r);
+        for (int32_t r = 0; r < it.tn; ++r, ++o) {
+            slots[o] = src;
+            written[o]++;
+        }
+        for (int64_t k = 0; k < n; ++k, ++o) {
+            slots[o] = tgt;
+            written[o]++;
+        }
+    }
+    for (int64_t k = 0; k < f.nslots; ++k) check(written[k] == 1, "slot written once", k, written[k]);
+    for (const FoldSeg& sg : f.segs)
+        for (int32_t q = sg.pb; q < sg.pe; ++q)
+            for (int32_t k = 0; k < f.parts[q].len; ++k) m.out[sg.off + f.parts[q].lo + k] += slots[f.parts[q].slot + k];
+    return m;
+}
+
+void run(int64_t n, int64_t leaf, int degree, double theta, bool gauss, bool separate_guarded, int tile, ItemCut cut) {
+    std::mt19937_64 rng(n * 31 + leaf);
+    std::uniform_real_distribution<double> u(-1.0, 1.0);
+    std::normal_distribution<double> g(0.0, 0.25);
+    std::vector<double> x[3], s[3];
+    for (auto& v : x) {
+        v.resize(n);
+        for (double& a : v) a = gauss ? g(rng) : u(rng);
+    }
+    Tree T;
+    build_tree(n, x[0].data(), x[1].data(), x[2].data(), leaf, T, s[0], s[1], s[2]);
+    Lists L, rest, rest0;
+    traverse(T, T, theta, degree, kSchemeDtt, L);
+    SymWork whole, parts;
+    whole.guard_near = parts.guard_near = separate_guarded;
+    split_symmetric(T, L, degree, true, true, rest0, whole, {}, separate_guarded, false, tile);
+    split_symmetric(T, L, degree, true, true, rest, parts, {}, separate_guarded, false, tile, cut);
+    for (SymWork* w : {&whole, &parts}) fold_parts(T, w->pp_items, w->pp_entries, false, w->pp_fold);
+    check(whole.pp_evaluations == parts.pp_evaluations && whole.cc_evaluations == parts.cc_evaluations, "terms");
+    for (int k = 0; k < 4; ++k) check(rest.tc[k] == rest0.tc[k] && rest.sc[k] == rest0.sc[k], "rest lists", k);
+    const Made a = apply(T, whole.pp_items, whole.pp_entries, false, degree, whole.pp_fold);
+    const Made b = apply(T, parts.pp_items, parts.pp_entries, false, degree, parts.pp_fold);
+    const Made c = apply(T, whole.cc_items, whole.cc_entries, true, degree, whole.cc_fold);
+    const Made d = apply(T, parts.cc_items, parts.cc_entries, true, degree, parts.cc_fold);
+    check(a.out == b.out, "particle sums of the cut items");
+    check(c.out == d.out, "proxy sums of the cut items");
+    for (size_t i = 0; i < parts.pp_items.size(); ++i) {       // guarded ranges stay apart from plain ones
+        const Item& it = parts.pp_items[i];
+        for (int32_t e = it.eb; e < it.ee && separate_guarded; ++e)
+            check(((uint32_t)parts.pp_entries[e].b >> 29 == SRC_RANGE_GUARD) == ((int64_t)i >= parts.pp_plain), "guard", (long long)i);
+    }
+    std::printf("n %lld leaf %lld: PP %lld -> %lld items (most sources %lld -> %lld), CC %lld -> %lld\n", (long long)n,
+                (long long)leaf, (long long)a.items, (long long)b.items, (long long)a.most, (long long)b.most,
+                (long long)c.items, (long long)d.items);
+    check(b.items >= a.items && d.items >= c.items, "a cut makes items, never fewer", b.items, a.items);
+}
+
+}  // namespace
+
+int main() {
+    for (bool guarded : {false, true}) {
+        run(4000, 60, 2, 0.7, false, guarded, 256, ItemCut{4096, 256});
+        run(6000, 700, 3, 0.8, true, guarded, 256, ItemCut{100, 256});
+        run(9000, 300, 2, 0.9, false, guarded, 512, ItemCut{1000000, 1});
+        run(5000, 2000, 4, 0.8, true, guarded, 1024, ItemCut{64, 512});
+        run(300, 500, 3, 0.7, false, guarded, 256, ItemCut{4096, 256});
+    }
+    if (failures) std::fprintf(stderr, "%d check(s) failed\n", failures);
+    return failures != 0;
+}
