@@ -132,20 +132,35 @@ __global__ __launch_bounds__(kBlock) void k_sym(const DevItem* __restrict__ item
 }
 
 // ---------------------------------------------------------------------------
-// Fold of a deterministic symmetric pass (fold.hpp): a work group takes 64
-// outputs of a segment (blockIdx.x the segment, y the 64), each of its four
-// waves every fourth batch of eight parts, and the waves' sums are added in
-// wave order: the same order of the same terms every time.  A fold waits on
-// memory (each part is one load per output, slots written by other CUs), so the
-// loads in flight count: one group per segment with its threads across the
-// outputs left 140 us for 137 leaves, 0.24 ms for 582 and 0.94 ms for 8192.
+// Folds of a deterministic symmetric pass (fold.hpp): each output adds its parts
+// in an order of their own that never changes.  A fold waits on memory (each
+// part is one load per output, from slots written by other CUs).
+//
+// k_sym_fold: one work group per segment, parts in their stored order; for folds
+// of many segments (kFoldManySegments), which fill the GPU that way.
+// k_sym_fold64: a work group takes 64 outputs of a segment (blockIdx.x the
+// segment, y the 64), each of its four waves every fourth batch of eight parts,
+// and the waves' sums are added in wave order.  Few segments give few groups, and
+// then the loads in flight count: 137 leaves 140 -> 27 us, 582 leaves 0.24 ->
+// 0.20 ms; but 8192 leaves 0.94 -> 1.22 ms (shorter runs of addresses per group).
 // ---------------------------------------------------------------------------
-constexpr int kFoldOutputs = 64;
+constexpr int kFoldManySegments = 2048;
 
 __global__ __launch_bounds__(kBlock) void k_sym_fold(const FoldSeg* __restrict__ segs,
                                                      const FoldPart* __restrict__ parts,
                                                      const double* __restrict__ slots, double* __restrict__ phi,
                                                      DegOut phihat) {
+    __shared__ FoldPart lp[kFoldLdsParts];
+    const FoldSeg sg = segs[blockIdx.x];
+    fold_body(sg, parts, slots, (sg.deg < 0 ? phi : phihat.p[sg.deg]) + sg.off, 0, sg.n, lp);
+}
+
+constexpr int kFoldOutputs = 64;
+
+__global__ __launch_bounds__(kBlock) void k_sym_fold64(const FoldSeg* __restrict__ segs,
+                                                       const FoldPart* __restrict__ parts,
+                                                       const double* __restrict__ slots, double* __restrict__ phi,
+                                                       DegOut phihat) {
     constexpr int U = 8;
     __shared__ double red[3][kFoldOutputs];
     const FoldSeg sg = segs[blockIdx.x];
@@ -1073,7 +1088,10 @@ void launch_sym_fold(const FoldSeg* segs, int n_segs, int max_n, const FoldPart*
                      double* phi, DegOut phihat, hipStream_t st) {
     if (n_segs <= 0 || max_n <= 0) return;
     const unsigned ny = (unsigned)std::min((max_n + kFoldOutputs - 1) / kFoldOutputs, 1024);
-    hipLaunchKernelGGL(k_sym_fold, dim3(n_segs, ny), dim3(kBlock), 0, st, segs, parts, slots, phi, phihat);
+    if (n_segs >= kFoldManySegments)
+        hipLaunchKernelGGL(k_sym_fold, dim3(n_segs), dim3(kBlock), 0, st, segs, parts, slots, phi, phihat);
+    else
+        hipLaunchKernelGGL(k_sym_fold64, dim3(n_segs, ny), dim3(kBlock), 0, st, segs, parts, slots, phi, phihat);
     CHECK_LAUNCH();
 }
 
