@@ -361,6 +361,14 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
     // 1E4 particles (leaf 500) 345 us with 62 items, 37 us with 1023; 1E5 Gaussian
     // particles 2.85 -> 1.7 ms; at 1E6 and more one item per tile is as good.
     const ItemCut sym_cut{16 * (int64_t)std::max(1, pl->cus), 256};
+    // PC pairs listed with their mirror CP pair are evaluated once for both as
+    // well (FP64), while their source slots, a proxy grid per pair and tile, stay
+    // below 4 GiB; beyond that (or where there are none) they stay one-way.  1E5
+    // Gaussian particles, n 8, leaf 2000: 1.6 + 1.0 ms one-way, 0.6 ms both ways.
+    auto pc_both_ways = [&](const Lists& L) {
+        return !fp32 && !L.tc[PC].empty() && !L.tc[CP].empty() &&
+               pc_source_slots(T, L, pl->degree, sym_tile) <= (double)((int64_t)4 << 30) / sizeof(double);
+    };
     auto particle_pass = [&](const DevBuf& items, int n, const DevBuf& entries, bool add, hipStream_t s) {
         if (mfma_pp)
             launch_pp_mfma(items.as<DevItem>(), n, entries.as<int2>(), pl->dtgt(), dT, pl->dsrc(), dS, tab,
@@ -383,6 +391,11 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
     };
     auto sym_pp_fold = [&](hipStream_t s) {
         const DevFold& f = pl->fold_pp;
+        launch_sym_fold(f.segs.as<FoldSeg>(), f.n_segs, f.max_n, f.parts.as<FoldPart>(), f.slots.as<double>(),
+                        pl->phi_tree.as<double>(), DegOut{}, s);
+    };
+    auto sym_pc_fold = [&](hipStream_t s) {
+        const DevFold& f = pl->fold_pc;
         launch_sym_fold(f.segs.as<FoldSeg>(), f.n_segs, f.max_n, f.parts.as<FoldPart>(), f.slots.as<double>(),
                         pl->phi_tree.as<double>(), DegOut{}, s);
     };
@@ -514,11 +527,13 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
         }
     }
     Lists& rest = pl->rest_lists;       // the lists without their symmetric pairs
+    bool sym_pc = false;                // the symmetric pairs hold PC/CP pairs
     if (symm && !varied) {
         // the near-field symmetric pass (the longest) is enqueued as soon as its
         // items are packed, and the rest is packed while it runs; it writes
         // only its slots, so it may run before the passes that write phi_tree
         // (its fold keeps its place after them)
+        sym_pc = pc_both_ways(pl->lists);
         split_symmetric(T, pl->lists, pl->degree, true, true, rest, pl->sym, [&] {
             Upload us;
             us.add(pl->sym_items, pl->sym.pp_items).add(pl->sym_entries, pl->sym.pp_entries);
@@ -527,11 +542,15 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
             PhaseMark mark(pl, BLDTT_PH_PP_SYM, st);
             sym_pp_pass(pl->sym_items, pl->sym_entries, pl->sym, st);
             mark_host(2);
-        }, sep_guard, false, sym_tile, sym_cut);
+        }, sep_guard, sym_pc, sym_tile, sym_cut);
         fold_parts(T, pl->sym.pp_items, pl->sym.pp_entries, false, pl->sym.pp_fold);
         drop_self_pairs(rest);
     }
-    if (symm && varied) split_symmetric(T, sep, pl->degree, false, true, rest, pl->sym_sep, {}, sep_guard, false, sym_tile, sym_cut);
+    if (symm && varied) {
+        sym_pc = pc_both_ways(sep);
+        split_symmetric(T, sep, pl->degree, false, true, rest, pl->sym_sep, {}, sep_guard, sym_pc, sym_tile, sym_cut);
+    }
+    if (sym_pc) build_pc_folds(T, varied ? pl->sym_sep : pl->sym);
     const SymWork& scc = varied ? pl->sym_sep : pl->sym;          // symmetric CC pairs
     std::vector<uint32_t> scc_deg;
     if (symm) scc_deg = sym_cc_degrees(T, scc);
@@ -552,6 +571,10 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
         pl->stats.interactions[k] = w.interactions[k] + (varied ? pl->work_near.interactions[k] : 0.0);
     pl->stats.interactions[PP] += sym_w + self_w;
     pl->stats.interactions[CC] += sym_c;
+    if (sym_pc) {                       // each value serves one PC and one CP term
+        pl->stats.interactions[PC] += 0.5 * scc.pc_evaluations;
+        pl->stats.interactions[CP] += 0.5 * scc.pc_evaluations;
+    }
     const double pass_w = w.interactions[PP] + w.interactions[PC];
     pl->stats.pass_interactions[0] = varied ? pl->work_near.interactions[PP] : pass_w;
     pl->stats.pass_interactions[1] = varied ? pass_w : 0.0;
@@ -569,6 +592,11 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
         up.add(pl->sym_cc_items, scc.cc_items).add(pl->sym_cc_entries, scc.cc_entries);
         add_bases(up, pl->fold_cc, scc.cc_fold);
         add_parts(up, pl->fold_cc, scc.cc_fold);
+    }
+    if (sym_pc) {
+        up.add(pl->sym_pc_items, scc.pc_items).add(pl->sym_pc_entries, scc.pc_entries).add(pl->sym_pc_sbase, scc.pc_sbase);
+        add_bases(up, pl->fold_pc, scc.pc_fold);
+        add_parts(up, pl->fold_pc, scc.pc_fold);
     }
     up.run(pl->staging, pl->arena, pl->staging_free, st);
 
@@ -598,6 +626,10 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
             launch_sym(ks, fp32, pl->mfma_transfer(), true, false, pl->sym_cc_items.as<DevItem>(), (int)scc.cc_items.size(),
                        pl->sym_cc_entries.as<int2>(), pl->dsrc(), dS, tab, deg_ptrs(pl->qhat_deg), nullptr, f.out(),
                        st);
+            if (sym_pc)         // their particle sums are folded with the particle passes below
+                launch_sym_pc(ks, pl->sym_pc_items.as<DevItem>(), (int)scc.pc_items.size(),
+                              pl->sym_pc_entries.as<int2>(), pl->dsrc(), dS, tab, deg_ptrs(pl->qhat_deg),
+                              pl->fold_pc.out(), SymSlots{f.slots.as<double>(), pl->sym_pc_sbase.as<int64_t>()}, st);
             launch_sym_fold(f.segs.as<FoldSeg>(), f.n_segs, f.max_n, f.parts.as<FoldPart>(), f.slots.as<double>(), nullptr,
                             deg_out(pl->phihat_deg), st);
         }
@@ -621,6 +653,7 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
             else particle_pass(pl->pitems, (int)w.pitems.size(), pl->pentries, false, st);
         }
         if (symm) sym_pp_fold(st);          // its pass was enqueued after the traversal
+        if (sym_pc) sym_pc_fold(st);
     } else {
         // the symmetric near-field pairs' fold: its parts are built now, while
         // the passes run, and it follows the near-field passes (the side
@@ -633,6 +666,7 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
         }
         HIPCHK(hipStreamWaitEvent(st, pl->ev_near_done, 0));
         if (symm) sym_pp_fold(st);
+        if (sym_pc) sym_pc_fold(st);
         PhaseMark mark(pl, BLDTT_PH_PPPC_SEP, st);
         particle_pass(pl->sep_items, (int)sep_items.size(), pl->pentries, true, st);
     }

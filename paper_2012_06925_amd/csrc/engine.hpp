@@ -248,6 +248,8 @@ struct SymWork {
     std::vector<Entry> pp_entries, cc_entries, pc_entries;
     std::vector<Item> pp_items, cc_items, pc_items;
     SymFold pp_fold, cc_fold;
+    SymFold pc_fold;                            // build_pc_folds: the particle side of the PC/CP items
+    std::vector<int64_t> pc_sbase;              // and the slot base of each one's sources in cc_fold
     int64_t pp_plain = 0;
     double pp_evaluations = 0.0, cc_evaluations = 0.0, pc_evaluations = 0.0;
     bool guard_near = false;                    // setting, as Work::guard_near
@@ -262,13 +264,20 @@ struct SymWork {
         pp_evaluations = cc_evaluations = pc_evaluations = 0.0;
         pp_fold.clear();
         cc_fold.clear();
+        pc_fold.clear();
+        pc_sbase.clear();
     }
 };
+// The folds of a SymWork with PC/CP items: cc_fold holds the CC items, then the
+// sources of the PC/CP items; pc_fold the targets of the PC/CP items.
+void build_pc_folds(const Tree& T, SymWork& sw);
+// At most how many slots the sources of the PC/CP items of L's pairs take.
+double pc_source_slots(const Tree& T, const Lists& L, int degree, int tile);
 // pp_ready, when given, is called as soon as the PP items and their slot bases
 // are complete (before `rest` and the CC items are formed), so their pass can
 // start early.  The PP fold's parts are left to the caller (fold_parts: the
 // fold runs after the pass, so they can be built while it runs); the CC
-// fold is built whole.
+// fold is built whole (with pc it is left to build_pc_folds).
 // With pc, a PC pair (A, B) whose mirror CP pair (B, A) is listed at the same
 // degree is evaluated once for both too (A's particles against B's proxies,
 // which are the same points as target and as source): pc_items are tiles of

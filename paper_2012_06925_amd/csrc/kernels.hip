@@ -131,6 +131,25 @@ __global__ __launch_bounds__(kBlock) void k_sym(const DevItem* __restrict__ item
     }
 }
 
+// PC pairs with their mirror CP pairs (FP64): particle tiles against the
+// partners' proxy grids, once for both; the tile's sums and the proxies' partials
+// go to slots of two folds.
+template <int KIND>
+__global__ __launch_bounds__(kBlock) void k_sym_pc(const DevItem* __restrict__ items, const int2* __restrict__ entries,
+                                                   DevParticles p, DevTree T, const double* __restrict__ tab,
+                                                   DegPtrs qhat, double param, SymSlots tgt, SymSlots src) {
+    __shared__ double4 pool[(sym_lds_bytes<false>() + 31) / 32];
+    const DevItem it = items[blockIdx.x];
+    const int64_t tb = tgt.ibase[blockIdx.x], sb = src.ibase[blockIdx.x];
+    auto body = [&](auto h) {
+        sym_body<false, false, decltype(h)::value, true, KIND>(it, entries, p, T, tab, qhat, pool, nullptr, tgt.slots, tb,
+                                                               src.slots, sb, param);
+    };
+    if (KIND == K_COULOMB && it.tn > 128) body(std::integral_constant<int, 4>{});
+    else if (it.tn > 64) body(std::integral_constant<int, 2>{});
+    else body(std::integral_constant<int, 1>{});
+}
+
 // ---------------------------------------------------------------------------
 // Folds of a deterministic symmetric pass (fold.hpp): each output adds its parts
 // in an order of their own that never changes.  A fold waits on memory (each
@@ -1081,6 +1100,23 @@ void launch_sym(KernelSpec k, bool fp32, bool mfma, bool proxies, bool guarded, 
     }
 #undef LAUNCH_SYM64
 #undef LAUNCH_SYM
+    CHECK_LAUNCH();
+}
+
+void launch_sym_pc(KernelSpec k, const DevItem* items, int n_items, const int2* entries, DevParticles p, DevTree T,
+                   const double* tab, DegPtrs qhat, SymSlots tgt, SymSlots src, hipStream_t st) {
+    if (n_items <= 0) return;
+    if (!tgt.slots || !tgt.ibase || !src.slots || !src.ibase) throw Error(-1, "symmetric pass without slots");
+#define LAUNCH_PC(KK) hipLaunchKernelGGL((k_sym_pc<KK>), dim3(n_items), dim3(kBlock), 0, st, items, entries, p, T, tab, \
+                                         qhat, k.param, tgt, src)
+    switch (k.kind) {
+    case K_COULOMB: LAUNCH_PC(K_COULOMB); break;
+    case K_YUKAWA: LAUNCH_PC(K_YUKAWA); break;
+    case K_OSC: LAUNCH_PC(K_OSC); break;
+    case K_REG: LAUNCH_PC(K_REG); break;
+    default: throw Error(-1, "no symmetric pass for this kernel");
+    }
+#undef LAUNCH_PC
     CHECK_LAUNCH();
 }
 

@@ -95,6 +95,12 @@ void launch_sym(KernelSpec k, bool fp32, bool mfma, bool proxies, bool guarded, 
                 const int2* entries, DevParticles p, DevTree T, const double* tab, DegPtrs qhat, double* nfp64,
                 SymSlots out, hipStream_t st);
 
+// PC pairs with their mirror CP pairs, each kernel value once for both (FP64):
+// items are particle tiles of a cluster with proxy entries of degree
+// item.degree; item i's target sums go to tgt, its source partials to src.
+void launch_sym_pc(KernelSpec k, const DevItem* items, int n_items, const int2* entries, DevParticles p, DevTree T,
+                   const double* tab, DegPtrs qhat, SymSlots tgt, SymSlots src, hipStream_t st);
+
 // out[k] += the parts of every segment (fold.hpp; max_n: the outputs of the largest):
 // phi (tree order) for particle segments, phihat.p[degree] for proxy ones,
 // which already hold the other terms.

@@ -284,9 +284,10 @@ struct bldtt_plan {
     int n_self_items = 0, n_self_sym_items = 0;
     bool self_ready = false;
     double self_evaluations = 0.0;
-    DevBuf sym_items, sym_entries, sym_cc_items, sym_cc_entries;
-    // folds of the symmetric passes: the main PP pass, the CC pass, the leaves' self pairs
-    DevFold fold_pp, fold_cc, fold_self;
+    DevBuf sym_items, sym_entries, sym_cc_items, sym_cc_entries, sym_pc_items, sym_pc_entries, sym_pc_sbase;
+    // folds of the symmetric passes: the main PP pass, the CC pass (and the proxy
+    // side of the PC/CP pass), the leaves' self pairs, the particle side of the PC/CP pass
+    DevFold fold_pp, fold_cc, fold_self, fold_pc;
     DevBuf model_buf;                        // device copy of the degree model (policy.dev_model)
     // FP32 evaluation: pairs of distinct points the last compute evaluated in
     // FP64 because FP32 coordinates do not resolve them (one device double)

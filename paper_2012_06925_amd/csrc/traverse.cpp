@@ -819,9 +819,12 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
             }
         });
         gather(blks, sw.cc_entries, sw.cc_items, sw.cc_evaluations);
-        build_fold(T, sw.cc_items, sw.cc_entries, true, sw.cc_fold);
+        if (!pc) build_fold(T, sw.cc_items, sw.cc_entries, true, sw.cc_fold);
     }
     if (pc) {
+        const double cap = cost_cap(L.tc[PC], L.sc[PC], [&](int64_t e, int64_t a, int64_t) {
+            return (double)T.count[a] * (double)cube(L.deg[PC].empty() ? degree : (int)L.deg[PC][e]);
+        });
         // per (cluster A, degree d): the partners B whose PC and CP pairs with A
         // are both listed at d, as proxy entries; tiles of A's particles
         std::vector<SymBlock> blks(nblk);
@@ -844,8 +847,14 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
                     B.evals += 2.0 * (double)T.count[a] * np;
                     for (int64_t tb = T.begin[a]; tb < T.begin[a] + T.count[a]; tb += kTile) {
                         const int64_t tn = std::min<int64_t>(kTile, T.begin[a] + T.count[a] - tb);
-                        B.items.push_back({np * (double)tn, Item{(int32_t)tb, (int32_t)tn, (int32_t)eb, (int32_t)ee,
-                                                                 (int32_t)a, (int32_t)d, (int32_t)tb}});
+                        const int64_t n = std::max<int64_t>(
+                            1, std::min<int64_t>(ee - eb, (int64_t)std::ceil(std::min(np * (double)tn / cap, 1e9))));
+                        for (int64_t c = 0; c < n; ++c) {
+                            const int64_t e0 = eb + (ee - eb) * c / n, e1 = eb + (ee - eb) * (c + 1) / n;
+                            B.items.push_back({(double)cube(d) * (double)(e1 - e0) * (double)tn,
+                                               Item{(int32_t)tb, (int32_t)tn, (int32_t)e0, (int32_t)e1, (int32_t)a,
+                                                    (int32_t)d, (int32_t)tb}});
+                        }
                     }
                 }
             }
@@ -998,6 +1007,31 @@ void fold_group_parts(const Tree& T, bool proxies, const std::vector<FoldGroup>&
         for (int64_t i = k * per; i < std::min(ni, (k + 1) * per); ++i)
             emit(i, [&](int32_t sg, const FoldPart& pt) { f.parts[fill[sg]++] = pt; });
     });
+}
+
+void build_pc_folds(const Tree& T, SymWork& sw) {
+    std::vector<std::vector<int64_t>> pb, cb;
+    const std::vector<FoldGroup> pg{{&sw.pc_items, &sw.pc_entries, FoldGroup::kParticleTargets}};
+    const std::vector<FoldGroup> cg{{&sw.cc_items, &sw.cc_entries, FoldGroup::kProxyBoth},
+                                    {&sw.pc_items, &sw.pc_entries, FoldGroup::kProxySources}};
+    sw.pc_fold.clear();
+    sw.cc_fold.clear();
+    sw.pc_fold.nslots = fold_group_bases(pg, pb);
+    sw.cc_fold.nslots = fold_group_bases(cg, cb);
+    fold_group_parts(T, false, pg, pb, sw.pc_fold);
+    fold_group_parts(T, true, cg, cb, sw.cc_fold);
+    sw.pc_fold.ibase = std::move(pb[0]);
+    sw.cc_fold.ibase = std::move(cb[0]);
+    sw.pc_sbase = std::move(cb[1]);
+}
+
+double pc_source_slots(const Tree& T, const Lists& L, int degree, int tile) {
+    double n = 0.0;
+    for (size_t e = 0; e < L.tc[PC].size(); ++e) {
+        const double P = (double)cube(L.deg[PC].empty() ? degree : (int)L.deg[PC][e]);
+        n += P * (double)((T.count[L.tc[PC][e]] + tile - 1) / tile);
+    }
+    return n;
 }
 
 void fold_bases(const std::vector<Item>& items, const std::vector<Entry>& entries, bool proxies, SymFold& f) {

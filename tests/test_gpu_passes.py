@@ -67,3 +67,26 @@ def test_padding_unsafe_problems_stay_one_sided(kernel, param, shift):
     ref = _computes(one, 1)[0]
     one.close()
     assert np.all(np.isfinite(ref)) and np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("kernel", ["coulomb", "yukawa", "oscillatory", "regcoulomb"])
+@pytest.mark.parametrize("n,leaf,degree", [(6000, 50, 3), (9001, 120, 5), (12000, 300, 6)])
+def test_mirrored_pc_cp_pairs_once_for_both(kernel, n, leaf, degree):
+    # leaves smaller than the proxy grids: PC pairs and their CP mirrors, tiles
+    # of one wave, of two and of four targets per lane
+    p = inputs.particles(n, "gaussian", seed=73)
+    kw = dict(kernel=kernel, theta=0.8, degree=degree, leaf=leaf)
+    plan = _plan(p, **kw)
+    a, b = _computes(plan)
+    st = plan.stats()
+    plan.close()
+    one = _plan(p, flags=_lib.ONE_SIDED_PP, **kw)
+    c = _computes(one, 1)[0]
+    st1 = one.stats()
+    one.close()
+    assert st["n_entries"]["PC"] > 0 and st["interactions"] == st1["interactions"]
+    assert st["pass_interactions"][0] < 0.5 * st1["interactions"]["PC"]      # few PC pairs left one-way
+    assert np.array_equal(a, b)
+    ref = core.bldtt(p, p, **kw)
+    _close(a, ref)
+    _close(c, ref)
