@@ -78,14 +78,21 @@ def test_mirrored_pc_cp_pairs_once_for_both(kernel, n, leaf, degree):
     kw = dict(kernel=kernel, theta=0.8, degree=degree, leaf=leaf)
     plan = _plan(p, **kw)
     a, b = _computes(plan)
-    st = plan.stats()
+    st, lists, tree = plan.stats(), plan.lists(), plan.tree()
     plan.close()
     one = _plan(p, flags=_lib.ONE_SIDED_PP, **kw)
     c = _computes(one, 1)[0]
     st1 = one.stats()
     one.close()
     assert st["n_entries"]["PC"] > 0 and st["interactions"] == st1["interactions"]
-    assert st["pass_interactions"][0] < 0.5 * st1["interactions"]["PC"]      # few PC pairs left one-way
+    # what the one-way particle pass keeps: PC pairs without a mirror, PP pairs
+    # of which one side is no leaf or that are listed one way
+    n, is_leaf, P = tree["count"], tree["nchild"] == 0, (degree + 1) ** 3
+    pairs = {k: set(zip(*(v.tolist() for v in lists[k]))) for k in ("PP", "PC", "CP")}
+    left = sum(int(n[a]) * P for a, b in pairs["PC"] if (b, a) not in pairs["CP"])
+    left += sum(int(n[a]) * int(n[b]) for a, b in pairs["PP"]
+                if a != b and not (is_leaf[a] and is_leaf[b] and (b, a) in pairs["PP"]))
+    assert st["pass_interactions"][0] == left < st1["interactions"]["PC"] + st1["interactions"]["PP"]
     assert np.array_equal(a, b)
     ref = core.bldtt(p, p, **kw)
     _close(a, ref)
