@@ -369,14 +369,9 @@ int bldtt_mlp_loss_grad(const float* model, const float* features, const float* 
     }
     return guarded([&] {
         hipStream_t st = static_cast<hipStream_t>(hip_stream);
-        std::vector<float> t((size_t)n * kNOut);
-        HIPCHK(hipMemcpy(t.data(), targets, sizeof(float) * t.size(), hipMemcpyDeviceToHost));
-        int64_t valid = 0;
-        for (float v : t) valid += !std::isnan(v);
         DevBuf work;
-        work.reserve(sizeof(float) * mlp_work_floats(n));
-        launch_mlp_loss_grad(model, features, targets, n, valid ? 1.f / (float)valid : 0.f, work.as<float>(), grad, loss,
-                             st);
+        work.alloc(sizeof(float) * mlp_work_floats(n));
+        launch_mlp_loss_grad(model, features, targets, n, work.as<float>(), grad, loss, st);
         HIPCHK(hipStreamSynchronize(st));
     });
 }
@@ -404,10 +399,10 @@ int bldtt_mlp_train(const float* features, const float* targets, int64_t n, int3
         init_model(features, n, seed, M);
         const int64_t B = std::min<int64_t>(batch, n);
         const int64_t nb = (n + B - 1) / B;
-        DevBuf d_model, d_grad, d_m, d_v, d_work, d_feat, d_tgt, d_loss;
+        DevBuf d_model, d_m, d_v, d_work, d_feat, d_tgt, d_loss;
         d_model.reserve(sizeof(float) * kNModel);
         HIPCHK(hipMemcpy(d_model.p, M.data(), sizeof(float) * kNModel, hipMemcpyHostToDevice));
-        for (DevBuf* b : {&d_grad, &d_m, &d_v}) {
+        for (DevBuf* b : {&d_m, &d_v}) {
             b->reserve(sizeof(float) * kNParams);
             HIPCHK(hipMemset(b->p, 0, sizeof(float) * kNParams));
         }
@@ -419,7 +414,6 @@ int bldtt_mlp_train(const float* features, const float* targets, int64_t n, int3
         std::iota(perm.begin(), perm.end(), 0);
         std::mt19937_64 rng(seed ^ 0x9e3779b97f4a7c15ull);
         std::vector<float> pf((size_t)kNIn * n), pt((size_t)kNOut * n), bl(nb);
-        std::vector<float> inv(nb);
         int step = 0;
         for (int ep = 0; ep < epochs; ++ep) {
             std::shuffle(perm.begin(), perm.end(), rng);
@@ -427,19 +421,13 @@ int bldtt_mlp_train(const float* features, const float* targets, int64_t n, int3
                 std::memcpy(&pf[kNIn * i], &features[kNIn * perm[i]], sizeof(float) * kNIn);
                 std::memcpy(&pt[kNOut * i], &targets[kNOut * perm[i]], sizeof(float) * kNOut);
             }
-            for (int64_t b = 0; b < nb; ++b) {
-                int64_t v = 0;
-                for (int64_t i = b * B * kNOut; i < std::min(n, (b + 1) * B) * kNOut; ++i) v += !std::isnan(pt[i]);
-                inv[b] = v ? 1.f / (float)v : 0.f;
-            }
             HIPCHK(hipMemcpyAsync(d_feat.p, pf.data(), sizeof(float) * pf.size(), hipMemcpyHostToDevice, st));
             HIPCHK(hipMemcpyAsync(d_tgt.p, pt.data(), sizeof(float) * pt.size(), hipMemcpyHostToDevice, st));
             for (int64_t b = 0; b < nb; ++b) {
                 const int64_t b0 = b * B, nbat = std::min(B, n - b0);
-                launch_mlp_loss_grad(d_model.as<float>(), d_feat.as<float>() + kNIn * b0, d_tgt.as<float>() + kNOut * b0,
-                                     nbat, inv[b], d_work.as<float>(), d_grad.as<float>(), d_loss.as<float>() + b, st);
-                launch_adam(d_model.as<float>(), d_grad.as<float>(), d_m.as<float>(), d_v.as<float>(), kNParams, lr, 0.9f,
-                            0.999f, 1e-8f, ++step, st);
+                launch_mlp_step(d_model.as<float>(), d_feat.as<float>() + kNIn * b0, d_tgt.as<float>() + kNOut * b0, nbat,
+                                d_work.as<float>(), d_loss.as<float>() + b, d_m.as<float>(), d_v.as<float>(), lr, 0.9f,
+                                0.999f, 1e-8f, ++step, st);
             }
             HIPCHK(hipMemcpyAsync(bl.data(), d_loss.p, sizeof(float) * nb, hipMemcpyDeviceToHost, st));
             HIPCHK(hipStreamSynchronize(st));

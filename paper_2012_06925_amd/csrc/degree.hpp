@@ -47,14 +47,15 @@ void pair_features(double rt, double rs, double R, int64_t ct, int64_t cs, float
 void launch_mlp_select(const float* model, const float* feats, const int64_t* counts, int64_t n, float log_tau,
                        int fallback, int pp_cc_only, uint8_t* choice, hipStream_t st);
 void launch_mlp_forward(const float* model, const float* feats, int64_t n, float* out, hipStream_t st);
-// One training step on a batch of n samples: loss = sum of squared errors over
-// the valid targets times inv_valid (NaN targets are ignored), and the gradient
-// of that loss with respect to every parameter into grad.  work holds
+// Loss and gradient of a batch of n samples: loss = sum of squared errors over the
+// valid targets divided by their number (NaN targets are ignored), and the
+// gradient of that loss with respect to every parameter into grad.  work holds
 // mlp_work_floats(n) floats.
-void launch_mlp_loss_grad(const float* model, const float* feats, const float* targets, int64_t n, float inv_valid,
-                          float* work, float* grad, float* loss, hipStream_t st);
-void launch_adam(float* params, const float* grad, float* m, float* v, int n, float lr, float b1, float b2, float eps,
-                 int step, hipStream_t st);
+void launch_mlp_loss_grad(const float* model, const float* feats, const float* targets, int64_t n, float* work,
+                          float* grad, float* loss, hipStream_t st);
+// The same followed by an Adam step (the step-th) on the model's parameters.
+void launch_mlp_step(float* model, const float* feats, const float* targets, int64_t n, float* work, float* loss, float* m,
+                     float* v, float lr, float b1, float b2, float eps, int step, hipStream_t st);
 int64_t mlp_work_floats(int64_t batch);
 // The same loss and gradient with the work memory in the library's static
 // device array (no allocation): n in [1, mlp_noalloc_max_samples()].

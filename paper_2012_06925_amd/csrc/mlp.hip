@@ -5,6 +5,7 @@
 // log10 pair error at degrees 2..12), FP32.  Parameter layout in degree.hpp.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <mutex>
@@ -50,9 +51,8 @@ __device__ __forceinline__ const float* stage_model(const float* __restrict__ M,
     return sM;
 }
 
-// Forward pass of one sample; a1, a2 receive the hidden activations when non-null.
-__device__ __forceinline__ void forward(const float* __restrict__ M, const float* x, float* y, float* a1,
-                                        float* a2) {
+// Forward pass of one sample.
+__device__ __forceinline__ void forward(const float* __restrict__ M, const float* x, float* y) {
     float h1[kNHid];
 #pragma unroll
     for (int o = 0; o < kNHid; ++o) {
@@ -60,7 +60,6 @@ __device__ __forceinline__ void forward(const float* __restrict__ M, const float
 #pragma unroll
         for (int k = 0; k < kNIn; ++k) s = fmaf(M[kOffW1 + o * kNIn + k], x[k], s);
         h1[o] = fast_tanh(s);
-        if (a1) a1[o] = h1[o];
     }
 #pragma unroll
     for (int k = 0; k < kNOut; ++k) y[k] = M[kOffB3 + k];
@@ -69,7 +68,6 @@ __device__ __forceinline__ void forward(const float* __restrict__ M, const float
 #pragma unroll
         for (int i = 0; i < kNHid; ++i) s = fmaf(M[kOffW2 + j * kNHid + i], h1[i], s);
         float a = fast_tanh(s);
-        if (a2) a2[j] = a;
 #pragma unroll
         for (int k = 0; k < kNOut; ++k) y[k] = fmaf(M[kOffW3 + k * kNHid + j], a, y[k]);
     }
@@ -121,7 +119,7 @@ __global__ __launch_bounds__(kBlock) void k_mlp_select(const float* __restrict__
     }
     float x[kNIn], y[kNOut];
     normalise(M, f, x);
-    forward(M, x, y, nullptr, nullptr);
+    forward(M, x, y);
     int best_t = 0, best_d = 0;
     double best = pair_cost(0, ct, cs, 0);
     for (int d = kDegMin; d <= kDegMax; ++d) {
@@ -147,153 +145,236 @@ __global__ __launch_bounds__(kBlock) void k_mlp_forward(const float* __restrict_
 #pragma unroll
     for (int k = 0; k < kNIn; ++k) f[k] = feats[kNIn * p + k];
     normalise(M, f, x);
-    forward(M, x, y, nullptr, nullptr);
+    forward(M, x, y);
 #pragma unroll
     for (int k = 0; k < kNOut; ++k) out[kNOut * p + k] = y[k];
 }
 
-// Work layout per batch of n: X[n][4] A1[n][64] A2[n][64] dY[n][11] dZ2[n][64] dZ1[n][64] sq[n]
-struct WorkView {
-    float *X, *A1, *A2, *dY, *dZ2, *dZ1, *sq;
-    __host__ __device__ WorkView(float* w, int64_t n)
-        : X(w), A1(w + kNIn * n), A2(A1 + kNHid * n), dY(A2 + kNHid * n), dZ2(dY + kNOut * n), dZ1(dZ2 + kNHid * n),
-          sq(dZ1 + kNHid * n) {}
+// ---------------------------------------------------------------------------
+// Loss and gradient of a batch in two launches.
+//
+// k_grad_part: a work group runs forward and backward of kGradSamples samples at
+// a time with the weights and every activation in LDS, and adds the samples'
+// contributions to the 5131 parameters' gradients in its registers (thread
+// (wave w, lane i) owns dW2[16 w .. 16 w + 15][i]), which it writes once at its
+// end.  Wave w holds samples 2 w, 2 w + 1, lane j the hidden unit j; W2 rows are
+// padded to 65 floats, so a row read across lanes and a column read both touch
+// every bank.  k_grad_finish adds the groups' partials in group order and
+// divides by the number of valid targets (and takes the Adam step when asked).
+//
+// Bound by latency: 10 MFLOP at 1024 samples, a few us of dependent LDS reads and
+// barriers per group.  Five kernels before (activations through memory, one
+// thread per parameter over every sample in turn, 260 us of it at 1024
+// samples) took 330 us, these two 15 us: a call 382 -> 49 us.
+// ---------------------------------------------------------------------------
+constexpr int kGradSamples = 8;                        // samples per round of a work group
+constexpr int kGradGroups = 208;                       // work groups at most
+constexpr int kGradPart = kNParams + 2;                // gradient sums, squared errors, valid targets (bits)
+constexpr int kW2Pitch = kNHid + 1;
+
+__global__ __launch_bounds__(kBlock) void k_grad_part(const float* __restrict__ M, const float* __restrict__ feats,
+                                                      const float* __restrict__ tgt, int64_t n,
+                                                      float* __restrict__ part) {
+    constexpr int S = kGradSamples;
+    static_assert(kBlock == 4 * kNHid && S == 8 && kNOut * S <= kBlock, "one wave per two samples, one lane per unit");
+    __shared__ float W1[kNHid * kNIn], B1[kNHid], W2[kNHid * kW2Pitch], B2[kNHid], W3[kNOut * kNHid], B3[kNOut];
+    __shared__ float X[S][kNIn];
+    __shared__ float A1[kNHid][S], A2[kNHid][S], Z2[kNHid][S], Z1[kNHid][S], dY[kNOut][S];
+    __shared__ float red[kBlock];
+    __shared__ unsigned redn[kBlock];
+    const int t = threadIdx.x, wave = t >> 6, j = t & 63;
+    for (int k = t; k < kNHid * kNIn; k += kBlock) W1[k] = M[kOffW1 + k];
+    for (int k = t; k < kNHid * kNHid; k += kBlock) W2[(k >> 6) * kW2Pitch + (k & 63)] = M[kOffW2 + k];
+    for (int k = t; k < kNOut * kNHid; k += kBlock) W3[k] = M[kOffW3 + k];
+    if (t < kNHid) {
+        B1[t] = M[kOffB1 + t];
+        B2[t] = M[kOffB2 + t];
+    }
+    if (t < kNOut) B3[t] = M[kOffB3 + t];
+    float g2[16], g3[3], g1 = 0.f, gb = 0.f, sq = 0.f;
+    unsigned valid = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) g2[k] = 0.f;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) g3[k] = 0.f;
+    const int s0 = 2 * wave;
+    for (int64_t b = (int64_t)blockIdx.x * S; b < n; b += (int64_t)gridDim.x * S) {
+        __syncthreads();                                   // the last round's readers are done
+        if (t < S) {
+            float f[kNIn] = {0.f, 0.f, 0.f, 0.f}, x[kNIn];
+            if (b + t < n)
+#pragma unroll
+                for (int k = 0; k < kNIn; ++k) f[k] = feats[kNIn * (b + t) + k];
+            normalise(M, f, x);
+#pragma unroll
+            for (int k = 0; k < kNIn; ++k) X[t][k] = x[k];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            float s = B1[j];
+#pragma unroll
+            for (int k = 0; k < kNIn; ++k) s = fmaf(W1[j * kNIn + k], X[s0 + q][k], s);
+            A1[j][s0 + q] = fast_tanh(s);
+        }
+        __syncthreads();
+        {
+            float u = B2[j], v = u;
+#pragma unroll 16
+            for (int i = 0; i < kNHid; ++i) {
+                const float w = W2[j * kW2Pitch + i];
+                u = fmaf(w, A1[i][s0], u);
+                v = fmaf(w, A1[i][s0 + 1], v);
+            }
+            A2[j][s0] = fast_tanh(u);
+            A2[j][s0 + 1] = fast_tanh(v);
+        }
+        __syncthreads();
+        if (t < kNOut * S) {                               // output o of sample c; twice its error, 0 for NaN targets
+            const int o = t >> 3, c = t & 7;
+            float y = B3[o];
+#pragma unroll 16
+            for (int i = 0; i < kNHid; ++i) y = fmaf(W3[o * kNHid + i], A2[i][c], y);
+            float d = 0.f;
+            if (b + c < n) {
+                const float want = tgt[kNOut * (b + c) + o];
+                if (!isnan(want)) {
+                    d = y - want;
+                    ++valid;
+                }
+            }
+            sq = fmaf(d, d, sq);
+            dY[o][c] = 2.f * d;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {                      // dZ2 = (W3^T dY) (1 - A2^2)
+            float s = 0.f;
+#pragma unroll
+            for (int o = 0; o < kNOut; ++o) s = fmaf(W3[o * kNHid + j], dY[o][s0 + q], s);
+            const float a = A2[j][s0 + q];
+            Z2[j][s0 + q] = s * (1.f - a * a);
+        }
+        __syncthreads();
+        {                                                  // dZ1 = (W2^T dZ2) (1 - A1^2), lane j the unit of layer 1
+            float u = 0.f, v = 0.f;
+#pragma unroll 16
+            for (int i = 0; i < kNHid; ++i) {
+                const float w = W2[i * kW2Pitch + j];
+                u = fmaf(w, Z2[i][s0], u);
+                v = fmaf(w, Z2[i][s0 + 1], v);
+            }
+            const float a = A1[j][s0], c = A1[j][s0 + 1];
+            Z1[j][s0] = u * (1.f - a * a);
+            Z1[j][s0 + 1] = v * (1.f - c * c);
+        }
+        __syncthreads();
+        // the samples' products, in sample order
+        float a1[S];
+#pragma unroll
+        for (int c = 0; c < S; ++c) a1[c] = A1[j][c];
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+#pragma unroll
+            for (int c = 0; c < S; ++c) g2[k] = fmaf(Z2[16 * wave + k][c], a1[c], g2[k]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const int o = wave + 4 * k;                    // row o of W3, lane j its column
+            if (o < kNOut)
+#pragma unroll
+                for (int c = 0; c < S; ++c) g3[k] = fmaf(dY[o][c], A2[j][c], g3[k]);
+        }
+#pragma unroll
+        for (int c = 0; c < S; ++c) g1 = fmaf(Z1[t >> 2][c], X[c][t & 3], g1);
+#pragma unroll
+        for (int c = 0; c < S; ++c)
+            gb += wave == 0 ? Z1[j][c] : (wave == 1 ? Z2[j][c] : (wave == 2 && j < kNOut ? dY[j < kNOut ? j : 0][c] : 0.f));
+    }
+    float* out = part + (int64_t)blockIdx.x * kGradPart;
+    out[kOffW1 + t] = g1;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) out[kOffW2 + (16 * wave + k) * kNHid + j] = g2[k];
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        if (wave + 4 * k < kNOut) out[kOffW3 + (wave + 4 * k) * kNHid + j] = g3[k];
+    if (wave == 0) out[kOffB1 + j] = gb;
+    if (wave == 1) out[kOffB2 + j] = gb;
+    if (wave == 2 && j < kNOut) out[kOffB3 + j] = gb;
+    red[t] = sq;
+    redn[t] = valid;
+    __syncthreads();
+    for (int k = kBlock / 2; k > 0; k >>= 1) {
+        if (t < k) {
+            red[t] += red[t + k];
+            redn[t] += redn[t + k];
+        }
+        __syncthreads();
+    }
+    if (t == 0) {
+        out[kNParams] = red[0];
+        out[kNParams + 1] = __uint_as_float(redn[0]);
+    }
+}
+
+// Adam state and constants of a training step (null parameters: gradient only).
+struct AdamStep {
+    float *p, *m, *v;
+    float lr, b1, b2, eps, c1, c2;
 };
 
-// Forward per sample; output error terms dY = 2 (y - t) / n_valid (0 for NaN targets).
-// inv_dev, when not null, holds 1/n_valid in device memory (it replaces inv_valid).
-__global__ __launch_bounds__(kBlock) void k_train_forward(const float* __restrict__ M, const float* __restrict__ feats,
-                                                          const float* __restrict__ tgt, int64_t n, float inv_valid,
-                                                          const float* __restrict__ inv_dev, float* __restrict__ work) {
-    __shared__ float sM[kNModel];
-    M = stage_model(M, sM);
-    if (inv_dev) inv_valid = *inv_dev;
-    const int64_t b = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (b >= n) return;
-    WorkView w(work, n);
-    float f[kNIn], x[kNIn], y[kNOut];
-#pragma unroll
-    for (int k = 0; k < kNIn; ++k) f[k] = feats[kNIn * b + k];
-    normalise(M, f, x);
-#pragma unroll
-    for (int k = 0; k < kNIn; ++k) w.X[kNIn * b + k] = x[k];
-    forward(M, x, y, w.A1 + kNHid * b, w.A2 + kNHid * b);
-    float sq = 0.f;
-#pragma unroll
-    for (int k = 0; k < kNOut; ++k) {
-        float t = tgt[kNOut * b + k];
-        float d = isnan(t) ? 0.f : y[k] - t;
-        sq = fmaf(d, d, sq);
-        w.dY[kNOut * b + k] = 2.f * d * inv_valid;
-    }
-    w.sq[b] = sq;
-}
-
-// dZ2[b][j] = (sum_o W3[o][j] dY[b][o]) (1 - A2^2)
-__global__ __launch_bounds__(kBlock) void k_back2(const float* __restrict__ M, int64_t n, float* __restrict__ work) {
-    const int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (idx >= n * kNHid) return;
-    WorkView w(work, n);
-    const int64_t b = idx / kNHid;
-    const int j = (int)(idx % kNHid);
+// grad = the groups' sums in group order / valid targets (0 when none is valid), 64
+// parameters per work group, each wave every fourth group; group 0 also writes
+// the loss.
+__global__ __launch_bounds__(kBlock) void k_grad_finish(const float* __restrict__ part, int groups,
+                                                        float* __restrict__ grad, float* __restrict__ loss, AdamStep a) {
+    __shared__ float red[4][kNHid];
+    __shared__ float rsq[kBlock];
+    __shared__ unsigned long long rn[kBlock];
+    const int t = threadIdx.x, wave = t >> 6, q = blockIdx.x * 64 + (t & 63);
+    rn[t] = t < groups ? __float_as_uint(part[(int64_t)t * kGradPart + kNParams + 1]) : 0u;
+    rsq[t] = t < groups ? part[(int64_t)t * kGradPart + kNParams] : 0.f;
     float s = 0.f;
-#pragma unroll
-    for (int o = 0; o < kNOut; ++o) s = fmaf(M[kOffW3 + o * kNHid + j], w.dY[kNOut * b + o], s);
-    const float a = w.A2[kNHid * b + j];
-    w.dZ2[kNHid * b + j] = s * (1.f - a * a);
-}
-
-// dZ1[b][i] = (sum_j W2[j][i] dZ2[b][j]) (1 - A1^2)
-__global__ __launch_bounds__(kBlock) void k_back1(const float* __restrict__ M, int64_t n, float* __restrict__ work) {
-    const int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (idx >= n * kNHid) return;
-    WorkView w(work, n);
-    const int64_t b = idx / kNHid;
-    const int i = (int)(idx % kNHid);
-    float s = 0.f;
-    for (int j = 0; j < kNHid; ++j) s = fmaf(M[kOffW2 + j * kNHid + i], w.dZ2[kNHid * b + j], s);
-    const float a = w.A1[kNHid * b + i];
-    w.dZ1[kNHid * b + i] = s * (1.f - a * a);
-}
-
-// Gradient of every parameter: one thread per parameter, summed over the batch
-// in sample order (deterministic).
-__global__ __launch_bounds__(kBlock) void k_grads(int64_t n, const float* __restrict__ work, float* __restrict__ grad) {
-    const int q = blockIdx.x * kBlock + threadIdx.x;
-    if (q >= kNParams) return;
-    WorkView w(const_cast<float*>(work), n);
-    const float *dOut, *in;
-    int nout, nin, o, i;
-    bool bias = false;
-    if (q < kOffB1) { dOut = w.dZ1; in = w.X; nout = kNHid; nin = kNIn; o = q / kNIn; i = q % kNIn; }
-    else if (q < kOffW2) { dOut = w.dZ1; in = nullptr; nout = kNHid; nin = 0; o = q - kOffB1; i = 0; bias = true; }
-    else if (q < kOffB2) { dOut = w.dZ2; in = w.A1; nout = kNHid; nin = kNHid; o = (q - kOffW2) / kNHid; i = (q - kOffW2) % kNHid; }
-    else if (q < kOffW3) { dOut = w.dZ2; in = nullptr; nout = kNHid; nin = 0; o = q - kOffB2; i = 0; bias = true; }
-    else if (q < kOffB3) { dOut = w.dY; in = w.A2; nout = kNOut; nin = kNHid; o = (q - kOffW3) / kNHid; i = (q - kOffW3) % kNHid; }
-    else { dOut = w.dY; in = nullptr; nout = kNOut; nin = 0; o = q - kOffB3; i = 0; bias = true; }
-    float s = 0.f;
-    for (int64_t b = 0; b < n; ++b) s = fmaf(dOut[nout * b + o], bias ? 1.f : in[nin * b + i], s);
-    grad[q] = s;
-}
-
-// Loss = sum of squared errors / n_valid, summed in a fixed order by one block.
-__global__ __launch_bounds__(kBlock) void k_loss(int64_t n, const float* __restrict__ work, float inv_valid,
-                                                 const float* __restrict__ inv_dev, float* __restrict__ loss) {
-    __shared__ float red[kBlock];
-    if (inv_dev) inv_valid = *inv_dev;
-    WorkView w(const_cast<float*>(work), n);
-    float s = 0.f;
-    for (int64_t b = threadIdx.x; b < n; b += kBlock) s += w.sq[b];
-    red[threadIdx.x] = s;
+    if (q < kNParams)
+#pragma unroll 8
+        for (int b = wave; b < groups; b += 4) s += part[(int64_t)b * kGradPart + q];
+    red[wave][t & 63] = s;
     __syncthreads();
     for (int k = kBlock / 2; k > 0; k >>= 1) {
-        if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
+        if (t < k) {
+            rn[t] += rn[t + k];
+            rsq[t] += rsq[t + k];
+        }
         __syncthreads();
     }
-    if (threadIdx.x == 0) *loss = red[0] * inv_valid;
-}
-
-// 1/n_valid of targets[n][11] (NaN entries excluded; 0 when none is valid),
-// counted by one block in a fixed order and rounded as the host computes it.
-__global__ __launch_bounds__(kBlock) void k_inv_valid(const float* __restrict__ tgt, int64_t n, float* __restrict__ out) {
-    __shared__ int64_t red[kBlock];
-    int64_t c = 0;
-    for (int64_t k = threadIdx.x; k < n * kNOut; k += kBlock) c += isnan(tgt[k]) ? 0 : 1;
-    red[threadIdx.x] = c;
-    __syncthreads();
-    for (int k = kBlock / 2; k > 0; k >>= 1) {
-        if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
-        __syncthreads();
+    const float inv = rn[0] > 0 ? __fdiv_rn(1.0f, (float)rn[0]) : 0.0f;
+    if (blockIdx.x == 0 && t == 0) *loss = rsq[0] * inv;
+    if (wave > 0 || q >= kNParams) return;
+    const float g = (((red[0][t] + red[1][t]) + red[2][t]) + red[3][t]) * inv;
+    if (grad) grad[q] = g;
+    if (a.p) {
+        const float mi = a.b1 * a.m[q] + (1.f - a.b1) * g;
+        const float vi = a.b2 * a.v[q] + (1.f - a.b2) * g * g;
+        a.m[q] = mi;
+        a.v[q] = vi;
+        a.p[q] -= a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
     }
-    if (threadIdx.x == 0) *out = red[0] > 0 ? __fdiv_rn(1.0f, (float)red[0]) : 0.0f;
 }
 
 // Work memory of bldtt_mlp_loss_grad_noalloc, one copy per GPU for the life of
-// the process: the loss-gradient work of up to kNoAllocSamples samples, then
-// 1/n_valid.  Host code reaches it only through the address that
-// hipGetSymbolAddress returns on each device.
+// the process: the partial gradients of every work group.  Host code reaches
+// it only through the address that hipGetSymbolAddress returns on each device.
 constexpr int64_t kNoAllocSamples = 4096;
-constexpr int64_t kNoAllocWork = kNoAllocSamples * (kNIn + 4 * kNHid + kNOut + 1);
-static __device__ __align__(256) float scratch[kNoAllocWork + 64];
-
-__global__ __launch_bounds__(kBlock) void k_adam(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
-                                                 float* __restrict__ v, int n, float lr, float b1, float b2, float eps,
-                                                 float c1, float c2) {
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.f - b1) * gi;
-    const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-}
+static __device__ __align__(256) float scratch[(int64_t)kGradGroups * kGradPart];
 
 inline unsigned blocks(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
 }  // namespace
 
-int64_t mlp_work_floats(int64_t batch) { return batch * (kNIn + 4 * kNHid + kNOut + 1); }
+namespace {
+int grad_groups(int64_t n) { return (int)std::min<int64_t>(kGradGroups, (n + kGradSamples - 1) / kGradSamples); }
+}  // namespace
+
+int64_t mlp_work_floats(int64_t batch) { return (int64_t)grad_groups(batch) * kGradPart; }
 
 void launch_mlp_select(const float* model, const float* feats, const int64_t* counts, int64_t n, float log_tau,
                        int fallback, int pp_cc_only, uint8_t* choice, hipStream_t st) {
@@ -310,15 +391,12 @@ void launch_mlp_forward(const float* model, const float* feats, int64_t n, float
 }
 
 namespace {
-// The five kernels of the loss and gradient; inv_dev as in k_train_forward.
-void enqueue_loss_grad(const float* model, const float* feats, const float* targets, int64_t n, float inv_valid,
-                       const float* inv_dev, float* work, float* grad, float* loss, hipStream_t st) {
-    hipLaunchKernelGGL(k_train_forward, dim3(blocks(n)), dim3(kBlock), 0, st, model, feats, targets, n, inv_valid,
-                       inv_dev, work);
-    hipLaunchKernelGGL(k_back2, dim3(blocks(n * kNHid)), dim3(kBlock), 0, st, model, n, work);
-    hipLaunchKernelGGL(k_back1, dim3(blocks(n * kNHid)), dim3(kBlock), 0, st, model, n, work);
-    hipLaunchKernelGGL(k_grads, dim3(blocks(kNParams)), dim3(kBlock), 0, st, n, (const float*)work, grad);
-    hipLaunchKernelGGL(k_loss, dim3(1), dim3(kBlock), 0, st, n, (const float*)work, inv_valid, inv_dev, loss);
+void enqueue_loss_grad(const float* model, const float* feats, const float* targets, int64_t n, float* work, float* grad,
+                       float* loss, const AdamStep& step, hipStream_t st) {
+    const int groups = grad_groups(n);
+    hipLaunchKernelGGL(k_grad_part, dim3(groups), dim3(kBlock), 0, st, model, feats, targets, n, work);
+    hipLaunchKernelGGL(k_grad_finish, dim3((kNParams + 63) / 64), dim3(kBlock), 0, st, (const float*)work, groups, grad,
+                       loss, step);
     CHECK_LAUNCH();
 }
 
@@ -345,10 +423,17 @@ float* scratch_on_current_device() {
 }
 }  // namespace
 
-void launch_mlp_loss_grad(const float* model, const float* feats, const float* targets, int64_t n, float inv_valid,
-                          float* work, float* grad, float* loss, hipStream_t st) {
+void launch_mlp_loss_grad(const float* model, const float* feats, const float* targets, int64_t n, float* work,
+                          float* grad, float* loss, hipStream_t st) {
     if (n <= 0) return;
-    enqueue_loss_grad(model, feats, targets, n, inv_valid, nullptr, work, grad, loss, st);
+    enqueue_loss_grad(model, feats, targets, n, work, grad, loss, AdamStep{}, st);
+}
+
+void launch_mlp_step(float* model, const float* feats, const float* targets, int64_t n, float* work, float* loss, float* m,
+                     float* v, float lr, float b1, float b2, float eps, int step, hipStream_t st) {
+    if (n <= 0) return;
+    const float c1 = 1.f - powf(b1, (float)step), c2 = 1.f - powf(b2, (float)step);
+    enqueue_loss_grad(model, feats, targets, n, work, nullptr, loss, AdamStep{model, m, v, lr, b1, b2, eps, c1, c2}, st);
 }
 
 int64_t mlp_noalloc_max_samples() { return kNoAllocSamples; }
@@ -356,17 +441,7 @@ int64_t mlp_noalloc_max_samples() { return kNoAllocSamples; }
 void launch_mlp_loss_grad_noalloc(const float* model, const float* feats, const float* targets, int64_t n, float* grad,
                                   float* loss, hipStream_t st) {
     if (n < 1 || n > kNoAllocSamples) throw Error(-1, "bldtt_mlp_loss_grad_noalloc: n must lie in [1, 4096]");
-    float* work = scratch_on_current_device();
-    float* inv = work + kNoAllocWork;            // 1/n_valid, written before it is read
-    hipLaunchKernelGGL(k_inv_valid, dim3(1), dim3(kBlock), 0, st, targets, n, inv);
-    enqueue_loss_grad(model, feats, targets, n, 0.0f, inv, work, grad, loss, st);
-}
-
-void launch_adam(float* params, const float* grad, float* m, float* v, int n, float lr, float b1, float b2, float eps,
-                 int step, hipStream_t st) {
-    const float c1 = 1.f - powf(b1, (float)step), c2 = 1.f - powf(b2, (float)step);
-    hipLaunchKernelGGL(k_adam, dim3(blocks(n)), dim3(kBlock), 0, st, params, grad, m, v, n, lr, b1, b2, eps, c1, c2);
-    CHECK_LAUNCH();
+    enqueue_loss_grad(model, feats, targets, n, scratch_on_current_device(), grad, loss, AdamStep{}, st);
 }
 
 }  // namespace bldtt
