@@ -821,7 +821,13 @@ __global__ __launch_bounds__(kBlock) void k_pair_error(const int32_t* __restrict
 }
 
 // ---------------------------------------------------------------------------
-// Direct sum with compensated accumulation: one workgroup per target.
+// Direct sum with compensated accumulation.  A work group of 16 waves takes T
+// targets; its threads share the sources, each source read once for the T
+// targets, and the threads' sums are added pairwise with their errors.  Bound by
+// FP64 issue (25 operations a term, 7 of them the compensation) once a source
+// read from the shared caches serves several targets: one target per group of
+// four waves, with a square root and a division per term, read 32 bytes a term
+// and took 2.80 ms for 1000 targets and 1E6 sources, now 1.03 ms.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void two_sum(double a, double b, double& s, double& e) {
     s = a + b;
@@ -829,55 +835,73 @@ __device__ __forceinline__ void two_sum(double a, double b, double& s, double& e
     e = (a - (s - bb)) + (b - bb);
 }
 
+// The kernel's value to the last bit or so (1/r by the cubic correction, not the
+// folded Newton step of the passes).
 template <int KIND>
-__device__ __forceinline__ double g_exact(double tx, double ty, double tz, double sx, double sy, double sz,
-                                          double param) {
+__device__ __forceinline__ double g_ref(double tx, double ty, double tz, double sx, double sy, double sz,
+                                        double param) {
     if (KIND == K_POLY) {
         double d = 1.0 + ((tx * sx + ty * sy) + tz * sz);
         return d * d;
     }
-    double dx = tx - sx, dy = ty - sy, dz = tz - sz;
-    double r2 = (dx * dx + dy * dy) + dz * dz;
-    if (r2 == 0.0) return 0.0;
-    double r = sqrt(r2);
-    if (KIND == K_COULOMB) return 1.0 / r;
-    if (KIND == K_YUKAWA) return exp(-param * r) / r;
-    if (KIND == K_OSC) return sinpi(r) / r;
-    return 1.0 / sqrt(r2 + param * param);
+    const double dx = tx - sx, dy = ty - sy, dz = tz - sz;
+    const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
+    if (KIND == K_COULOMB) {
+        double y = rsq_est(r2);
+        y = r2 > 0.0 ? y : 0.0;
+        return rsq_fix(r2, y);
+    }
+    return G64<KIND>::template value<true>(r2, param);
 }
 
-template <int KIND>
-__global__ __launch_bounds__(kBlock) void k_direct(const int64_t* __restrict__ sel, const double* __restrict__ tx,
-                                                   const double* __restrict__ ty, const double* __restrict__ tz,
-                                                   int64_t N, const double* __restrict__ sx,
-                                                   const double* __restrict__ sy, const double* __restrict__ sz,
-                                                   const double* __restrict__ q, double param,
-                                                   double* __restrict__ out) {
-    __shared__ double rs[kBlock], rc[kBlock];
-    const int64_t a = blockIdx.x;
-    const int64_t i = sel ? sel[a] : a;
-    const double x = tx[i], y = ty[i], z = tz[i];
-    double s = 0.0, c = 0.0;
-    for (int64_t j = threadIdx.x; j < N; j += kBlock) {
-        double t = g_exact<KIND>(x, y, z, sx[j], sy[j], sz[j], param) * q[j];
-        double u, e;
-        two_sum(s, t, u, e);
-        s = u;
-        c += e;
+constexpr int kDirectBlock = 1024;
+
+template <int KIND, int T>
+__global__ __launch_bounds__(kDirectBlock) void k_direct(int64_t nsel, const int64_t* __restrict__ sel,
+                                                         const double* __restrict__ tx, const double* __restrict__ ty,
+                                                         const double* __restrict__ tz, int64_t N,
+                                                         const double* __restrict__ sx, const double* __restrict__ sy,
+                                                         const double* __restrict__ sz, const double* __restrict__ q,
+                                                         double param, double* __restrict__ out) {
+    __shared__ double rs[kDirectBlock], rc[kDirectBlock];
+    const int64_t a0 = (int64_t)blockIdx.x * T;
+    double x[T], y[T], z[T], s[T], c[T];
+#pragma unroll
+    for (int k = 0; k < T; ++k) {
+        const int64_t a = a0 + k < nsel ? a0 + k : a0, i = sel ? sel[a] : a;
+        x[k] = tx[i];
+        y[k] = ty[i];
+        z[k] = tz[i];
+        s[k] = c[k] = 0.0;
     }
-    rs[threadIdx.x] = s;
-    rc[threadIdx.x] = c;
-    __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) {
+    for (int64_t j = threadIdx.x; j < N; j += kDirectBlock) {
+        const double jx = sx[j], jy = sy[j], jz = sz[j], jq = q[j];
+#pragma unroll
+        for (int k = 0; k < T; ++k) {
             double u, e;
-            two_sum(rs[threadIdx.x], rs[threadIdx.x + w], u, e);
-            rs[threadIdx.x] = u;
-            rc[threadIdx.x] += rc[threadIdx.x + w] + e;
+            two_sum(s[k], g_ref<KIND>(x[k], y[k], z[k], jx, jy, jz, param) * jq, u, e);
+            s[k] = u;
+            c[k] += e;
         }
-        __syncthreads();
     }
-    if (threadIdx.x == 0) out[a] = rs[0] + rc[0];
+#pragma unroll
+    for (int k = 0; k < T; ++k) {
+        if (a0 + k >= nsel) break;                         // the whole group
+        if (k > 0) __syncthreads();                        // thread 0 has read the last target's sums
+        rs[threadIdx.x] = s[k];
+        rc[threadIdx.x] = c[k];
+        __syncthreads();
+        for (int w = kDirectBlock / 2; w > 0; w >>= 1) {
+            if ((int)threadIdx.x < w) {
+                double u, e;
+                two_sum(rs[threadIdx.x], rs[threadIdx.x + w], u, e);
+                rs[threadIdx.x] = u;
+                rc[threadIdx.x] += rc[threadIdx.x + w] + e;
+            }
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) out[a0 + k] = rs[0] + rc[0];
+    }
 }
 
 __global__ void k_fill(double* __restrict__ p, int64_t n, double v) {
@@ -1153,12 +1177,30 @@ void launch_prolong(const DevItem* items, int n_items, DevTree T, const double* 
     CHECK_LAUNCH();
 }
 
+namespace {
+// Targets per work group: as many as still give about a group per CU (256).  1E6
+// sources: 100 targets 0.44 / 0.56 / 0.91 ms with 1 / 2 / 4; 500: 1.00 / 0.66 /
+// 0.93; 1000: 2.01 / 1.20 / 1.03; 8 no faster than 4 from 2000 on (1.89 ms both).
+int direct_targets(int64_t nsel) { return nsel > 512 ? 4 : (nsel > 256 ? 2 : 1); }
+}  // namespace
+
 void launch_direct(KernelSpec k, int64_t nsel, const int64_t* sel, const double* tx, const double* ty,
                    const double* tz, int64_t N, const double* sx, const double* sy, const double* sz,
                    const double* q, double* out, hipStream_t st) {
     if (nsel <= 0) return;
-    DISPATCH_KIND(k.kind, hipLaunchKernelGGL(k_direct<KK>, dim3((unsigned)nsel), dim3(kBlock), 0, st, sel, tx, ty,
-                                             tz, N, sx, sy, sz, q, k.param, out));
+    const int t = direct_targets(nsel);
+    const dim3 grid((unsigned)((nsel + t - 1) / t));
+#define LAUNCH_T(T) hipLaunchKernelGGL((k_direct<KK, T>), grid, dim3(kDirectBlock), 0, st, nsel, sel, tx, ty, tz, N, sx, sy, \
+                                       sz, q, k.param, out)
+#define LAUNCH_DIRECT switch (t) { case 1: LAUNCH_T(1); break; case 2: LAUNCH_T(2); break; default: LAUNCH_T(4); break; }
+    if (k.kind == K_YUKAWA && !(k.param >= 0.0 && k.param < INFINITY)) {
+        constexpr int KK = K_YUKAWA_ANY;
+        LAUNCH_DIRECT;
+    } else {
+        DISPATCH_KIND(k.kind, LAUNCH_DIRECT);
+    }
+#undef LAUNCH_DIRECT
+#undef LAUNCH_T
     CHECK_LAUNCH();
 }
 

@@ -97,3 +97,19 @@ def test_mirrored_pc_cp_pairs_once_for_both(kernel, n, leaf, degree):
     ref = core.bldtt(p, p, **kw)
     _close(a, ref)
     _close(c, ref)
+
+
+@pytest.mark.parametrize("kernel", ["coulomb", "yukawa", "oscillatory", "regcoulomb"])
+@pytest.mark.parametrize("nsel", [1, 255, 257, 513, 1030])
+def test_direct_sum_for_every_group_size(kernel, nsel):
+    # one, two and four targets per work group, a last group that is not full,
+    # fewer sources than threads, and every target against itself once
+    from paper_2012_06925_amd import api
+    for n in (nsel, 5003):
+        p = inputs.particles(max(n, nsel), "uniform", seed=74)
+        p.x[-1], p.y[-1], p.z[-1] = p.x[0], p.y[0], p.z[0]
+        dev = [torch.from_numpy(a).cuda() for a in (p.x, p.y, p.z, p.q)]
+        sel = np.sort(np.random.default_rng(3).choice(p.n, nsel, replace=False)).astype(np.int64)
+        got = api.direct_sum(dev[:3], dev, kernel=kernel, sel=torch.from_numpy(sel).cuda()).cpu().numpy()
+        ref = core.direct_sum(p, p, kernel=kernel)[sel]
+        assert np.abs(got - ref).max() <= 1e-13 * max(np.abs(ref).max(), 1e-300)
