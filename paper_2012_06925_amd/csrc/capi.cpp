@@ -369,14 +369,29 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
         return !fp32 && !L.tc[PC].empty() && !L.tc[CP].empty() &&
                pc_source_slots(T, L, pl->degree, sym_tile) <= (double)((int64_t)4 << 30) / sizeof(double);
     };
-    auto particle_pass = [&](const DevBuf& items, int n, const DevBuf& entries, bool add, hipStream_t s) {
+    auto particle_pass = [&](const DevBuf& items, int n, const DevBuf& entries, bool add, hipStream_t s,
+                             SymSlots cut = {}) {
         if (mfma_pp)
             launch_pp_mfma(items.as<DevItem>(), n, entries.as<int2>(), pl->dtgt(), dT, pl->dsrc(), dS, tab,
-                           deg_ptrs(pl->qhat_deg), pl->phi_tree.as<double>(), add, nfp64, s);
+                           deg_ptrs(pl->qhat_deg), pl->phi_tree.as<double>(), add, nfp64, s, cut);
         else
             launch_interact(ks, fp32, false, pl->tpt, items.as<DevItem>(), n, entries.as<int2>(), pl->dtgt(), dT,
                             pl->dsrc(), dS, tab, deg_ptrs(pl->qhat_deg), pl->phi_tree.as<double>(), DegOut{}, s,
-                            add, nfp64);
+                            add, nfp64, cut);
+    };
+    // The one-way items of small problems, and of few clusters with long lists,
+    // are cut like the symmetric ones: `cut` holds the pieces (empty: nothing to
+    // cut), and the pass is followed by the fold of its pieces.  1E5 targets on a
+    // sphere, 2E5 Gaussian sources (Yukawa): see the figures at cut_items' test.
+    auto particle_pass_cut = [&](const DevBuf& items, int n, const DevBuf& entries, bool add, hipStream_t s,
+                                 const CutItems& cut, const DevBuf& cut_items, const DevFold& f) {
+        if (cut.items.empty()) {
+            particle_pass(items, n, entries, add, s);
+            return;
+        }
+        particle_pass(cut_items, (int)cut.items.size(), entries, add, s, f.out());
+        launch_sym_fold(f.segs.as<FoldSeg>(), f.n_segs, f.max_n, f.parts.as<FoldPart>(), f.slots.as<double>(),
+                        pl->phi_tree.as<double>(), DegOut{}, s);
     };
     // symmetric PP items: those without guarded ranges, then those with (their
     // slot bases uploaded with them, the slots reserved by add_bases); the
@@ -406,6 +421,13 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
     auto add_parts = [](Upload& u, DevFold& d, const SymFold& f) {
         d.set_segments(f);
         u.add(d.segs, f.segs).add(d.parts, f.parts);
+    };
+
+    auto add_cut = [&](Upload& u, const CutItems& cut, DevBuf& items, DevFold& d) {
+        if (cut.items.empty()) return;
+        u.add(items, cut.items);
+        add_bases(u, d, cut.fold);
+        add_parts(u, d, cut.fold);
     };
 
     // profiled computes: fold what has finished; wait only when every event set is in use
@@ -505,12 +527,15 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
                                            [](const Item& it) { return it.ee == it.eb; }),
                             wn.pitems.end());
         if (!symm) fork();
+        cut_items(wn.pitems, wn.pentries, false, sym_cut, pl->cut_near);
         Upload un;
         un.add(pl->near_items, wn.pitems).add(pl->near_entries, wn.pentries);
+        add_cut(un, pl->cut_near, pl->cut_near_items, pl->fold_cut_near);
         un.run(pl->staging_rest, pl->arena_rest, pl->staging_rest_free, pl->side);
         {
             PhaseMark mark(pl, BLDTT_PH_PPPC, pl->side);
-            particle_pass(pl->near_items, (int)wn.pitems.size(), pl->near_entries, symm, pl->side);
+            particle_pass_cut(pl->near_items, (int)wn.pitems.size(), pl->near_entries, symm, pl->side, pl->cut_near,
+                              pl->cut_near_items, pl->fold_cut_near);
         }
         HIPCHK(hipEventRecord(pl->ev_near_done, pl->side));
         if (!symm) mark_host(2);
@@ -583,7 +608,12 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
     pl->stats.pass_interactions[4] = self_w;
     pl->stats.down_degree = w.down_degree;
     pl->stats.degree_mask = w.src_degrees | w.tgt_degrees;
+    // (every leaf's tiles stay whole in w.pitems for the leaf interpolation)
+    cut_items(varied || symm ? sep_items : w.pitems, w.pentries, false, sym_cut, pl->cut_part);
+    cut_items(w.qitems, w.qentries, true, sym_cut, pl->cut_prox);
     Upload up;
+    add_cut(up, pl->cut_part, pl->cut_part_items, pl->fold_cut_part);
+    add_cut(up, pl->cut_prox, pl->cut_prox_items, pl->fold_cut_prox);
     up.add(pl->pitems, w.pitems).add(pl->pentries, w.pentries).add(pl->qitems, w.qitems)
         .add(pl->qentries, w.qentries).add(pl->has_far, w.leaf_has_far).add(pl->prolong, w.prolong);
     if (varied || symm) up.add(pl->sep_items, sep_items);
@@ -618,9 +648,15 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
         const uint32_t need = w.tgt_degrees | (1u << D);
         clear_proxies(need & ~prefill);
         pl->fill_degrees_last = need;
-        launch_interact(ks, fp32, true, pl->tpt_proxy, pl->qitems.as<DevItem>(), (int)w.qitems.size(),
-                        pl->qentries.as<int2>(), pl->dtgt(), dT, pl->dsrc(), dS, tab, deg_ptrs(pl->qhat_deg),
-                        nullptr, deg_out(pl->phihat_deg), st);
+        const bool cut = !pl->cut_prox.items.empty();
+        const DevFold& fq = pl->fold_cut_prox;
+        launch_interact(ks, fp32, true, pl->tpt_proxy, (cut ? pl->cut_prox_items : pl->qitems).as<DevItem>(),
+                        (int)(cut ? pl->cut_prox.items.size() : w.qitems.size()), pl->qentries.as<int2>(), pl->dtgt(),
+                        dT, pl->dsrc(), dS, tab, deg_ptrs(pl->qhat_deg), nullptr, deg_out(pl->phihat_deg), st, false,
+                        nullptr, cut ? fq.out() : SymSlots{});
+        if (cut)
+            launch_sym_fold(fq.segs.as<FoldSeg>(), fq.n_segs, fq.max_n, fq.parts.as<FoldPart>(), fq.slots.as<double>(),
+                            nullptr, deg_out(pl->phihat_deg), st);
         if (symm) {             // symmetric CC pairs add to the proxy potentials the pass above wrote
             const DevFold& f = pl->fold_cc;
             launch_sym(ks, fp32, pl->mfma_transfer(), true, false, pl->sym_cc_items.as<DevItem>(), (int)scc.cc_items.size(),
@@ -649,8 +685,8 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
     if (!varied) {
         {
             PhaseMark mark(pl, BLDTT_PH_PPPC, st);
-            if (symm) particle_pass(pl->sep_items, (int)sep_items.size(), pl->pentries, true, st);
-            else particle_pass(pl->pitems, (int)w.pitems.size(), pl->pentries, false, st);
+            particle_pass_cut(symm ? pl->sep_items : pl->pitems, (int)(symm ? sep_items.size() : w.pitems.size()),
+                              pl->pentries, symm, st, pl->cut_part, pl->cut_part_items, pl->fold_cut_part);
         }
         if (symm) sym_pp_fold(st);          // its pass was enqueued after the traversal
         if (sym_pc) sym_pc_fold(st);
@@ -668,7 +704,8 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
         if (symm) sym_pp_fold(st);
         if (sym_pc) sym_pc_fold(st);
         PhaseMark mark(pl, BLDTT_PH_PPPC_SEP, st);
-        particle_pass(pl->sep_items, (int)sep_items.size(), pl->pentries, true, st);
+        particle_pass_cut(pl->sep_items, (int)sep_items.size(), pl->pentries, true, st, pl->cut_part, pl->cut_part_items,
+                          pl->fold_cut_part);
     }
     // 5. leaves to targets, caller order
     {

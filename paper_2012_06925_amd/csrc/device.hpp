@@ -295,7 +295,8 @@ constexpr int interact_lds_bytes() { return kChunk * (int)sizeof(typename Stage<
 // Sources are staged through LDS and read by all lanes at the same address.
 // `add` says how particle sums are stored: written, or added to what the
 // outputs hold (a second pass over the same targets); proxy sums are written.
-// Each item owns its outputs.
+// Each item owns its outputs.  `slot`: the sums go there instead (a later piece
+// of a cut item, folded afterwards).
 // ---------------------------------------------------------------------------
 enum { OUT_WRITE = 0, OUT_ADD = 1 };
 
@@ -304,7 +305,8 @@ __device__ __forceinline__ void interact_body(const DevItem& it, const int2* __r
                                               DevTree Tt, DevParticles src, DevTree S, const double* __restrict__ tab,
                                               const DegPtrs& qhat, double param, double* __restrict__ out,
                                               const DegOut& pout, typename Stage<F32>::V* lds,
-                                              int add = OUT_WRITE, double* nfp64 = nullptr) {
+                                              int add = OUT_WRITE, double* nfp64 = nullptr,
+                                              double* slot = nullptr) {
     using St = Stage<F32>;
     using V = typename St::V;
     using R = typename std::conditional<F32, float, double>::type;
@@ -431,7 +433,9 @@ __device__ __forceinline__ void interact_body(const DevItem& it, const int2* __r
     for (int j = 0; j < T; ++j) {
         int r = slab + lane + 64 * j;
         if (r < it.tn) {
-            if (PROXY_TGT) {
+            if (slot) {
+                slot[r] = acc[j];
+            } else if (PROXY_TGT) {
                 pout.p[it.degree][(int64_t)it.slot * Pt + it.t0 + r] = acc[j];
             } else {
                 out[it.slot + r] = add == OUT_ADD ? out[it.slot + r] + acc[j] : acc[j];

@@ -244,6 +244,22 @@ int64_t fold_group_bases(const std::vector<FoldGroup>& groups, std::vector<std::
 void fold_group_parts(const Tree& T, bool proxies, const std::vector<FoldGroup>& groups,
                       const std::vector<std::vector<int64_t>>& bases, SymFold& f);
 
+// One-way items cut along their sources (ItemCut): the first piece of an item
+// writes (or adds to) the outputs as the whole item would, the others write slots
+// that a fold adds to them afterwards, in piece order.  items stays empty when
+// nothing is cut; fold.ibase[i] is piece i's slot base, -1 for the outputs.  The
+// pieces' entries are appended to `entries`.  proxies: proxy targets.
+struct CutItems {
+    std::vector<Item> items;
+    SymFold fold;
+    void clear() {
+        items.clear();
+        fold.clear();
+    }
+};
+void cut_items(const std::vector<Item>& items, std::vector<Entry>& entries, bool proxies, const ItemCut& cut,
+               CutItems& out);
+
 struct SymWork {
     std::vector<Entry> pp_entries, cc_entries, pc_entries;
     std::vector<Item> pp_items, cc_items, pc_items;

@@ -43,15 +43,22 @@ using namespace dev;
 
 [[noreturn]] void throw_hip(hipError_t e, const char* where);
 
+// The slots of this work group's item when it is a later piece of a cut one, else null.
+__device__ __forceinline__ double* piece_slot(const SymSlots& cut) {
+    if (!cut.ibase) return nullptr;
+    const int64_t b = cut.ibase[blockIdx.x];
+    return b >= 0 ? cut.slots + b : nullptr;
+}
+
 template <int KIND, bool F32, int T, bool PROXY_TGT>
 __global__ __launch_bounds__(kBlock) void k_interact(const DevItem* __restrict__ items,
                                                      const int2* __restrict__ entries, DevParticles tgt, DevTree Tt,
                                                      DevParticles src, DevTree S, const double* __restrict__ tab,
                                                      DegPtrs qhat, double param, double* __restrict__ out,
-                                                     DegOut pout, int add, double* __restrict__ nfp64) {
+                                                     DegOut pout, int add, double* __restrict__ nfp64, SymSlots cut) {
     __shared__ typename Stage<F32>::V lds[kChunk];
     interact_body<KIND, F32, T, PROXY_TGT>(items[blockIdx.x], entries, tgt, Tt, src, S, tab, qhat, param, out, pout,
-                                           lds, add != 0, nfp64);
+                                           lds, add != 0, nfp64, piece_slot(cut));
 }
 
 // MF selects the matrix-core form of the contraction (device.hpp).
@@ -534,7 +541,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) void k_pp_mfma(
     const DevItem* __restrict__ items, const int2* __restrict__ entries, DevParticles tgt, DevTree Tt,
     DevParticles src, DevTree S, const double* __restrict__ tab, DegPtrs qhat, double* __restrict__ out, int add,
-    double* __restrict__ nfp64) {
+    double* __restrict__ nfp64, SymSlots cut) {
     __shared__ MfmaLds L;
     const DevItem it = items[blockIdx.x];
     if (add && it.ee == it.eb) return;           // nothing to add (the whole group leaves together)
@@ -618,8 +625,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
     if (active) {
         const int row = 64 * wave + 16 * (col >> 2) + grp + 4 * (col & 3);
         const double v = reduce_rows(acc, col) + (row < it.tn ? L.corr[row] : 0.0);
+        double* slot = piece_slot(cut);
         if (row < it.tn) {
-            if (add) out[it.slot + row] += v;
+            if (slot) slot[row] = v;
+            else if (add) out[it.slot + row] += v;
             else out[it.slot + row] = v;
         }
     }
@@ -1034,14 +1043,14 @@ namespace {
 template <int KK, bool F32, bool PROXY_TGT>
 void launch_interact_t(int tpt, const DevItem* items, int n_items, const int2* entries, DevParticles tgt, DevTree Tt,
                        DevParticles src, DevTree S, const double* tab, DegPtrs qhat, double param, double* out,
-                       DegOut pout, int add, double* nfp64, hipStream_t st) {
+                       DegOut pout, int add, double* nfp64, SymSlots cut, hipStream_t st) {
     switch (tpt) {
     case 1: hipLaunchKernelGGL((k_interact<KK, F32, 1, PROXY_TGT>), dim3(n_items), dim3(kBlock), 0, st, items, entries,
-                               tgt, Tt, src, S, tab, qhat, param, out, pout, add, nfp64); break;
+                               tgt, Tt, src, S, tab, qhat, param, out, pout, add, nfp64, cut); break;
     case 2: hipLaunchKernelGGL((k_interact<KK, F32, 2, PROXY_TGT>), dim3(n_items), dim3(kBlock), 0, st, items, entries,
-                               tgt, Tt, src, S, tab, qhat, param, out, pout, add, nfp64); break;
+                               tgt, Tt, src, S, tab, qhat, param, out, pout, add, nfp64, cut); break;
     case 4: hipLaunchKernelGGL((k_interact<KK, F32, 4, PROXY_TGT>), dim3(n_items), dim3(kBlock), 0, st, items, entries,
-                               tgt, Tt, src, S, tab, qhat, param, out, pout, add, nfp64); break;
+                               tgt, Tt, src, S, tab, qhat, param, out, pout, add, nfp64, cut); break;
     default: throw Error(-1, "targets per thread must be 1, 2 or 4");
     }
 }
@@ -1049,11 +1058,11 @@ void launch_interact_t(int tpt, const DevItem* items, int n_items, const int2* e
 
 void launch_interact(KernelSpec k, bool fp32, bool proxy_targets, int tpt, const DevItem* items, int n_items,
                      const int2* entries, DevParticles tgt, DevTree Tt, DevParticles src, DevTree S, const double* tab,
-                     DegPtrs qhat, double* out, DegOut pout, hipStream_t st, bool add, double* nfp64) {
+                     DegPtrs qhat, double* out, DegOut pout, hipStream_t st, bool add, double* nfp64, SymSlots cut) {
     if (n_items <= 0) return;
     if (add && proxy_targets) throw Error(-1, "accumulating mode is for particle targets");
     if (fp32 && k.kind == K_POLY) throw Error(-5, "the polynomial test kernel runs in FP64 only");
-#define LAUNCH_ONE(F, PT) launch_interact_t<KK, F, PT>(tpt, items, n_items, entries, tgt, Tt, src, S, tab, qhat, k.param, out, pout, add ? OUT_ADD : OUT_WRITE, nfp64, st)
+#define LAUNCH_ONE(F, PT) launch_interact_t<KK, F, PT>(tpt, items, n_items, entries, tgt, Tt, src, S, tab, qhat, k.param, out, pout, add ? OUT_ADD : OUT_WRITE, nfp64, cut, st)
     if (fp32) {
         if (proxy_targets) { DISPATCH_KIND(k.kind, LAUNCH_ONE(true, true)); }
         else { DISPATCH_KIND(k.kind, LAUNCH_ONE(true, false)); }
@@ -1080,10 +1089,10 @@ void launch_down_leaf(int degree, bool mfma, const DevItem* items, int n_items, 
 
 void launch_pp_mfma(const DevItem* items, int n_items, const int2* entries, DevParticles tgt, DevTree Tt,
                     DevParticles src, DevTree S, const double* tab, DegPtrs qhat, double* out, bool add, double* nfp64,
-                    hipStream_t st) {
+                    hipStream_t st, SymSlots cut) {
     if (n_items <= 0) return;
     hipLaunchKernelGGL(k_pp_mfma, dim3(n_items), dim3(kBlock), 0, st, items, entries, tgt, Tt, src, S, tab, qhat, out,
-                       add ? 1 : 0, nfp64);
+                       add ? 1 : 0, nfp64, cut);
     CHECK_LAUNCH();
 }
 

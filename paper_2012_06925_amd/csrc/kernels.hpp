@@ -65,16 +65,24 @@ void launch_up_transfer(int degree, bool mfma, const int32_t* parents, int n_par
 void launch_down_transfer(int degree, bool mfma, const int32_t* kids, int n_kids, DevTree T, const double* tab,
                           double* phihat, hipStream_t st);
 
+// Slots of the items of a pass whose sums a fold adds to the outputs afterwards
+// (fold.hpp), and the slot base of each item.
+struct SymSlots {
+    double* slots = nullptr;
+    const int64_t* ibase = nullptr;
+};
+
 // Interaction sums: proxy_targets = false for PP + PC into the particles of a
 // leaf (out = potentials in tree order; with add, out += the sums), true for
 // CP + CC into the proxies of a cluster (pout = proxy potentials).  tpt:
 // targets per thread (1, 2 or 4).  nfp64 (device double, may be null): the
 // FP32 forms count there the pairs of distinct points they evaluate in FP64
-// because FP32 coordinates do not resolve them (here and below).
+// because FP32 coordinates do not resolve them (here and below).  cut: item i with
+// cut.ibase[i] >= 0 (a later piece of a cut item) writes its sums to those slots.
 void launch_interact(KernelSpec k, bool fp32, bool proxy_targets, int tpt, const DevItem* items, int n_items,
                      const int2* entries, DevParticles tgt, DevTree Tt, DevParticles src, DevTree S, const double* tab,
                      DegPtrs qhat, double* out, DegOut pout, hipStream_t st, bool add = false,
-                     double* nfp64 = nullptr);
+                     double* nfp64 = nullptr, SymSlots cut = {});
 
 // Symmetric passes (targets = sources; Coulomb in FP32, the four physical
 // kernels in FP64): items are tiles of a target
@@ -87,10 +95,6 @@ void launch_interact(KernelSpec k, bool fp32, bool proxy_targets, int tpt, const
 // come from the FP64 matrix cores.
 // guarded: the items' entries are all flagged SRC_RANGE_GUARD (else none is).
 constexpr int kSymTileLong = 512;     // targets per item at most for Yukawa, oscillatory, regularized Coulomb
-struct SymSlots {
-    double* slots;
-    const int64_t* ibase;
-};
 void launch_sym(KernelSpec k, bool fp32, bool mfma, bool proxies, bool guarded, const DevItem* items, int n_items,
                 const int2* entries, DevParticles p, DevTree T, const double* tab, DegPtrs qhat, double* nfp64,
                 SymSlots out, hipStream_t st);
@@ -112,7 +116,7 @@ void launch_sym_fold(const FoldSeg* segs, int n_segs, int max_n, const FoldPart*
 // Items must hold at most 256 targets; out[slot + r] = (add: +=) the sum.
 void launch_pp_mfma(const DevItem* items, int n_items, const int2* entries, DevParticles tgt, DevTree Tt,
                     DevParticles src, DevTree S, const double* tab, DegPtrs qhat, double* out, bool add, double* nfp64,
-                    hipStream_t st);
+                    hipStream_t st, SymSlots cut = {});
 
 // Proxy charges of every degree d < D in mask, restricted exactly from the
 // degree-D charges of each of the n_clusters clusters of T: to.p[d][c].

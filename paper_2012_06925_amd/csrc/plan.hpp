@@ -288,6 +288,11 @@ struct bldtt_plan {
     // folds of the symmetric passes: the main PP pass, the CC pass (and the proxy
     // side of the PC/CP pass), the leaves' self pairs, the particle side of the PC/CP pass
     DevFold fold_pp, fold_cc, fold_self, fold_pc;
+    // the one-way passes' items when some are cut (CutItems), with the folds of the
+    // pieces: near-field (per-pair degree form), particle and proxy targets
+    CutItems cut_near, cut_part, cut_prox;
+    DevBuf cut_near_items, cut_part_items, cut_prox_items;
+    DevFold fold_cut_near, fold_cut_part, fold_cut_prox;
     DevBuf model_buf;                        // device copy of the degree model (policy.dev_model)
     // FP32 evaluation: pairs of distinct points the last compute evaluated in
     // FP64 because FP32 coordinates do not resolve them (one device double)

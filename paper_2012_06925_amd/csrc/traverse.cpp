@@ -502,6 +502,97 @@ void pack_work(const Tree& T, const Tree& S, const Lists& L, int degree, int til
     sort_items(items, w.qitems);
 }
 
+void cut_items(const std::vector<Item>& items, std::vector<Entry>& entries, bool proxies, const ItemCut& cut,
+               CutItems& out) {
+    out.clear();
+    auto sources_of = [](const Entry& e) {
+        const int low = e.b & kCountMask;
+        return (uint32_t)e.b >> 29 == SRC_PROXY ? cube(low) : (int64_t)low;
+    };
+    // lanes of an item: its targets in whole waves
+    auto lanes_of = [](const Item& it) { return (int64_t)(it.tn + 63) / 64 * 64; };
+    std::vector<int64_t> src(items.size(), 0);
+    double total = 0.0;
+    for (size_t i = 0; i < items.size(); ++i) {
+        for (int32_t e = items[i].eb; e < items[i].ee; ++e) src[i] += sources_of(entries[e]);
+        total += (double)src[i] * (double)lanes_of(items[i]);
+    }
+    const double cap = std::max(1.0, total / (double)std::max<int64_t>(1, cut.want));
+    std::vector<std::pair<double, Item>> cost;
+    std::vector<int64_t> base;                            // slot base per item of `cost`, -1: the outputs
+    bool any = false;
+    cost.reserve(items.size());
+    for (size_t i = 0; i < items.size(); ++i) {
+        const Item& it = items[i];
+        const int64_t lanes = lanes_of(it);
+        const int64_t chunk = std::max((int64_t)std::min(cap / (double)lanes, 1e15), cut.min_src);
+        // no cut for less than half a chunk more than one
+        if (2 * src[i] < 3 * chunk) {
+            cost.push_back({(double)src[i] * (double)lanes, it});
+            base.push_back(-1);
+            continue;
+        }
+        any = true;
+        const int64_t pieces = (src[i] + chunk - 1) / chunk;
+        const int64_t each = ((src[i] + pieces - 1) / pieces + 255) / 256 * 256;   // whole rounds of the matrix-core pass
+        FoldSeg sg;
+        sg.off = proxies ? (int64_t)it.slot * cube(it.degree) + it.t0 : (int64_t)it.slot;
+        sg.n = it.tn;
+        sg.deg = proxies ? it.degree : -1;
+        sg.pb = (int32_t)out.fold.parts.size();
+        int32_t at = (int32_t)entries.size();
+        int64_t have = 0;
+        bool first = true;
+        auto close = [&] {
+            Item piece = it;
+            piece.eb = at;
+            piece.ee = at = (int32_t)entries.size();
+            cost.push_back({(double)have * (double)lanes, piece});
+            if (first) {
+                base.push_back(-1);
+                first = false;
+            } else {
+                base.push_back(out.fold.nslots);
+                out.fold.parts.push_back(FoldPart{out.fold.nslots, 0, it.tn});
+                out.fold.nslots += it.tn;
+            }
+            have = 0;
+        };
+        for (int32_t e = it.eb; e < it.ee; ++e) {
+            const Entry en = entries[e];                   // by value: entries grows below
+            if ((uint32_t)en.b >> 29 == SRC_PROXY) {       // a grid stays whole
+                entries.push_back(en);
+                have += sources_of(en);
+                if (have >= each) close();
+                continue;
+            }
+            const uint32_t kind = (uint32_t)en.b & ~(uint32_t)kCountMask;
+            for (int64_t a = en.a, n = en.b & kCountMask; n > 0;) {
+                const int64_t m = std::min(n, each - have);
+                entries.push_back(Entry{(int32_t)a, (int32_t)(kind | (uint32_t)m)});
+                a += m;
+                n -= m;
+                have += m;
+                if (have >= each) close();
+            }
+        }
+        if (have > 0) close();
+        sg.pe = (int32_t)out.fold.parts.size();
+        if (sg.pe > sg.pb) out.fold.segs.push_back(sg);
+    }
+    if (!any) return;
+    // longest first; the slot bases follow their items
+    std::vector<size_t> order(cost.size());
+    std::iota(order.begin(), order.end(), (size_t)0);
+    std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) { return cost[x].first > cost[y].first; });
+    out.items.reserve(order.size());
+    out.fold.ibase.reserve(order.size());
+    for (size_t k : order) {
+        out.items.push_back(cost[k].second);
+        out.fold.ibase.push_back(base[k]);
+    }
+}
+
 namespace {
 
 // Pairs of one type as CSR by target cluster: partner key (source cluster,

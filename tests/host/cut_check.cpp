@@ -108,9 +108,86 @@ void run(int64_t n, int64_t leaf, int degree, double theta, bool gauss, bool sep
     check(b.items >= a.items && d.items >= c.items, "a cut makes items, never fewer", b.items, a.items);
 }
 
+// One-way items: what the pieces give every output, the first of an item
+// directly and the others through slots and the fold, equals the whole items'.
+void run_one_way(int64_t m, int64_t n, int64_t leaf, int degree, double theta, int scheme, ItemCut cut) {
+    std::mt19937_64 rng(m * 7 + n);
+    std::normal_distribution<double> g(0.0, 0.4);
+    std::vector<double> x[3], y[3], sx[3], sy[3];
+    for (int d = 0; d < 3; ++d) {
+        x[d].resize(m);
+        y[d].resize(n);
+        for (double& a : x[d]) a = g(rng);
+        for (double& a : y[d]) a = g(rng);
+    }
+    Tree T, S;
+    build_tree(m, x[0].data(), x[1].data(), x[2].data(), leaf, T, sx[0], sx[1], sx[2]);
+    build_tree(n, y[0].data(), y[1].data(), y[2].data(), leaf, S, sy[0], sy[1], sy[2]);
+    Lists L;
+    traverse(T, S, theta, degree, scheme, L);
+    Work w;
+    pack_work(T, S, L, degree, 512, 512, w);
+    for (bool proxies : {false, true}) {
+        std::vector<Entry>& entries = proxies ? w.qentries : w.pentries;
+        const std::vector<Item>& items = proxies ? w.qitems : w.pitems;
+        const int64_t P = cube3(degree), nout = proxies ? T.size() * P : m;
+        auto sum = [&](const Item& it) {
+            double v = 0.0;
+            for (int32_t e = it.eb; e < it.ee; ++e) {
+                const int64_t low = entries[e].b & kCountMask;
+                const bool grid = (uint32_t)entries[e].b >> 29 == SRC_PROXY;
+                for (int64_t k = 0; k < (grid ? cube3((int)low) : low); ++k)
+                    v += weight(grid ? (1 << 20) + entries[e].a * 1000 + k : entries[e].a + k);
+            }
+            return v;
+        };
+        auto at = [&](const Item& it) { return proxies ? it.slot * P + it.t0 : (int64_t)it.slot; };
+        std::vector<double> want(nout, 0.0), got(nout, 0.0);
+        for (const Item& it : items)
+            for (int32_t r = 0; r < it.tn; ++r) want[at(it) + r] = sum(it);
+        CutItems c;
+        cut_items(items, entries, proxies, cut, c);
+        if (c.items.empty()) {
+            std::printf("  nothing to cut\n");
+            continue;
+        }
+        check(c.items.size() == c.fold.ibase.size(), "a base per piece");
+        std::vector<double> slots(c.fold.nslots, 0.0);
+        std::vector<int> direct(nout, 0);
+        int64_t empty = 0, whole_empty = 0;
+        for (size_t i = 0; i < c.items.size(); ++i) {
+            const Item& it = c.items[i];
+            empty += it.ee == it.eb;
+            for (int32_t r = 0; r < it.tn; ++r) {
+                if (c.fold.ibase[i] >= 0) slots[c.fold.ibase[i] + r] = sum(it);
+                else {
+                    got[at(it) + r] = sum(it);
+                    direct[at(it) + r]++;
+                }
+            }
+        }
+        for (const Item& it : items) whole_empty += it.ee == it.eb;
+        check(empty == whole_empty, "pieces hold sources", empty, whole_empty);
+        for (const FoldSeg& sg : c.fold.segs)
+            for (int32_t q = sg.pb; q < sg.pe; ++q)
+                for (int32_t k = 0; k < c.fold.parts[q].len; ++k)
+                    got[sg.off + c.fold.parts[q].lo + k] += slots[c.fold.parts[q].slot + k];
+        check(got == want, "one-way sums of the pieces", proxies);
+        for (const Item& it : items)
+            for (int32_t r = 0; r < it.tn; ++r) check(direct[at(it) + r] == 1, "one piece writes each output", it.slot, r);
+        std::printf("one-way m %lld n %lld proxies %d: %zu -> %zu items\n", (long long)m, (long long)n, proxies,
+                    items.size(), c.items.size());
+    }
+}
+
 }  // namespace
 
 int main() {
+    run_one_way(3000, 9000, 200, 3, 0.7, kSchemeDtt, ItemCut{4096, 256});
+    run_one_way(700, 20000, 1000, 5, 0.8, kSchemeBltc, ItemCut{4096, 256});
+    run_one_way(20000, 700, 300, 4, 0.8, kSchemeCpBltc, ItemCut{4096, 256});
+    run_one_way(10, 5000, 60, 2, 0.9, kSchemeDtt, ItemCut{1000000, 1});
+    run_one_way(5, 7, 60, 2, 0.9, kSchemeDtt, ItemCut{4096, 256});
     for (bool guarded : {false, true}) {
         run(4000, 60, 2, 0.7, false, guarded, 256, ItemCut{4096, 256});
         run(6000, 700, 3, 0.8, true, guarded, 256, ItemCut{100, 256});
