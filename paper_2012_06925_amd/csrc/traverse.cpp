@@ -20,6 +20,7 @@
 // starts at the target root, and separated target clusters with more than n_p
 // particles receive it by CP.
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <numeric>
 
@@ -159,10 +160,12 @@ void traverse_roots(const Tree& T, const Tree& S, const std::vector<std::pair<in
     Ctx x{T, S, theta, degree, scheme, defer_separated};
     out.clear();
     // Breadth-first expansion until there is enough independent work, then
-    // depth-first recursion per frontier pair on all threads.  Per-pair lists
-    // are concatenated in frontier order, so the output is deterministic.
+    // depth-first recursion on all threads, the frontier in as many runs as keep
+    // the threads even.  The runs' lists (kept per calling thread: no fresh pages
+    // per compute) are concatenated in frontier order, so the output is
+    // deterministic.
     std::vector<std::pair<int64_t, int64_t>> cur(roots), nxt;
-    const size_t want = (size_t)64 * num_threads();
+    const size_t want = (size_t)16 * num_threads();
     while (!cur.empty() && cur.size() < want) {
         nxt.clear();
         for (auto& pr : cur) {
@@ -171,19 +174,43 @@ void traverse_roots(const Tree& T, const Tree& S, const std::vector<std::pair<in
         }
         cur.swap(nxt);
     }
-    std::vector<Lists> part(cur.size());
-    parallel_run((int64_t)cur.size(), [&](int64_t i) { recurse(x, cur[i].first, cur[i].second, part[i]); });
+    const int64_t runs = std::min<int64_t>((int64_t)cur.size(), (int64_t)8 * num_threads());
+    static thread_local std::vector<Lists> tl_part;
+    std::vector<Lists>& part = tl_part;
+    if ((int64_t)part.size() < runs) part.resize(runs);
+    parallel_run(runs, [&](int64_t r) {
+        part[r].clear();
+        for (int64_t i = (int64_t)cur.size() * r / runs; i < (int64_t)cur.size() * (r + 1) / runs; ++i)
+            recurse(x, cur[i].first, cur[i].second, part[r]);
+    });
+    // list k of run r goes to [at[r][k], at[r][k] + its size); list 4: the deferred pairs
+    std::vector<std::array<size_t, 5>> at(runs + 1);
+    for (int k = 0; k < 4; ++k) at[0][k] = out.tc[k].size();
+    at[0][4] = out.sep_tc.size();
+    for (int64_t r = 0; r < runs; ++r) {
+        for (int k = 0; k < 4; ++k) at[r + 1][k] = at[r][k] + part[r].tc[k].size();
+        at[r + 1][4] = at[r][4] + part[r].sep_tc.size();
+    }
     for (int k = 0; k < 4; ++k) {
-        for (auto& p : part) {
-            out.tc[k].insert(out.tc[k].end(), p.tc[k].begin(), p.tc[k].end());
-            out.sc[k].insert(out.sc[k].end(), p.sc[k].begin(), p.sc[k].end());
-            out.deg[k].insert(out.deg[k].end(), p.deg[k].begin(), p.deg[k].end());
+        out.tc[k].resize(at[runs][k]);
+        out.sc[k].resize(at[runs][k]);
+        out.deg[k].resize(at[runs][k]);
+    }
+    out.sep_tc.resize(at[runs][4]);
+    out.sep_sc.resize(at[runs][4]);
+    parallel_run(runs, [&](int64_t r) {
+        const Lists& p = part[r];
+        for (int k = 0; k < 4; ++k) {
+            std::copy(p.tc[k].begin(), p.tc[k].end(), out.tc[k].begin() + at[r][k]);
+            std::copy(p.sc[k].begin(), p.sc[k].end(), out.sc[k].begin() + at[r][k]);
+            std::copy(p.deg[k].begin(), p.deg[k].end(), out.deg[k].begin() + at[r][k]);
         }
-    }
-    for (auto& p : part) {
-        out.sep_tc.insert(out.sep_tc.end(), p.sep_tc.begin(), p.sep_tc.end());
-        out.sep_sc.insert(out.sep_sc.end(), p.sep_sc.begin(), p.sep_sc.end());
-    }
+        std::copy(p.sep_tc.begin(), p.sep_tc.end(), out.sep_tc.begin() + at[r][4]);
+        std::copy(p.sep_sc.begin(), p.sep_sc.end(), out.sep_sc.begin() + at[r][4]);
+    });
+    // a large problem's lists are not kept beside the plan's own
+    for (int64_t r = 0; r < runs; ++r)
+        if (at[runs][0] + at[runs][3] + at[runs][4] > ((size_t)1 << 22)) part[r] = Lists();
 }
 
 namespace {
@@ -209,7 +236,7 @@ ByTarget group(const Tree& T, const Lists& L, int t0, int t1, int degree) {
         while (i >= base[ty - t0 + 1]) ++ty;
         e = i - base[ty - t0];
     };
-    const int64_t nch = std::max<int64_t>(1, std::min<int64_t>(4 * num_threads(), E / 16384 + 1));
+    const int64_t nch = std::max<int64_t>(1, std::min<int64_t>(4 * num_threads(), E / 4096 + 1));
     const int64_t per = (E + nch - 1) / nch;
     std::vector<int64_t> cnt(nch * nc, 0);
     parallel_run(nch, [&](int64_t k) {
@@ -371,7 +398,7 @@ void pack_work(const Tree& T, const Tree& S, const Lists& L, int degree, int til
     auto deg_of = [&](int ty, size_t e) { return L.deg[ty].empty() ? degree : (int)L.deg[ty][e]; };
     for (int ty = 0; ty < 4; ++ty) {
         const int64_t n = (int64_t)L.tc[ty].size();
-        const int64_t nch = std::max<int64_t>(1, std::min<int64_t>(4 * num_threads(), n / 16384 + 1));
+        const int64_t nch = std::max<int64_t>(1, std::min<int64_t>(4 * num_threads(), n / 4096 + 1));
         const int64_t per = (n + nch - 1) / nch;
         std::vector<double> acc(nch, 0.0);
         std::vector<uint32_t> sd(nch, 0), td(nch, 0);
@@ -595,18 +622,28 @@ void cut_items(const std::vector<Item>& items, std::vector<Entry>& entries, bool
 
 namespace {
 
-// Pairs of one type as CSR by target cluster: partner key (source cluster,
-// degree) sorted per target; only pairs accepted by `take`.
+// Pairs of one type as CSR by target cluster: partners sorted by (source
+// cluster, degree) per target, only pairs accepted by `take`, each with its
+// list position and a flag, set by mirror(), that its mirror is listed too.
 struct PairIndex {
+    struct Rec {
+        int64_t key;                 // source cluster << 4 | degree
+        int64_t e;                   // position in the list
+        bool operator<(const Rec& o) const { return key < o.key; }
+        int64_t sc() const { return key >> 4; }
+        int deg() const { return (int)(key & 15); }
+    };
+    static constexpr int64_t kBlk = 32;
     std::vector<int64_t> off, cnt;
-    std::vector<std::pair<int64_t, int>> part;
+    std::vector<Rec> part;
+    std::vector<uint8_t> both;       // per Rec
     template <class F>
     void build(int64_t nc, const std::vector<int64_t>& tc, const std::vector<int64_t>& sc, const std::vector<int8_t>& dg,
                int degree, F take) {
         // counting sort by target with per-chunk counts (see group); the order
         // within a target is fixed by the sort below
         const int64_t n = (int64_t)tc.size();
-        const int64_t nch = std::max<int64_t>(1, std::min<int64_t>(4 * num_threads(), n / 16384 + 1));
+        const int64_t nch = std::max<int64_t>(1, std::min<int64_t>(4 * num_threads(), n / 4096 + 1));
         const int64_t per = (n + nch - 1) / nch;
         cnt.assign(nch * nc, 0);
         parallel_run(nch, [&](int64_t k) {
@@ -625,19 +662,39 @@ struct PairIndex {
             off[c + 1] = run;
         }
         part.resize(off[nc]);
+        both.assign(off[nc], 0);
         parallel_run(nch, [&](int64_t k) {
             int64_t* fill = cnt.data() + k * nc;
             for (int64_t e = k * per; e < std::min(n, (k + 1) * per); ++e)
-                if (take(tc[e], sc[e])) part[fill[tc[e]]++] = {sc[e], dg.empty() ? degree : (int)dg[e]};
+                if (take(tc[e], sc[e])) part[fill[tc[e]]++] = Rec{sc[e] << 4 | (dg.empty() ? degree : (int)dg[e]), e};
         });
-        constexpr int64_t kBlk = 256;
         parallel_run((nc + kBlk - 1) / kBlk, [&](int64_t b) {
             for (int64_t c = b * kBlk; c < std::min(nc, (b + 1) * kBlk); ++c)
                 std::sort(part.begin() + off[c], part.begin() + off[c + 1]);
         });
     }
-    bool has(int64_t a, int64_t b, int d) const {
-        return std::binary_search(part.begin() + off[a], part.begin() + off[a + 1], std::make_pair(b, d));
+    // Flags every pair (a, b, d) here with (b, a, d) in `other`, on both sides, and
+    // clears their entries of `keep` (this list's) and `other_keep`.  One search per
+    // pair, by the smaller cluster when the two indexes are the same one: no two
+    // threads write one flag.
+    void mirror(PairIndex& other, std::vector<uint8_t>& keep, std::vector<uint8_t>& other_keep) {
+        const int64_t nc = (int64_t)off.size() - 1;
+        const bool same = &other == this;
+        parallel_run((nc + kBlk - 1) / kBlk, [&](int64_t blk) {
+            for (int64_t a = blk * kBlk; a < std::min(nc, (blk + 1) * kBlk); ++a)
+                for (int64_t k = off[a]; k < off[a + 1]; ++k) {
+                    const int64_t b = part[k].sc();
+                    if (same && b <= a) continue;
+                    const Rec want{a << 4 | part[k].deg(), 0};
+                    const auto end = other.part.begin() + other.off[b + 1];
+                    const auto it = std::lower_bound(other.part.begin() + other.off[b], end, want);
+                    if (it == end || it->key != want.key) continue;
+                    both[k] = 1;
+                    other.both[it - other.part.begin()] = 1;
+                    keep[part[k].e] = 0;
+                    other_keep[it->e] = 0;
+                }
+        });
     }
 };
 
@@ -719,36 +776,28 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
                      const ItemCut& cut) {
     sw.clear();
     const int64_t nc = T.size();
-    constexpr int64_t kBlk = 256;
+    constexpr int64_t kBlk = 32;
     const int64_t kTile = tile;
     const int64_t nblk = (nc + kBlk - 1) / kBlk;
     // kept per calling thread, so a plan repacked every compute touches no fresh
     // pages; the workers reach the caller's copies through these references
     static thread_local PairIndex tl_ipp, tl_icc, tl_ipc, tl_icp;
-    static thread_local std::vector<uint8_t> tl_keep;
+    static thread_local std::vector<uint8_t> tl_keep[4];
     PairIndex &ipp = tl_ipp, &icc = tl_icc, &ipc = tl_ipc, &icp = tl_icp;
-    std::vector<uint8_t>& keep = tl_keep;
+    std::vector<uint8_t>* keep = tl_keep;        // per entry: not one of a pair evaluated once for both
+    for (int k = 0; k < 4; ++k) keep[k].assign(L.tc[k].size(), 1);
     const std::vector<int8_t> no_degrees;        // PP pairs are matched without their degree
-    if (pp)
+    if (pp) {
         ipp.build(nc, L.tc[PP], L.sc[PP], no_degrees, 0,
                   [&](int64_t a, int64_t b) { return a != b && T.is_leaf(a) && T.is_leaf(b); });
-    if (cc) icc.build(nc, L.tc[CC], L.sc[CC], L.deg[CC], degree, [](int64_t a, int64_t b) { return a != b; });
-    auto sym_pp = [&](int64_t a, int64_t b) {
-        return pp && a != b && T.is_leaf(a) && T.is_leaf(b) && ipp.has(a, b, 0) && ipp.has(b, a, 0);
-    };
-    auto sym_cc = [&](int64_t a, int64_t b, int d) { return cc && a != b && icc.has(a, b, d) && icc.has(b, a, d); };
-    if (pc) {
-        auto all = [](int64_t, int64_t) { return true; };
-        ipc.build(nc, L.tc[PC], L.sc[PC], L.deg[PC], degree, all);        // particles of a <- proxies of b
-        icp.build(nc, L.tc[CP], L.sc[CP], L.deg[CP], degree, all);        // proxies of a <- particles of b
+        ipp.mirror(ipp, keep[PP], keep[PP]);
     }
-    // PC (a, b) listed with its mirror CP (b, a) at degree d
-    auto sym_pc = [&](int64_t a, int64_t b, int d) { return pc && ipc.has(a, b, d) && icp.has(b, a, d); };
+    // the indexes of CC, PC and CP pairs are formed after pp_ready, below
     // the most one item may cost, from the symmetric pairs' kernel values
     auto cost_cap = [&](const std::vector<int64_t>& tc, const std::vector<int64_t>& sc, auto&& values) {
         if (cut.want <= 0) return 1e300;
         const int64_t n = (int64_t)tc.size();
-        const int64_t nch = std::max<int64_t>(1, std::min<int64_t>(4 * num_threads(), n / 16384 + 1));
+        const int64_t nch = std::max<int64_t>(1, std::min<int64_t>(4 * num_threads(), n / 4096 + 1));
         const int64_t per = (n + nch - 1) / nch;
         std::vector<double> part(nch, 0.0);
         parallel_run(nch, [&](int64_t k) {
@@ -772,8 +821,8 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
                 if (!T.is_leaf(a)) continue;
                 double src = 0.0;
                 for (int64_t k = ipp.off[a]; k < ipp.off[a + 1]; ++k) {
-                    const int64_t b = ipp.part[k].first;
-                    if (b > a && ipp.has(b, a, 0)) {
+                    const int64_t b = ipp.part[k].sc();
+                    if (b > a && ipp.both[k]) {
                         ((sw.guard_near ? range_guarded(T, a, T, b) : boxes_touch(T, a, T, b)) ? rg : rp)
                             .emplace_back(T.begin[b], T.count[b]);
                         src += (double)T.count[b];
@@ -826,8 +875,19 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
         fold_bases(sw.pp_items, sw.pp_entries, false, sw.pp_fold);
     }
     if (pp_ready) pp_ready();
+    if (cc) {
+        icc.build(nc, L.tc[CC], L.sc[CC], L.deg[CC], degree, [](int64_t a, int64_t b) { return a != b; });
+        icc.mirror(icc, keep[CC], keep[CC]);
+    }
+    if (pc) {
+        // PC (a, b) listed with its mirror CP (b, a) at the same degree
+        auto all = [](int64_t, int64_t) { return true; };
+        ipc.build(nc, L.tc[PC], L.sc[PC], L.deg[PC], degree, all);        // particles of a <- proxies of b
+        icp.build(nc, L.tc[CP], L.sc[CP], L.deg[CP], degree, all);        // proxies of a <- particles of b
+        ipc.mirror(icp, keep[PC], keep[CP]);
+    }
     // the rest: every entry except both directions of the symmetric pairs,
-    // in list order (flags and per-chunk compaction on all threads)
+    // in list order (per-chunk compaction on all threads)
     for (int k = 0; k < 4; ++k) {
         const bool typed = !L.deg[k].empty();
         const int64_t n = (int64_t)L.tc[k].size();
@@ -838,19 +898,13 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
             rest.deg[k] = L.deg[k];
             continue;
         }
-        const int64_t nch = std::max<int64_t>(1, std::min<int64_t>(4 * num_threads(), n / 16384 + 1));
+        const uint8_t* kp = keep[k].data();
+        const int64_t nch = std::max<int64_t>(1, std::min<int64_t>(4 * num_threads(), n / 4096 + 1));
         const int64_t per = (n + nch - 1) / nch;
-        keep.resize(n);
         std::vector<int64_t> kept(nch + 1, 0);
         parallel_run(nch, [&](int64_t c) {
             int64_t m = 0;
-            for (int64_t e = c * per; e < std::min(n, (c + 1) * per); ++e) {
-                const int64_t a = L.tc[k][e], b = L.sc[k][e];
-                const int d = typed ? (int)L.deg[k][e] : degree;
-                keep[e] = !((k == PP && sym_pp(a, b)) || (k == CC && sym_cc(a, b, d)) || (k == PC && sym_pc(a, b, d)) ||
-                            (k == CP && sym_pc(b, a, d)));
-                m += keep[e];
-            }
+            for (int64_t e = c * per; e < std::min(n, (c + 1) * per); ++e) m += kp[e];
             kept[c + 1] = m;
         });
         for (int64_t c = 0; c < nch; ++c) kept[c + 1] += kept[c];
@@ -860,7 +914,7 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
         parallel_run(nch, [&](int64_t c) {
             int64_t o = kept[c];
             for (int64_t e = c * per; e < std::min(n, (c + 1) * per); ++e) {
-                if (!keep[e]) continue;
+                if (!kp[e]) continue;
                 rest.tc[k][o] = L.tc[k][e];
                 rest.sc[k][o] = L.sc[k][e];
                 if (typed) rest.deg[k][o] = L.deg[k][e];
@@ -882,13 +936,13 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
             SymBlock& B = blks[bi];
             for (int64_t a = bi * kBlk; a < std::min(nc, (bi + 1) * kBlk); ++a) {
                 uint32_t used = 0;
-                for (int64_t q = icc.off[a]; q < icc.off[a + 1]; ++q) used |= 1u << icc.part[q].second;
+                for (int64_t q = icc.off[a]; q < icc.off[a + 1]; ++q) used |= icc.both[q] ? 1u << icc.part[q].deg() : 0u;
                 for (int d = 0; d <= kMaxDegree; ++d) {
                     if (!(used >> d & 1)) continue;
                     const int64_t eb = (int64_t)B.entries.size();
                     for (int64_t q = icc.off[a]; q < icc.off[a + 1]; ++q) {
-                        const int64_t b = icc.part[q].first;
-                        if (icc.part[q].second == d && b > a && icc.has(b, a, d))
+                        const int64_t b = icc.part[q].sc();
+                        if (icc.part[q].deg() == d && b > a && icc.both[q])
                             B.entries.push_back(Entry{(int32_t)b, (int32_t)((uint32_t)SRC_PROXY << 29 | (uint32_t)d)});
                     }
                     const int64_t ee = (int64_t)B.entries.size();
@@ -923,13 +977,13 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
             SymBlock& B = blks[bi];
             for (int64_t a = bi * kBlk; a < std::min(nc, (bi + 1) * kBlk); ++a) {
                 uint32_t used = 0;
-                for (int64_t q = ipc.off[a]; q < ipc.off[a + 1]; ++q) used |= 1u << ipc.part[q].second;
+                for (int64_t q = ipc.off[a]; q < ipc.off[a + 1]; ++q) used |= ipc.both[q] ? 1u << ipc.part[q].deg() : 0u;
                 for (int d = 0; d <= kMaxDegree; ++d) {
                     if (!(used >> d & 1)) continue;
                     const int64_t eb = (int64_t)B.entries.size();
                     for (int64_t q = ipc.off[a]; q < ipc.off[a + 1]; ++q) {
-                        const int64_t b = ipc.part[q].first;
-                        if (ipc.part[q].second == d && icp.has(b, a, d))
+                        const int64_t b = ipc.part[q].sc();
+                        if (ipc.part[q].deg() == d && ipc.both[q])
                             B.entries.push_back(Entry{(int32_t)b, (int32_t)((uint32_t)SRC_PROXY << 29 | (uint32_t)d)});
                     }
                     const int64_t ee = (int64_t)B.entries.size();

@@ -26,6 +26,9 @@
 #include <condition_variable>
 #include <cstdlib>
 #include <cstring>
+#include <exception>
+#include <functional>
+#include <memory>
 #include <mutex>
 #include <thread>
 
@@ -38,7 +41,21 @@ namespace bldtt {
 // ---------------------------------------------------------------------------
 namespace {
 
+// One parallel region at a time.  The regions of a summation are short (tens of
+// microseconds for small problems) and follow each other closely, so a region is
+// over when its tasks are, not when every worker has looked at it; workers watch
+// for the next region for a short while before they sleep, and only as many
+// sleepers are woken as there are tasks.  (Waking and awaiting every worker made
+// the list packing of 7E4 particles slower on 16 threads than on one.)
 class Pool {
+    struct Job {
+        const std::function<void(int64_t)>* fn = nullptr;
+        int64_t n = 0;
+        std::atomic<int64_t> next{0}, done{0};
+        std::mutex m;
+        std::exception_ptr error;            // the first a task threw
+    };
+
 public:
     Pool() {
         int n = (int)std::thread::hardware_concurrency();
@@ -52,7 +69,7 @@ public:
         {
             std::lock_guard<std::mutex> g(m_);
             stop_ = true;
-            ++gen_;
+            gen_.fetch_add(1);
         }
         cv_.notify_all();
         for (auto& t : workers_) t.join();
@@ -66,53 +83,87 @@ public:
             return;
         }
         std::unique_lock<std::mutex> outer(run_m_);   // one parallel region at a time
+        auto job = std::make_shared<Job>();
+        job->fn = &fn;
+        job->n = n;
+        int64_t wake;
         {
             std::lock_guard<std::mutex> g(m_);
-            fn_ = &fn;
-            n_ = n;
-            next_.store(0);
-            active_ = (int)workers_.size();
-            ++gen_;
+            job_ = job;
+            gen_.fetch_add(1);
+            wake = std::min<int64_t>(sleepers_, n - 1);
         }
-        cv_.notify_all();
-        work();
-        std::unique_lock<std::mutex> g(m_);
-        done_cv_.wait(g, [this] { return active_ == 0; });
-        fn_ = nullptr;
+        for (int64_t i = 0; i < wake; ++i) cv_.notify_one();
+        work(*job);
+        for (int spin = 0; job->done.load(std::memory_order_acquire) < n; ++spin) {
+            if (spin < kSpins) {
+                pause();
+                continue;
+            }
+            std::unique_lock<std::mutex> g(m_);
+            waiting_ = true;
+            done_cv_.wait(g, [&] { return job->done.load() >= n; });
+            waiting_ = false;
+        }
+        {
+            std::lock_guard<std::mutex> g(m_);
+            job_.reset();
+        }
+        if (job->error) std::rethrow_exception(job->error);
     }
 
 private:
-    void work() {
+    static constexpr int kSpins = 2000;               // some tens of microseconds
+    static void pause() {
+#if defined(__x86_64__)
+        __builtin_ia32_pause();
+#endif
+    }
+    // A worker may arrive after its job is over: it then finds no index left and
+    // never touches fn, which lives only as long as run().
+    void work(Job& job) {
         for (;;) {
-            int64_t i = next_.fetch_add(1);
-            if (i >= n_) break;
-            (*fn_)(i);
+            const int64_t i = job.next.fetch_add(1);
+            if (i >= job.n) break;
+            try {
+                (*job.fn)(i);
+            } catch (...) {
+                std::lock_guard<std::mutex> g(job.m);
+                if (!job.error) job.error = std::current_exception();
+            }
+            if (job.done.fetch_add(1) + 1 == job.n) {
+                std::lock_guard<std::mutex> g(m_);
+                if (waiting_) done_cv_.notify_one();
+            }
         }
     }
     void loop() {
         uint64_t seen = 0;
         for (;;) {
+            for (int spin = 0; spin < kSpins && gen_.load(std::memory_order_acquire) == seen; ++spin) pause();
+            std::shared_ptr<Job> job;
             {
                 std::unique_lock<std::mutex> g(m_);
-                cv_.wait(g, [&] { return gen_ != seen; });
-                seen = gen_;
+                if (gen_.load() == seen) {
+                    ++sleepers_;
+                    cv_.wait(g, [&] { return gen_.load() != seen; });
+                    --sleepers_;
+                }
+                seen = gen_.load();
                 if (stop_) return;
+                job = job_;
             }
-            work();
-            std::lock_guard<std::mutex> g(m_);
-            if (--active_ == 0) done_cv_.notify_one();
+            if (job) work(*job);
         }
     }
     int nthreads_ = 1;
     std::vector<std::thread> workers_;
     std::mutex m_, run_m_;
     std::condition_variable cv_, done_cv_;
-    const std::function<void(int64_t)>* fn_ = nullptr;
-    int64_t n_ = 0;
-    std::atomic<int64_t> next_{0};
-    int active_ = 0;
-    uint64_t gen_ = 0;
-    bool stop_ = false;
+    std::shared_ptr<Job> job_;
+    std::atomic<uint64_t> gen_{0};
+    int64_t sleepers_ = 0;
+    bool waiting_ = false, stop_ = false;
 };
 
 Pool& pool() {
