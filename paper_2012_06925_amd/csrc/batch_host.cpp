@@ -305,7 +305,11 @@ void pack(bldtt_batch* b, int tpt) {
     Work& w = b->work;
     w.guard_near = (b->flags & BLDTT_FP32_EVAL) != 0;   // FP32 batches guard near particle ranges too
     if (b->symmetric()) {
-        split_symmetric(b->T(), b->lists, b->degree, true, true, b->rest, b->sym, {}, false, true);
+        // few tasks per resident work group: cut the longest (a task costs fences and
+        // counters, so not as finely as the single plans: 40 problems of up to 1E5
+        // particles 8.25 ms uncut, 7.97 with 2048, 8.41 with 8192; 20 of up to 2E4
+        // 0.97 / 0.83 / 1.05 ms)
+        split_symmetric(b->T(), b->lists, b->degree, true, true, b->rest, b->sym, {}, false, true, 256, ItemCut{2048, 256});
         const std::vector<uint32_t> extra = sym_cc_degrees(b->T(), b->sym);
         pack_work(b->T(), b->S, b->rest, b->degree, kThreads * tpt, kThreads * tpt, w, &extra);
     } else {
