@@ -50,7 +50,25 @@ void upload_bytes(DevBuf& b, const void* src, size_t n) {
     if (n) HIPCHK(hipMemcpy(b.p, src, n, hipMemcpyHostToDevice));
 }
 
-void upload_tree(DevTreeBufs& d, const Tree& t) {
+void SetupUpload::add(DevBuf& b, const void* src, size_t n) {
+    if (n > (size_t)1 << 16) {
+        upload_bytes(b, src, n);
+        return;
+    }
+    const size_t off = (host.size() + 255) & ~(size_t)255;
+    host.resize(off + n);
+    if (n) std::memcpy(host.data() + off, src, n);
+    parts.push_back(Part{&b, off, n});
+}
+
+void SetupUpload::flush(DevBuf& arena) {
+    upload_bytes(arena, host.data(), host.size());
+    for (const Part& p : parts) p.dst->alias(static_cast<char*>(arena.p) + p.off, p.n);
+    parts.clear();
+    host.clear();
+}
+
+void upload_tree(DevTreeBufs& d, const Tree& t, SetupUpload* u) {
     int64_t nc = t.size();
     std::vector<double> box(6 * nc);
     std::vector<int32_t> begin(nc), count(nc), nchild(nc), child(8 * nc), parent(nc);
@@ -65,12 +83,15 @@ void upload_tree(DevTreeBufs& d, const Tree& t) {
         parent[c] = (int32_t)t.parent[c];
         for (int k = 0; k < 8; ++k) child[8 * c + k] = (int32_t)t.child[8 * c + k];
     }
-    upload(d.box, box);
-    upload(d.begin, begin);
-    upload(d.count, count);
-    upload(d.nchild, nchild);
-    upload(d.child, child);
-    upload(d.parent, parent);
+    SetupUpload own;
+    SetupUpload& to = u ? *u : own;
+    to.add(d.box, box);
+    to.add(d.begin, begin);
+    to.add(d.count, count);
+    to.add(d.nchild, nchild);
+    to.add(d.child, child);
+    to.add(d.parent, parent);
+    if (!u) own.flush(d.arena);
 }
 
 bool all_finite(const double* a, int64_t n) {
@@ -254,7 +275,7 @@ struct Upload {
 // symmetric kernels' tile: the pairs inside a tile one-sided (guarded: i = j
 // and coincident points give r = 0), and each tile against the leaf's later
 // particles symmetric, once for both (longest first).
-void ensure_self_work(bldtt_plan* pl) {
+void ensure_self_work(bldtt_plan* pl, SetupUpload& up) {
     if (pl->self_ready) return;
     const Tree& T = pl->T();
     constexpr int64_t kTile = 256;
@@ -285,17 +306,17 @@ void ensure_self_work(bldtt_plan* pl) {
     std::vector<Item> sym;
     sym.reserve(si.size());
     for (auto& x : si) sym.push_back(x.second);
-    upload_bytes(pl->self_items, di.data(), sizeof(Item) * di.size());
-    upload_bytes(pl->self_entries, de.data(), sizeof(Entry) * de.size());
-    upload_bytes(pl->self_sym_items, sym.data(), sizeof(Item) * sym.size());
-    upload_bytes(pl->self_sym_entries, se.data(), sizeof(Entry) * se.size());
+    up.add(pl->self_items, di);
+    up.add(pl->self_entries, de);
+    up.add(pl->self_sym_items, sym);
+    up.add(pl->self_sym_entries, se);
     SymFold fold;
     build_fold(T, sym, se, false, fold);
     DevFold& f = pl->fold_self;
     f.slots.alloc(sizeof(double) * (size_t)std::max<int64_t>(fold.nslots, 1));
-    upload(f.ibase, fold.ibase);
-    upload(f.segs, fold.segs);
-    upload(f.parts, fold.parts);
+    up.add(f.ibase, fold.ibase);
+    up.add(f.segs, fold.segs);
+    up.add(f.parts, fold.parts);
     f.set_segments(fold);
     pl->n_self_items = (int)di.size();
     pl->n_self_sym_items = (int)sym.size();
@@ -465,7 +486,6 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
     // ... and the self pairs of the leaves (known before the traversal) write
     // the particle potentials first; every later particle pass adds
     if (symm) {
-        ensure_self_work(pl);
         PhaseMark mark(pl, BLDTT_PH_PP_SELF, st);
         particle_pass(pl->self_items, pl->n_self_items, pl->self_entries, false, st);
         const DevFold& f = pl->fold_self;
@@ -727,7 +747,7 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
 
 // Trees built on the host: the particles copied down, the trees built, the
 // permuted particles copied up.
-void setup_host_tree(bldtt_plan* pl, const bldtt_particles* p, hipStream_t st) {
+void setup_host_tree(bldtt_plan* pl, const bldtt_particles* p, hipStream_t st, SetupUpload& up) {
     (void)st;
     const int64_t M = p->M, N = p->N;
     std::vector<double> hs[4], ht[3];
@@ -752,12 +772,12 @@ void setup_host_tree(bldtt_plan* pl, const bldtt_particles* p, hipStream_t st) {
     upload(pl->sy, sxs[1]);
     upload(pl->sz, sxs[2]);
     upload(pl->sq, qs);
-    upload_tree(pl->dS, pl->S);
+    upload_tree(pl->dS, pl->S, &up);
     if (!pl->aliased) {
         upload(pl->tx, txs[0]);
         upload(pl->ty, txs[1]);
         upload(pl->tz, txs[2]);
-        upload_tree(pl->dTsep, pl->Tsep);
+        upload_tree(pl->dTsep, pl->Tsep, &up);
     }
 }
 
@@ -770,6 +790,7 @@ void setup_device(bldtt_plan* pl, const bldtt_particles* p, hipStream_t st) {
         HIPCHK(hipDeviceGetAttribute(&pl->cus, hipDeviceAttributeMultiprocessorCount, dev));
     }
     const int64_t M = p->M, N = p->N;
+    SetupUpload up;
     if (pl->flags & BLDTT_DEVICE_TREE) {
         // trees built on the GPU (treebuild.hip): the particles never leave the device
         const double* src[4] = {p->sx, p->sy, p->sz, p->q};
@@ -781,32 +802,32 @@ void setup_device(bldtt_plan* pl, const bldtt_particles* p, hipStream_t st) {
         DevBuf sidx, tidx;
         build_tree_device(N, p->sx, p->sy, p->sz, pl->leaf, pl->S, pl->sx, pl->sy, pl->sz, sidx, st);
         gather_device(p->q, sidx, N, pl->sq, st);
-        upload_tree(pl->dS, pl->S);
+        upload_tree(pl->dS, pl->S, &up);
         if (!pl->aliased) {
             build_tree_device(M, p->tx, p->ty, p->tz, pl->leaf, pl->Tsep, pl->tx, pl->ty, pl->tz, tidx, st);
-            upload_tree(pl->dTsep, pl->Tsep);
+            upload_tree(pl->dTsep, pl->Tsep, &up);
         }
         HIPCHK(hipStreamSynchronize(st));
     } else {
-        setup_host_tree(pl, p, st);
+        setup_host_tree(pl, p, st, up);
     }
     const Tree& T = pl->T();
     std::vector<int32_t> perm(M);
     for (int64_t i = 0; i < M; ++i) perm[i] = (int32_t)T.perm[i];
-    upload(pl->perm, perm);
-    upload(pl->tab, node_table());
+    up.add(pl->perm, perm);
+    up.add(pl->tab, node_table());
     std::vector<int32_t> leaves;
     for (int64_t c = 0; c < pl->S.size(); ++c)
         if (pl->S.is_leaf(c)) leaves.push_back((int32_t)c);
-    upload(pl->src_leaves, leaves);
+    up.add(pl->src_leaves, leaves);
     pl->n_src_leaves = (int)leaves.size();
     pl->n_tgt_leaves = 0;
     for (int64_t c = 0; c < T.size(); ++c) pl->n_tgt_leaves += T.is_leaf(c) ? 1 : 0;
     std::vector<int32_t> ids;
     level_lists(pl->S, true, ids, pl->up_off);
-    upload(pl->up_parents, ids);
+    up.add(pl->up_parents, ids);
     level_lists(T, false, ids, pl->down_off);
-    upload(pl->down_kids, ids);
+    up.add(pl->down_kids, ids);
     pl->phi_tree.alloc(sizeof(double) * M);
     if (pl->flags & BLDTT_FP32_EVAL) {
         pl->nfp64.alloc(sizeof(double));
@@ -828,7 +849,8 @@ void setup_device(bldtt_plan* pl, const bldtt_particles* p, hipStream_t st) {
         for (auto& set : pl->prof_ev)
             for (auto& e : set) HIPCHK(hipEventCreate(&e));
     HIPCHK(hipEventRecord(pl->staging_free, st));
-    if (pl->symmetric_pp()) ensure_self_work(pl);
+    if (pl->symmetric_pp()) ensure_self_work(pl, up);
+    up.flush(pl->arena_setup);
     if (pl->device_walk()) walk_upload(pl->walk, T, pl->S, pl->aliased);
     fill_stats_tree(pl);
     pl->stats.setup_ms = now_ms() - t0;

@@ -116,7 +116,7 @@ struct PinnedBuf {
 };
 
 struct DevTreeBufs {
-    DevBuf box, begin, count, nchild, child, parent;
+    DevBuf arena, box, begin, count, nchild, child, parent;
     DevTree view() const {
         return DevTree{box.as<double>(), begin.as<int32_t>(), count.as<int32_t>(), nchild.as<int32_t>(),
                        child.as<int32_t>(), parent.as<int32_t>()};
@@ -170,11 +170,27 @@ bool all_finite_device(const double* const* arrays, int count, int64_t n, hipStr
 // to[i] = from[idx[i]] on the device (to allocated here).
 void gather_device(const double* from, const DevBuf& idx, int64_t n, DevBuf& to, hipStream_t st);
 
+// The many small arrays of a plan's setup, gathered on the host and copied once
+// into one device buffer that they become views of (a copy of its own costs
+// each 15 to 35 us); arrays above 64 KiB are copied by themselves.
+struct SetupUpload {
+    std::vector<char> host;
+    struct Part {
+        DevBuf* dst;
+        size_t off, n;
+    };
+    std::vector<Part> parts;
+    void add(DevBuf& b, const void* src, size_t n);
+    template <class T>
+    void add(DevBuf& b, const std::vector<T>& v) { add(b, v.data(), sizeof(T) * v.size()); }
+    void flush(DevBuf& arena);
+};
+
 // Host helpers shared by the plan and the batch (capi.cpp).
 void upload_bytes(DevBuf& b, const void* src, size_t n);
 template <class T>
 inline void upload(DevBuf& b, const std::vector<T>& v) { upload_bytes(b, v.data(), sizeof(T) * v.size()); }
-void upload_tree(DevTreeBufs& d, const Tree& t);
+void upload_tree(DevTreeBufs& d, const Tree& t, SetupUpload* u = nullptr);
 bool all_finite(const double* a, int64_t n);
 void validate(const bldtt_particles* p, int32_t kernel, double theta, int32_t degree, int64_t leaf_size);
 void level_lists(const Tree& t, bool parents, std::vector<int32_t>& ids, std::vector<int64_t>& off);
@@ -243,6 +259,7 @@ struct bldtt_plan {
     bool mfma_transfer() const { return (flags & BLDTT_VALU_PASSES) == 0; }   // and the FP32 symmetric passes
     bool mfma_leaf() const { return (flags & BLDTT_MFMA_LEAF) != 0; }
     PinnedBuf staging;
+    DevBuf arena_setup;                      // the small arrays of the setup
     DevBuf arena, arena_near, arena_rest;                // device side of the per-compute uploads (one copy each)
     uint32_t fill_degrees_last = 0;          // degrees of proxy potentials cleared by the last compute
     hipEvent_t staging_free = nullptr;

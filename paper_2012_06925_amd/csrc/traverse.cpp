@@ -166,7 +166,8 @@ void traverse_roots(const Tree& T, const Tree& S, const std::vector<std::pair<in
     // deterministic.
     std::vector<std::pair<int64_t, int64_t>> cur(roots), nxt;
     const size_t want = (size_t)16 * num_threads();
-    while (!cur.empty() && cur.size() < want) {
+    const bool small = T.size() + S.size() < 128;         // some thousand pairs: not worth waking threads
+    while (!small && !cur.empty() && cur.size() < want) {
         nxt.clear();
         for (auto& pr : cur) {
             int ty = step(x, pr.first, pr.second, [&](int64_t a, int64_t b) { nxt.emplace_back(a, b); });
@@ -174,7 +175,7 @@ void traverse_roots(const Tree& T, const Tree& S, const std::vector<std::pair<in
         }
         cur.swap(nxt);
     }
-    const int64_t runs = std::min<int64_t>((int64_t)cur.size(), (int64_t)8 * num_threads());
+    const int64_t runs = small ? 1 : std::min<int64_t>((int64_t)cur.size(), (int64_t)8 * num_threads());
     static thread_local std::vector<Lists> tl_part;
     std::vector<Lists>& part = tl_part;
     if ((int64_t)part.size() < runs) part.resize(runs);
@@ -633,8 +634,8 @@ struct PairIndex {
         int64_t sc() const { return key >> 4; }
         int deg() const { return (int)(key & 15); }
     };
-    static constexpr int64_t kBlk = 32;
     std::vector<int64_t> off, cnt;
+    int64_t kBlk = 32;               // clusters per task
     std::vector<Rec> part;
     std::vector<uint8_t> both;       // per Rec
     template <class F>
@@ -643,6 +644,7 @@ struct PairIndex {
         // counting sort by target with per-chunk counts (see group); the order
         // within a target is fixed by the sort below
         const int64_t n = (int64_t)tc.size();
+        kBlk = n < 4096 ? std::max<int64_t>(1, nc) : 32;
         const int64_t nch = std::max<int64_t>(1, std::min<int64_t>(4 * num_threads(), n / 4096 + 1));
         const int64_t per = (n + nch - 1) / nch;
         cnt.assign(nch * nc, 0);
@@ -702,6 +704,12 @@ struct SymBlock {
     std::vector<Entry> entries;
     std::vector<std::pair<double, Item>> items, gitems;    // items without / with guarded ranges
     double evals = 0.0;
+    void clear() {
+        entries.clear();
+        items.clear();
+        gitems.clear();
+        evals = 0.0;
+    }
 };
 
 // The particle-range entries [at, end) of E cut at every multiple of `chunk`
@@ -776,7 +784,10 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
                      const ItemCut& cut) {
     sw.clear();
     const int64_t nc = T.size();
-    constexpr int64_t kBlk = 32;
+    // small problems stay on this thread: their regions cost more than they do
+    size_t listed = 0;
+    for (int k = 0; k < 4; ++k) listed += L.tc[k].size();
+    const int64_t kBlk = listed < 4096 ? std::max<int64_t>(1, nc) : 32;
     const int64_t kTile = tile;
     const int64_t nblk = (nc + kBlk - 1) / kBlk;
     // kept per calling thread, so a plan repacked every compute touches no fresh
@@ -793,6 +804,15 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
         ipp.mirror(ipp, keep[PP], keep[PP]);
     }
     // the indexes of CC, PC and CP pairs are formed after pp_ready, below
+    // the blocks of one list type at a time, kept like the indexes
+    static thread_local std::vector<SymBlock> tl_blks;
+    std::vector<SymBlock>& all_blks = tl_blks;
+    auto blocks = [&]() -> std::vector<SymBlock>& {
+        if ((int64_t)all_blks.size() > 4 * nblk + 1024) all_blks.clear();      // a much larger problem's
+        all_blks.resize(nblk);
+        for (SymBlock& b : all_blks) b.clear();
+        return all_blks;
+    };
     // the most one item may cost, from the symmetric pairs' kernel values
     auto cost_cap = [&](const std::vector<int64_t>& tc, const std::vector<int64_t>& sc, auto&& values) {
         if (cut.want <= 0) return 1e300;
@@ -812,7 +832,7 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
             return a != b && T.is_leaf(a) && T.is_leaf(b) ? 0.5 * (double)T.count[a] * (double)T.count[b] : 0.0;
         });
         // per leaf A: the partners B > A as merged particle ranges, tiles of A's particles
-        std::vector<SymBlock> blks(nblk);
+        std::vector<SymBlock>& blks = blocks();
         parallel_run(nblk, [&](int64_t bi) {
             SymBlock& B = blks[bi];
             std::vector<std::pair<int64_t, int64_t>> rp, rg, none;
@@ -931,7 +951,7 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
         });
         // per (cluster A, degree d): the partners B > A at d, tiles of A's
         // proxies, as many partners per item as the cap allows
-        std::vector<SymBlock> blks(nblk);
+        std::vector<SymBlock>& blks = blocks();
         parallel_run(nblk, [&](int64_t bi) {
             SymBlock& B = blks[bi];
             for (int64_t a = bi * kBlk; a < std::min(nc, (bi + 1) * kBlk); ++a) {
@@ -972,7 +992,7 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
         });
         // per (cluster A, degree d): the partners B whose PC and CP pairs with A
         // are both listed at d, as proxy entries; tiles of A's particles
-        std::vector<SymBlock> blks(nblk);
+        std::vector<SymBlock>& blks = blocks();
         parallel_run(nblk, [&](int64_t bi) {
             SymBlock& B = blks[bi];
             for (int64_t a = bi * kBlk; a < std::min(nc, (bi + 1) * kBlk); ++a) {
@@ -1129,7 +1149,7 @@ void fold_group_parts(const Tree& T, bool proxies, const std::vector<FoldGroup>&
     // parts grouped by segment, chunks of items in order (a parallel counting
     // sort: chunk k's parts of a segment follow those of chunks < k)
     const int64_t ns = (int64_t)f.segs.size();
-    const int64_t nch = std::max<int64_t>(1, std::min<int64_t>(4 * num_threads(), ni / 64 + 1));
+    const int64_t nch = std::max<int64_t>(1, std::min<int64_t>(num_threads(), ni / 256 + 1));
     const int64_t per = (ni + nch - 1) / nch;
     std::vector<int32_t> cnt(nch * ns, 0);
     parallel_run(nch, [&](int64_t k) {

@@ -28,7 +28,6 @@
 #include <cstring>
 #include <exception>
 #include <functional>
-#include <memory>
 #include <mutex>
 #include <thread>
 
@@ -44,18 +43,16 @@ namespace {
 // One parallel region at a time.  The regions of a summation are short (tens of
 // microseconds for small problems) and follow each other closely, so a region is
 // over when its tasks are, not when every worker has looked at it; workers watch
-// for the next region for a short while before they sleep, and only as many
-// sleepers are woken as there are tasks.  (Waking and awaiting every worker made
-// the list packing of 7E4 particles slower on 16 threads than on one.)
+// for the next region for some tens of microseconds before they sleep and take
+// their task numbers without a lock, and only as many sleepers are woken as
+// there are tasks.  (Waking and awaiting every worker made the list packing of
+// 7E4 particles slower on 16 threads than on one.)
+//
+// state_ holds the region's generation (16 bits), its task count (24) and the
+// next task (24) in one word: a number taken from it belongs to the region whose
+// count came with it, and fn_ stays valid until that task is counted done.  A
+// late worker sees no number left and touches nothing else.
 class Pool {
-    struct Job {
-        const std::function<void(int64_t)>* fn = nullptr;
-        int64_t n = 0;
-        std::atomic<int64_t> next{0}, done{0};
-        std::mutex m;
-        std::exception_ptr error;            // the first a task threw
-    };
-
 public:
     Pool() {
         int n = (int)std::thread::hardware_concurrency();
@@ -68,8 +65,7 @@ public:
     ~Pool() {
         {
             std::lock_guard<std::mutex> g(m_);
-            stop_ = true;
-            gen_.fetch_add(1);
+            stop_.store(true);
         }
         cv_.notify_all();
         for (auto& t : workers_) t.join();
@@ -82,88 +78,91 @@ public:
             for (int64_t i = 0; i < n; ++i) fn(i);
             return;
         }
-        std::unique_lock<std::mutex> outer(run_m_);   // one parallel region at a time
-        auto job = std::make_shared<Job>();
-        job->fn = &fn;
-        job->n = n;
-        int64_t wake;
-        {
-            std::lock_guard<std::mutex> g(m_);
-            job_ = job;
-            gen_.fetch_add(1);
-            wake = std::min<int64_t>(sleepers_, n - 1);
+        if (n > kMaxTasks) {                          // runs of tasks that fit the count's bits
+            const int64_t per = (n + kMaxTasks - 1) / kMaxTasks;
+            run((n + per - 1) / per, [&](int64_t r) {
+                for (int64_t i = r * per; i < std::min(n, (r + 1) * per); ++i) fn(i);
+            });
+            return;
         }
-        for (int64_t i = 0; i < wake; ++i) cv_.notify_one();
-        work(*job);
-        for (int spin = 0; job->done.load(std::memory_order_acquire) < n; ++spin) {
+        std::unique_lock<std::mutex> outer(run_m_);   // one parallel region at a time
+        fn_ = &fn;
+        done_.store(0, std::memory_order_relaxed);
+        error_ = nullptr;
+        gen_ = (gen_ + 1) & 0xffff;
+        state_.store(gen_ << 48 | (uint64_t)n << 24);
+        int64_t wake = std::min<int64_t>(sleepers_.load(), n - 1);
+        if (wake > 0) {
+            std::lock_guard<std::mutex> g(m_);        // a worker about to sleep has looked, or waits by now
+        }
+        for (; wake > 0; --wake) cv_.notify_one();
+        work();
+        for (int spin = 0; done_.load(std::memory_order_acquire) < n; ++spin) {
             if (spin < kSpins) {
                 pause();
                 continue;
             }
             std::unique_lock<std::mutex> g(m_);
-            waiting_ = true;
-            done_cv_.wait(g, [&] { return job->done.load() >= n; });
-            waiting_ = false;
+            waiting_.store(true);
+            done_cv_.wait(g, [&] { return done_.load() >= n; });
+            waiting_.store(false);
         }
-        {
-            std::lock_guard<std::mutex> g(m_);
-            job_.reset();
-        }
-        if (job->error) std::rethrow_exception(job->error);
+        if (error_) std::rethrow_exception(error_);
     }
 
 private:
-    static constexpr int kSpins = 2000;               // some tens of microseconds
+    static constexpr int kSpins = 2000;
+    static constexpr int64_t kMaxTasks = 1 << 23;
     static void pause() {
 #if defined(__x86_64__)
         __builtin_ia32_pause();
 #endif
     }
-    // A worker may arrive after its job is over: it then finds no index left and
-    // never touches fn, which lives only as long as run().
-    void work(Job& job) {
-        for (;;) {
-            const int64_t i = job.next.fetch_add(1);
-            if (i >= job.n) break;
+    static int64_t tasks(uint64_t s) { return (int64_t)(s >> 24 & 0xffffff); }
+    static int64_t next(uint64_t s) { return (int64_t)(s & 0xffffff); }
+    bool open() const {
+        const uint64_t s = state_.load();
+        return next(s) < tasks(s);
+    }
+    void work() {
+        while (open()) {
+            const uint64_t s = state_.fetch_add(1);
+            if (next(s) >= tasks(s)) break;
             try {
-                (*job.fn)(i);
-            } catch (...) {
-                std::lock_guard<std::mutex> g(job.m);
-                if (!job.error) job.error = std::current_exception();
-            }
-            if (job.done.fetch_add(1) + 1 == job.n) {
+                (*fn_)(next(s));
+            } catch (...) {                           // the region's first is thrown again by run()
                 std::lock_guard<std::mutex> g(m_);
-                if (waiting_) done_cv_.notify_one();
+                if (!error_) error_ = std::current_exception();
+            }
+            if (done_.fetch_add(1) + 1 == tasks(s) && waiting_.load()) {
+                std::lock_guard<std::mutex> g(m_);
+                done_cv_.notify_one();
             }
         }
     }
     void loop() {
-        uint64_t seen = 0;
-        for (;;) {
-            for (int spin = 0; spin < kSpins && gen_.load(std::memory_order_acquire) == seen; ++spin) pause();
-            std::shared_ptr<Job> job;
-            {
+        while (!stop_.load()) {
+            for (int spin = 0; spin < kSpins && !open(); ++spin) pause();
+            if (!open()) {
                 std::unique_lock<std::mutex> g(m_);
-                if (gen_.load() == seen) {
-                    ++sleepers_;
-                    cv_.wait(g, [&] { return gen_.load() != seen; });
-                    --sleepers_;
-                }
-                seen = gen_.load();
-                if (stop_) return;
-                job = job_;
+                sleepers_.fetch_add(1);
+                cv_.wait(g, [&] { return stop_.load() || open(); });
+                sleepers_.fetch_sub(1);
+                if (stop_.load()) return;
             }
-            if (job) work(*job);
+            work();
         }
     }
     int nthreads_ = 1;
     std::vector<std::thread> workers_;
     std::mutex m_, run_m_;
     std::condition_variable cv_, done_cv_;
-    std::shared_ptr<Job> job_;
-    std::atomic<uint64_t> gen_{0};
-    int64_t sleepers_ = 0;
-    bool waiting_ = false, stop_ = false;
+    const std::function<void(int64_t)>* fn_ = nullptr;
+    std::atomic<uint64_t> state_{0};
+    std::atomic<int64_t> done_{0}, sleepers_{0};
+    std::atomic<bool> waiting_{false}, stop_{false};
+    uint64_t gen_ = 0;
+    std::exception_ptr error_;
 };
 
 Pool& pool() {
