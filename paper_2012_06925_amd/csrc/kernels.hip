@@ -73,10 +73,15 @@ __global__ __launch_bounds__(kBlock) void k_up_leaf(const int32_t* __restrict__ 
 }
 
 template <int M, bool MF>
-__global__ __launch_bounds__(kBlock) void k_up_transfer(const int32_t* __restrict__ parents, DevTree S,
-                                                        const double* __restrict__ tab,
-                                                        double* __restrict__ qhat) {
-    __shared__ double lds[up_transfer_lds_bytes<M>() / sizeof(double)];
+constexpr int up_transfer_threads() { return MF ? 64 * up_transfer_waves<M>() : kBlock; }
+
+template <int M, bool MF>
+__global__ __launch_bounds__((up_transfer_threads<M, MF>())) void k_up_transfer(const int32_t* __restrict__ parents,
+                                                                              DevTree S,
+                                                                              const double* __restrict__ tab,
+                                                                              double* __restrict__ qhat) {
+    constexpr int B = MF ? up_transfer_mfma_lds_bytes<M>() : up_transfer_lds_bytes<M>();
+    __shared__ double lds[B / sizeof(double)];
     if constexpr (MF) up_transfer_mfma_body<M>(parents[blockIdx.x], S, tab, qhat, lds);
     else up_transfer_body<M>(parents[blockIdx.x], S, tab, qhat, lds);
 }
@@ -965,7 +970,9 @@ template <int M>
 struct UpTransfer {
     static void run(bool mf, const int32_t* parents, int n, DevTree S, const double* tab, double* qhat,
                     hipStream_t st) {
-        if (mf) hipLaunchKernelGGL((k_up_transfer<M, true>), dim3(n), dim3(kBlock), 0, st, parents, S, tab, qhat);
+        if (mf)
+            hipLaunchKernelGGL((k_up_transfer<M, true>), dim3(n), dim3(up_transfer_threads<M, true>()), 0, st, parents,
+                               S, tab, qhat);
         else hipLaunchKernelGGL((k_up_transfer<M, false>), dim3(n), dim3(kBlock), 0, st, parents, S, tab, qhat);
     }
 };
