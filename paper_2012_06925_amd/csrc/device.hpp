@@ -447,24 +447,26 @@ __device__ __forceinline__ void interact_body(const DevItem& it, const int2* __r
 // ---------------------------------------------------------------------------
 // Upward pass, leaves: qhat_k = sum_j q_j Lx_k1(x_j) Ly_k2(y_j) Lz_k3(z_j).
 // Thread (k2, k3) of group g accumulates the M values k1 for the particles
-// j = g (mod groups); the groups are summed at the end.
+// j = g (mod groups); the groups are summed at the end (in the LDS of the bases).
+// NT threads: 256, or 1024 where few leaves leave the GPU to latency (a chunk of
+// NT / 4 particles per round).
 // ---------------------------------------------------------------------------
-constexpr int kUpChunk = 64;
+constexpr int kUpChunk = 64;                 // particles per round of the 256-thread forms
 
-template <int M>
+template <int M, int NT = kBlock>
 constexpr int up_leaf_lds_bytes() {
-    constexpr int P = M * M * M, G = kBlock / (M * M);
-    return (int)sizeof(double) * (3 * kUpChunk * M + (G > 1 ? G * P : 1));
+    constexpr int P = M * M * M, G = NT / (M * M), w = 3 * (NT / 4) * M, red = G > 1 ? G * P : 1;
+    return (int)sizeof(double) * (w > red ? w : red);
 }
 
-template <int M>
+template <int M, int NT = kBlock>
 __device__ __forceinline__ void up_leaf_body(int c, DevTree S, DevParticles src, const double* __restrict__ tab,
                                              double* __restrict__ qhat, double* lds) {
     constexpr int P2 = M * M, P = M * M * M;
-    constexpr int G = kBlock / P2;
-    constexpr int CH = kUpChunk;
+    constexpr int G = NT / P2;
+    constexpr int CH = NT / 4;
     double (*w)[CH][M] = reinterpret_cast<double (*)[CH][M]>(lds);
-    double* red = lds + 3 * CH * M;
+    double* red = lds;
     const double* box = S.box + 6 * c;
     const int b = S.begin[c], n = S.count[c];
     const int tid = threadIdx.x, g = tid / P2, r = tid % P2, k2 = r % M, k3 = r / M;
@@ -516,7 +518,7 @@ __device__ __forceinline__ void up_leaf_body(int c, DevTree S, DevParticles src,
         for (int k = 0; k < M; ++k) red[g * P + k + M * r] = acc[k];
     }
     __syncthreads();
-    for (int k = tid; k < P; k += kBlock) {
+    for (int k = tid; k < P; k += NT) {
         double s = 0.0;
         for (int gg = 0; gg < G; ++gg) s += red[gg * P + k];
         out[k] = s;
