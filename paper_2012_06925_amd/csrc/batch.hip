@@ -21,6 +21,10 @@
 //              same points as target and as source); A's sums go to the
 //              particle fold, B's to the proxy fold; each item counts for its
 //              problem (like an s item) and for every partner B
+//   [r item]   the same pairs where A has few particles, the other way round: tiles
+//              of B's proxies against the particles of such partners A; each item
+//              counts for its problem and for B (40 problems of 1E4..1E5 particles,
+//              degree 7, as tiles of A's few particles 7.6 ms, so 7.2)
 //   [p item]   PP + PC sums into target particles (PC needs the upward pass)
 //   [dn_xfer]  a cluster's symmetric CC and CP slots folded into its proxy
 //              potentials in their stored order, then parent-to-child proxy
@@ -102,6 +106,14 @@ __device__ __forceinline__ void signal_partners(int32_t* first, int32_t* dn, con
         __hip_atomic_fetch_add(dn + entries[e].x, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Same, counted in *p0 and in *p1.
+__device__ __forceinline__ void signal_partners(int32_t* p0, int32_t* p1) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    __syncthreads();
+    if (threadIdx.x < 2)
+        __hip_atomic_fetch_add(threadIdx.x == 0 ? p0 : p1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Same, counted in dn[first] and in dn[entries[e].x] for e in [eb, ee).
 __device__ __forceinline__ void signal_clusters(int32_t* dn, int first, const int2* entries, int eb, int ee) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
@@ -131,8 +143,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 
     // the symmetric PP items right after the upward pass: they need nothing
     // before them, and keep the SIMDs busy while the upward pass completes
-    const int e0 = a.n_leaves, e1 = e0 + a.n_parents, ev = e1 + a.n_s, eq = ev + a.n_q, e2 = eq + a.n_c,
-              em = e2 + a.n_m, e3 = em + a.n_p, e4 = e3 + a.n_kids;
+    constexpr bool SYM = !F32 && KIND == K_COULOMB;      // (other kinds keep no registers for those ranges)
+    const int n_s = SYM ? a.n_s : 0, n_c = SYM ? a.n_c : 0, n_m = SYM ? a.n_m : 0, n_r = SYM ? a.n_r : 0;
+    const int e0 = a.n_leaves, e1 = e0 + a.n_parents, ev = e1 + n_s, eq = ev + a.n_q, e2 = eq + n_c,
+              er = e2 + n_m, em = er + n_r, e3 = em + a.n_p, e4 = e3 + a.n_kids;
     const int n_up = e1;
     bool up_seen = false;                     // this group has already acquired the finished upward pass
     for (;;) {
@@ -159,7 +173,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             if (par >= 0 && threadIdx.x == 0)
                 __hip_atomic_fetch_add(a.ctr + C_UP_DONE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else if (t < ev) {
-            if constexpr (!F32 && KIND == K_COULOMB) {
+            if constexpr (SYM) {
                 const DevItem it = a.sitems[t - e1];
                 const int64_t base = a.sbase[t - e1];
                 // four targets per lane, and fewer for the tails of leaves: one
@@ -189,7 +203,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                                               nullptr, a.po, vl, OUT_WRITE);
             signal(a.dn + it.cluster);
         } else if (t < e2) {
-            if constexpr (!F32 && KIND == K_COULOMB) {
+            if constexpr (SYM) {
                 const DevItem it = a.citems[t - eq];
                 if (!up_seen) {
                     wait2(a, a.ctr + C_UP_DONE, n_up, nullptr, 0);
@@ -200,21 +214,43 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                                       a.cslots, base + it.tn);
                 signal_clusters(a.dn, it.cluster, a.centries, it.eb, it.ee);
             }
-        } else if (t < em) {
-            if constexpr (!F32 && KIND == K_COULOMB) {
+        } else if (t < er) {
+            if constexpr (SYM) {
                 const int i = t - e2;
                 const DevItem it = a.mitems[i];
                 if (!up_seen) {
                     wait2(a, a.ctr + C_UP_DONE, n_up, nullptr, 0);
                     up_seen = true;
                 }
-                if (it.tn <= 64)
+                if (it.tn > 128)
+                    sym_body<false, false, 4, true>(it, a.mentries, a.src, a.S, a.tab_all, a.qp, pool, nullptr,
+                                                    a.sslots, a.mtbase[i], a.cslots, a.msbase[i]);
+                else if (it.tn <= 64)
                     sym_body<false, false, 1, true>(it, a.mentries, a.src, a.S, a.tab_all, a.qp, pool, nullptr,
                                                     a.sslots, a.mtbase[i], a.cslots, a.msbase[i]);
                 else
                     sym_body<false, false, 2, true>(it, a.mentries, a.src, a.S, a.tab_all, a.qp, pool, nullptr,
                                                     a.sslots, a.mtbase[i], a.cslots, a.msbase[i]);
                 signal_partners(a.sdone + a.prob[it.cluster], a.dn, a.mentries, it.eb, it.ee);
+            }
+        } else if (t < em) {
+            if constexpr (SYM) {
+                const int i = t - er;
+                const DevItem it = a.ritems[i];
+                if (!up_seen) {
+                    wait2(a, a.ctr + C_UP_DONE, n_up, nullptr, 0);
+                    up_seen = true;
+                }
+                if (it.tn > 128)
+                    sym_body<false, true, 4, false>(it, a.rentries, a.src, a.S, a.tab_all, a.qp, pool, nullptr,
+                                                    a.cslots, a.rtbase[i], a.sslots, a.rsbase[i]);
+                else if (it.tn > 64)
+                    sym_body<false, true, 2, false>(it, a.rentries, a.src, a.S, a.tab_all, a.qp, pool, nullptr,
+                                                    a.cslots, a.rtbase[i], a.sslots, a.rsbase[i]);
+                else
+                    sym_body<false, true, 1, false>(it, a.rentries, a.src, a.S, a.tab_all, a.qp, pool, nullptr,
+                                                    a.cslots, a.rtbase[i], a.sslots, a.rsbase[i]);
+                signal_partners(a.sdone + a.prob[it.cluster], a.dn + it.cluster);
             }
         } else if (t < e3) {
             const int i = t - em;
@@ -235,7 +271,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             // potentials (the same thread later adds the transfer to each
             // output it folded)
             down_transfer_stage<M>(c, a.T, a.tab, a.phihat, dl);
-            if (a.cslots && a.cseg[c] >= 0) {
+            if (SYM && a.cslots && a.cseg[c] >= 0) {
                 const FoldSeg sg = a.csegs[a.cseg[c]];
                 fold_body(sg, a.cparts, a.cslots, a.phihat + sg.off, 0, sg.n,
                           reinterpret_cast<FoldPart*>(reinterpret_cast<char*>(pool) + kXferFold));
@@ -248,9 +284,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             const DevItem it = a.pitems[i];
             const int c = it.cluster;
             const int prob = a.prob[c];
-            if (a.n_s + a.n_m > 0) wait2(a, a.sdone + prob, a.s_need[prob], nullptr, 0);
+            if (n_s + n_m + n_r > 0) wait2(a, a.sdone + prob, a.s_need[prob], nullptr, 0);
             wait2(a, a.pdone + i, 1, a.dn + c, a.nq[c] + (a.T.parent[c] >= 0 ? 1 : 0));
-            if (a.sslots && a.pseg[i] >= 0) {
+            if (SYM && a.sslots && a.pseg[i] >= 0) {
                 const FoldSeg sg = a.psegs[a.pseg[i]];
                 const int k0 = it.t0 - (int)sg.off;
                 fold_body(sg, a.pparts, a.sslots, a.phi_tree + sg.off, k0, k0 + it.tn,

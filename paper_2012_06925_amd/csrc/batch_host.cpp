@@ -52,10 +52,11 @@ struct bldtt_batch {
     DevTreeBufs dS, dTt;
     const DevTreeBufs& dT() const { return aliased ? dS : dTt; }
     DevBuf leaves, parents, kids, qitems, qentries, qneeds, pitems, pentries, pneeds, has_far, nq, prob, caller0_d,
-        outs, counters, sitems, sentries, s_need, citems, centries, mitems, mentries;
+        outs, counters, sitems, sentries, s_need, citems, centries, mitems, mentries,
+        ritems, rentries;
     // folds of the symmetric items: slots, slot bases, segments, parts, and the
     // segment of each particle item (PP) and of each target cluster (CC)
-    DevBuf sslots, sbase, mtbase, psegs, pparts, pseg, cslots, cbase, msbase, csegs, cparts, cseg;
+    DevBuf sslots, sbase, mtbase, rsbase, rtbase, psegs, pparts, pseg, cslots, cbase, msbase, csegs, cparts, cseg;
     int n_leaves = 0, n_parents = 0, n_kids = 0;
     int64_t n_counters = 0;
     PinnedBuf outs_host;
@@ -251,9 +252,11 @@ void upload_folds(bldtt_batch* b) {
     SymFold& pf = sw.pp_fold;
     SymFold& cf = sw.cc_fold;
     const std::vector<FoldGroup> pg = {{&sw.pp_items, &sw.pp_entries, FoldGroup::kParticleBoth},
-                                       {&sw.pc_items, &sw.pc_entries, FoldGroup::kParticleTargets}};
+                                       {&sw.pc_items, &sw.pc_entries, FoldGroup::kParticleTargets},
+                                       {&sw.cp_items, &sw.cp_entries, FoldGroup::kParticleSources}};
     const std::vector<FoldGroup> cg = {{&sw.cc_items, &sw.cc_entries, FoldGroup::kProxyBoth},
-                                       {&sw.pc_items, &sw.pc_entries, FoldGroup::kProxySources}};
+                                       {&sw.pc_items, &sw.pc_entries, FoldGroup::kProxySources},
+                                       {&sw.cp_items, &sw.cp_entries, FoldGroup::kProxyTargets}};
     std::vector<std::vector<int64_t>> pb, cb;
     pf.clear();
     cf.clear();
@@ -288,12 +291,14 @@ void upload_folds(bldtt_batch* b) {
     b->sslots.alloc(sizeof(double) * std::max<int64_t>(1, pf.nslots));
     upload(b->sbase, pb[0]);
     upload(b->mtbase, pb[1]);
+    upload(b->rsbase, pb[2]);
     upload(b->psegs, pf.segs);
     upload(b->pparts, pf.parts);
     upload(b->pseg, pseg);
     b->cslots.alloc(sizeof(double) * std::max<int64_t>(1, cf.nslots));
     upload(b->cbase, cb[0]);
     upload(b->msbase, cb[1]);
+    upload(b->rtbase, cb[2]);
     upload(b->csegs, cf.segs);
     upload(b->cparts, cf.parts);
     upload(b->cseg, cseg);
@@ -309,7 +314,7 @@ void pack(bldtt_batch* b, int tpt) {
         // counters, so not as finely as the single plans: 40 problems of up to 1E5
         // particles 8.25 ms uncut, 7.97 with 2048, 8.41 with 8192; 20 of up to 2E4
         // 0.97 / 0.83 / 1.05 ms)
-        split_symmetric(b->T(), b->lists, b->degree, true, true, b->rest, b->sym, {}, false, true, 256, ItemCut{2048, 256});
+        split_symmetric(b->T(), b->lists, b->degree, true, true, b->rest, b->sym, {}, false, true, 256, ItemCut{2048, 256, true});
         const std::vector<uint32_t> extra = sym_cc_degrees(b->T(), b->sym);
         pack_work(b->T(), b->S, b->rest, b->degree, kThreads * tpt, kThreads * tpt, w, &extra);
     } else {
@@ -325,7 +330,7 @@ void pack(bldtt_batch* b, int tpt) {
     b->packed_tpt_valid = true;
     b->stats.n_tasks = (int64_t)b->n_leaves + b->n_parents + (int64_t)w.qitems.size() + 2 * (int64_t)w.pitems.size() +
                        (int64_t)b->sym.pp_items.size() + (int64_t)b->sym.cc_items.size() +
-                       (int64_t)b->sym.pc_items.size() + b->n_kids;
+                       (int64_t)b->sym.pc_items.size() + (int64_t)b->sym.cp_items.size() + b->n_kids;
     if (b->host_only) return;
     auto needs = [](const std::vector<Item>& items, const std::vector<Entry>& entries) {
         std::vector<uint8_t> f(items.size(), 0);
@@ -348,6 +353,7 @@ void pack(bldtt_batch* b, int tpt) {
     }
     for (const Item& it : b->sym.pc_items)
         for (int e = it.eb; e < it.ee; ++e) nq[b->sym.pc_entries[e].a] += 1;
+    for (const Item& it : b->sym.cp_items) nq[it.cluster] += 1;
     upload(b->qitems, w.qitems);
     upload(b->qentries, w.qentries);
     upload(b->qneeds, needs(w.qitems, w.qentries));
@@ -362,10 +368,13 @@ void pack(bldtt_batch* b, int tpt) {
     upload(b->centries, b->sym.cc_entries);
     upload(b->mitems, b->sym.pc_items);
     upload(b->mentries, b->sym.pc_entries);
+    upload(b->ritems, b->sym.cp_items);
+    upload(b->rentries, b->sym.cp_entries);
     // symmetric items each problem's final interpolations wait for (PP and PC/CP)
     std::vector<int32_t> s_need(b->count, 0);
     for (const Item& it : b->sym.pp_items) s_need[b->prob_of_cluster[it.cluster]] += 1;
     for (const Item& it : b->sym.pc_items) s_need[b->prob_of_cluster[it.cluster]] += 1;
+    for (const Item& it : b->sym.cp_items) s_need[b->prob_of_cluster[it.cluster]] += 1;
     upload(b->s_need, s_need);
     if (b->symmetric()) upload_folds(b);
     b->n_counters = kGlobalCounters + b->S.size() + b->T().size() + (int64_t)w.pitems.size() + b->count;
@@ -421,11 +430,16 @@ BatchDev device_args(const bldtt_batch* b) {
     a.mitems = b->mitems.as<DevItem>();
     a.mentries = b->mentries.as<int2>();
     a.n_m = (int)b->sym.pc_items.size();
+    a.ritems = b->ritems.as<DevItem>();
+    a.rentries = b->rentries.as<int2>();
+    a.n_r = (int)b->sym.cp_items.size();
     if (b->symmetric()) {
         a.sslots = b->sslots.as<double>();
         a.sbase = b->sbase.as<int64_t>();
         a.mtbase = b->mtbase.as<int64_t>();
         a.msbase = b->msbase.as<int64_t>();
+        a.rsbase = b->rsbase.as<int64_t>();
+        a.rtbase = b->rtbase.as<int64_t>();
         a.psegs = b->psegs.as<FoldSeg>();
         a.pparts = b->pparts.as<FoldPart>();
         a.pseg = b->pseg.as<int32_t>();
@@ -436,7 +450,7 @@ BatchDev device_args(const bldtt_batch* b) {
         a.cseg = b->cseg.as<int32_t>();
     }
     a.n_kids = b->n_kids;
-    a.n_tasks = a.n_leaves + a.n_parents + a.n_q + a.n_c + a.n_m + 2 * a.n_p + a.n_s + a.n_kids;
+    a.n_tasks = a.n_leaves + a.n_parents + a.n_q + a.n_c + a.n_m + a.n_r + 2 * a.n_p + a.n_s + a.n_kids;
     a.spin_limit = b->spin_limit;
     a.param = b->param;
     return a;

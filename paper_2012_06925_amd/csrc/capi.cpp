@@ -381,7 +381,7 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
     // tiles and many partners, and one item per tile left the GPU idle: the pass of
     // 1E4 particles (leaf 500) 345 us with 62 items, 37 us with 1023; 1E5 Gaussian
     // particles 2.85 -> 1.7 ms; at 1E6 and more one item per tile is as good.
-    const ItemCut sym_cut{16 * (int64_t)std::max(1, pl->cus), 256};
+    const ItemCut sym_cut{16 * (int64_t)std::max(1, pl->cus), 256, true};
     // PC pairs listed with their mirror CP pair are evaluated once for both as
     // well (FP64), while their source slots, a proxy grid per pair and tile, stay
     // below 4 GiB; beyond that (or where there are none) they stay one-way.  1E5
@@ -645,6 +645,8 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
     }
     if (sym_pc) {
         up.add(pl->sym_pc_items, scc.pc_items).add(pl->sym_pc_entries, scc.pc_entries).add(pl->sym_pc_sbase, scc.pc_sbase);
+        up.add(pl->sym_cp_items, scc.cp_items).add(pl->sym_cp_entries, scc.cp_entries)
+            .add(pl->sym_cp_tbase, scc.cp_tbase).add(pl->sym_cp_sbase, scc.cp_sbase);
         add_bases(up, pl->fold_pc, scc.pc_fold);
         add_parts(up, pl->fold_pc, scc.pc_fold);
     }
@@ -683,9 +685,15 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
                        pl->sym_cc_entries.as<int2>(), pl->dsrc(), dS, tab, deg_ptrs(pl->qhat_deg), nullptr, f.out(),
                        st);
             if (sym_pc)         // their particle sums are folded with the particle passes below
-                launch_sym_pc(ks, pl->sym_pc_items.as<DevItem>(), (int)scc.pc_items.size(),
-                              pl->sym_pc_entries.as<int2>(), pl->dsrc(), dS, tab, deg_ptrs(pl->qhat_deg),
-                              pl->fold_pc.out(), SymSlots{f.slots.as<double>(), pl->sym_pc_sbase.as<int64_t>()}, st);
+                launch_sym_pc(ks,
+                              SymPcPart{pl->sym_pc_items.as<DevItem>(), pl->sym_pc_entries.as<int2>(),
+                                        (int)scc.pc_items.size(), pl->fold_pc.ibase.as<int64_t>(),
+                                        pl->sym_pc_sbase.as<int64_t>()},
+                              SymPcPart{pl->sym_cp_items.as<DevItem>(), pl->sym_cp_entries.as<int2>(),
+                                        (int)scc.cp_items.size(), pl->sym_cp_sbase.as<int64_t>(),
+                                        pl->sym_cp_tbase.as<int64_t>()},
+                              pl->dsrc(), dS, tab, deg_ptrs(pl->qhat_deg), pl->fold_pc.slots.as<double>(),
+                              f.slots.as<double>(), st);
             launch_sym_fold(f.segs.as<FoldSeg>(), f.n_segs, f.max_n, f.parts.as<FoldPart>(), f.slots.as<double>(), nullptr,
                             deg_out(pl->phihat_deg), st);
         }

@@ -180,8 +180,10 @@ void pack_work(const Tree& T, const Tree& S, const Lists& L, int degree, int til
 // (targets x sources), each with at least min_src sources (an item's loads,
 // barriers and last reduction are worth some hundred sources).  want 0: one
 // item per tile of targets, however many sources it has.
+// proxy_tiles: PC/CP pairs may be tiled over the proxies (see SymWork::cp_items).
 struct ItemCut {
     int64_t want = 0, min_src = 1;
+    bool proxy_tiles = false;
 };
 
 // Symmetric pairs of a targets = sources plan (one tree): with `pp`, leaf
@@ -232,10 +234,11 @@ void fold_parts(const Tree& T, const std::vector<Item>& items, const std::vector
 // ranges, particle segments), symmetric CC items (target tile and source
 // proxies, proxy segments), and the two sides of the symmetric PC/CP items:
 // their target particles (particle segments, split at leaf boundaries) and
-// their source proxies (proxy segments).  fold_group_bases gives each item its
+// their source proxies (proxy segments), or, for cp_items, their target proxies
+// and their source particles.  fold_group_bases gives each item its
 // slot base (all groups' slots one after another) and returns the slot count.
 struct FoldGroup {
-    enum Kind { kParticleBoth, kProxyBoth, kParticleTargets, kProxySources };
+    enum Kind { kParticleBoth, kProxyBoth, kParticleTargets, kProxySources, kProxyTargets, kParticleSources };
     const std::vector<Item>* items;
     const std::vector<Entry>* entries;
     Kind kind;
@@ -261,11 +264,17 @@ void cut_items(const std::vector<Item>& items, std::vector<Entry>& entries, bool
                CutItems& out);
 
 struct SymWork {
-    std::vector<Entry> pp_entries, cc_entries, pc_entries;
+    std::vector<Entry> pp_entries, cc_entries, pc_entries, cp_entries;
     std::vector<Item> pp_items, cc_items, pc_items;
+    // With ItemCut::proxy_tiles, the PC/CP pairs whose particles fill their lanes
+    // worse than the proxy grid does (clusters of few particles; wave tiles of
+    // 64 lanes): items over tiles of B's proxies with the merged particle ranges
+    // of such partners A as sources, the same values the other way round.
+    std::vector<Item> cp_items;
     SymFold pp_fold, cc_fold;
     SymFold pc_fold;                            // build_pc_folds: the particle side of the PC/CP items
-    std::vector<int64_t> pc_sbase;              // and the slot base of each one's sources in cc_fold
+    std::vector<int64_t> pc_sbase;              // and the slot base of each one's sources in cc_fold;
+    std::vector<int64_t> cp_tbase, cp_sbase;    // of each cp item's targets in cc_fold, sources in pc_fold
     int64_t pp_plain = 0;
     double pp_evaluations = 0.0, cc_evaluations = 0.0, pc_evaluations = 0.0;
     bool guard_near = false;                    // setting, as Work::guard_near
@@ -273,19 +282,23 @@ struct SymWork {
         pp_entries.clear();
         cc_entries.clear();
         pc_entries.clear();
+        cp_entries.clear();
         pp_items.clear();
         cc_items.clear();
         pc_items.clear();
+        cp_items.clear();
         pp_plain = 0;
         pp_evaluations = cc_evaluations = pc_evaluations = 0.0;
         pp_fold.clear();
         cc_fold.clear();
         pc_fold.clear();
         pc_sbase.clear();
+        cp_tbase.clear();
+        cp_sbase.clear();
     }
 };
 // The folds of a SymWork with PC/CP items: cc_fold holds the CC items, then the
-// sources of the PC/CP items; pc_fold the targets of the PC/CP items.
+// proxy side of the PC/CP items; pc_fold their particle side.
 void build_pc_folds(const Tree& T, SymWork& sw);
 // At most how many slots the sources of the PC/CP items of L's pairs take.
 double pc_source_slots(const Tree& T, const Lists& L, int degree, int tile);

@@ -144,23 +144,40 @@ __global__ __launch_bounds__(kBlock) void k_sym(const DevItem* __restrict__ item
     }
 }
 
-// PC pairs with their mirror CP pairs (FP64): particle tiles against the
-// partners' proxy grids, once for both; the tile's sums and the proxies' partials
-// go to slots of two folds.
+// PC pairs with their mirror CP pairs (FP64), once for both: particle tiles
+// against the partners' proxy grids (the first n_pc blocks), then tiles of a grid
+// against the particles of small partners; the sums of the two sides go to slots
+// of two folds.  A cluster of a few particles as the tile leaves most lanes idle,
+// and at one target per lane each pair reads its source from LDS (the limit), so
+// the grid is the tile there: 1E5 Gaussian particles (leaf 300, n 8; PC clusters
+// of 40..300) 2.73 -> 2.29 ms, 3E5 Yukawa 9.84 -> 9.58.  One launch, because
+// either part may be a few blocks (1E4 particles, leaf 500: 4 and 18).
 template <int KIND>
-__global__ __launch_bounds__(kBlock) void k_sym_pc(const DevItem* __restrict__ items, const int2* __restrict__ entries,
-                                                   DevParticles p, DevTree T, const double* __restrict__ tab,
-                                                   DegPtrs qhat, double param, SymSlots tgt, SymSlots src) {
+__global__ __launch_bounds__(kBlock) void k_sym_pc(SymPcPart pc, SymPcPart cp, DevParticles p, DevTree T,
+                                                   const double* __restrict__ tab, DegPtrs qhat, double param,
+                                                   double* __restrict__ pslots, double* __restrict__ cslots) {
     __shared__ double4 pool[(sym_lds_bytes<false>() + 31) / 32];
-    const DevItem it = items[blockIdx.x];
-    const int64_t tb = tgt.ibase[blockIdx.x], sb = src.ibase[blockIdx.x];
-    auto body = [&](auto h) {
-        sym_body<false, false, decltype(h)::value, true, KIND>(it, entries, p, T, tab, qhat, pool, nullptr, tgt.slots, tb,
-                                                               src.slots, sb, param);
-    };
-    if (KIND == K_COULOMB && it.tn > 128) body(std::integral_constant<int, 4>{});
-    else if (it.tn > 64) body(std::integral_constant<int, 2>{});
-    else body(std::integral_constant<int, 1>{});
+    if ((int)blockIdx.x < pc.n) {
+        const int i = blockIdx.x;
+        const DevItem it = pc.items[i];
+        auto body = [&](auto h) {
+            sym_body<false, false, decltype(h)::value, true, KIND>(it, pc.entries, p, T, tab, qhat, pool, nullptr, pslots,
+                                                                   pc.pbase[i], cslots, pc.cbase[i], param);
+        };
+        if (KIND == K_COULOMB && it.tn > 128) body(std::integral_constant<int, 4>{});
+        else if (it.tn > 64) body(std::integral_constant<int, 2>{});
+        else body(std::integral_constant<int, 1>{});
+    } else {
+        const int i = blockIdx.x - pc.n;
+        const DevItem it = cp.items[i];
+        auto body = [&](auto h) {
+            sym_body<false, true, decltype(h)::value, false, KIND>(it, cp.entries, p, T, tab, qhat, pool, nullptr, cslots,
+                                                                   cp.cbase[i], pslots, cp.pbase[i], param);
+        };
+        if (KIND == K_COULOMB && it.tn > 128) body(std::integral_constant<int, 4>{});
+        else if (it.tn > 64) body(std::integral_constant<int, 2>{});
+        else body(std::integral_constant<int, 1>{});
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1146,12 +1163,13 @@ void launch_sym(KernelSpec k, bool fp32, bool mfma, bool proxies, bool guarded, 
     CHECK_LAUNCH();
 }
 
-void launch_sym_pc(KernelSpec k, const DevItem* items, int n_items, const int2* entries, DevParticles p, DevTree T,
-                   const double* tab, DegPtrs qhat, SymSlots tgt, SymSlots src, hipStream_t st) {
-    if (n_items <= 0) return;
-    if (!tgt.slots || !tgt.ibase || !src.slots || !src.ibase) throw Error(-1, "symmetric pass without slots");
-#define LAUNCH_PC(KK) hipLaunchKernelGGL((k_sym_pc<KK>), dim3(n_items), dim3(kBlock), 0, st, items, entries, p, T, tab, \
-                                         qhat, k.param, tgt, src)
+void launch_sym_pc(KernelSpec k, SymPcPart pc, SymPcPart cp, DevParticles p, DevTree T, const double* tab,
+                   DegPtrs qhat, double* pslots, double* cslots, hipStream_t st) {
+    if (pc.n + cp.n <= 0) return;
+    for (const SymPcPart& w : {pc, cp})
+        if (w.n > 0 && (!pslots || !cslots || !w.pbase || !w.cbase)) throw Error(-1, "symmetric pass without slots");
+#define LAUNCH_PC(KK) hipLaunchKernelGGL((k_sym_pc<KK>), dim3(pc.n + cp.n), dim3(kBlock), 0, st, pc, cp, p, T, tab, qhat, \
+                                         k.param, pslots, cslots)
     switch (k.kind) {
     case K_COULOMB: LAUNCH_PC(K_COULOMB); break;
     case K_YUKAWA: LAUNCH_PC(K_YUKAWA); break;

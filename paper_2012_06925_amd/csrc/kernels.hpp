@@ -99,11 +99,18 @@ void launch_sym(KernelSpec k, bool fp32, bool mfma, bool proxies, bool guarded, 
                 const int2* entries, DevParticles p, DevTree T, const double* tab, DegPtrs qhat, double* nfp64,
                 SymSlots out, hipStream_t st);
 
-// PC pairs with their mirror CP pairs, each kernel value once for both (FP64):
-// items are particle tiles of a cluster with proxy entries of degree
-// item.degree; item i's target sums go to tgt, its source partials to src.
-void launch_sym_pc(KernelSpec k, const DevItem* items, int n_items, const int2* entries, DevParticles p, DevTree T,
-                   const double* tab, DegPtrs qhat, SymSlots tgt, SymSlots src, hipStream_t st);
+// PC pairs with their mirror CP pairs, each kernel value once for both (FP64).
+// pc: particle tiles of a cluster with proxy entries of degree item.degree; cp:
+// tiles of a cluster's proxies with particle ranges.  The particle sums go to
+// pslots at each item's pbase, the proxy sums to cslots at its cbase.
+struct SymPcPart {
+    const DevItem* items;
+    const int2* entries;
+    int n;
+    const int64_t *pbase, *cbase;
+};
+void launch_sym_pc(KernelSpec k, SymPcPart pc, SymPcPart cp, DevParticles p, DevTree T, const double* tab,
+                   DegPtrs qhat, double* pslots, double* cslots, hipStream_t st);
 
 // out[k] += the parts of every segment (fold.hpp; max_n: the outputs of the largest):
 // phi (tree order) for particle segments, phihat.p[degree] for proxy ones,
@@ -183,17 +190,22 @@ struct BatchDev {
     const DevItem* mitems;      // symmetric PC/CP items (same batches): particle tiles, proxy entries
     const int2* mentries;
     int n_m;
+    const DevItem* ritems;      // symmetric PC/CP items the other way round: proxy tiles, particle ranges
+    const int2* rentries;
+    int n_r;
     // folds of the symmetric items (fold.hpp; set for batches of targets =
     // sources Coulomb problems in FP64, else null)
-    double* sslots;             // particle fold: the s items' slots, then the m items' target slots;
+    double* sslots;             // particle fold: the s items' slots, then the particle side of the m and r items;
     const int64_t* sbase;       // slot base per s item, segments per leaf
     const int64_t* mtbase;      // per m item: the base of its target slots here
+    const int64_t* rsbase;      // per r item: the base of its source slots here
     const FoldSeg* psegs;
     const FoldPart* pparts;
     const int32_t* pseg;        // per particle item: the segment of its leaf
-    double* cslots;             // proxy fold: the c items' slots, then the m items' source slots;
+    double* cslots;             // proxy fold: the c items' slots, then the proxy side of the m and r items;
     const int64_t* cbase;       // slot base per c item, segments per cluster
     const int64_t* msbase;      // per m item: the base of its source slots here
+    const int64_t* rtbase;      // per r item: the base of its target slots here
     const FoldSeg* csegs;
     const FoldPart* cparts;
     const int32_t* cseg;        // per target cluster: its segment, or -1

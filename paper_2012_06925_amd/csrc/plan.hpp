@@ -301,7 +301,8 @@ struct bldtt_plan {
     int n_self_items = 0, n_self_sym_items = 0;
     bool self_ready = false;
     double self_evaluations = 0.0;
-    DevBuf sym_items, sym_entries, sym_cc_items, sym_cc_entries, sym_pc_items, sym_pc_entries, sym_pc_sbase;
+    DevBuf sym_items, sym_entries, sym_cc_items, sym_cc_entries, sym_pc_items, sym_pc_entries, sym_pc_sbase,
+        sym_cp_items, sym_cp_entries, sym_cp_tbase, sym_cp_sbase;
     // folds of the symmetric passes: the main PP pass, the CC pass (and the proxy
     // side of the PC/CP pass), the leaves' self pairs, the particle side of the PC/CP pass
     DevFold fold_pp, fold_cc, fold_self, fold_pc;

@@ -776,6 +776,7 @@ std::vector<uint32_t> sym_cc_degrees(const Tree& T, const SymWork& sw) {
     for (const Item& it : sw.cc_items) m[it.cluster] |= 1u << it.degree;
     for (const Entry& e : sw.cc_entries) m[e.a] |= 1u << (e.b & kCountMask);
     for (const Entry& e : sw.pc_entries) m[e.a] |= 1u << (e.b & kCountMask);
+    for (const Item& it : sw.cp_items) m[it.cluster] |= 1u << it.degree;
     return m;
 }
 
@@ -805,13 +806,14 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
     }
     // the indexes of CC, PC and CP pairs are formed after pp_ready, below
     // the blocks of one list type at a time, kept like the indexes
-    static thread_local std::vector<SymBlock> tl_blks;
-    std::vector<SymBlock>& all_blks = tl_blks;
-    auto blocks = [&]() -> std::vector<SymBlock>& {
-        if ((int64_t)all_blks.size() > 4 * nblk + 1024) all_blks.clear();      // a much larger problem's
-        all_blks.resize(nblk);
-        for (SymBlock& b : all_blks) b.clear();
-        return all_blks;
+    static thread_local std::vector<SymBlock> tl_blks[2];
+    std::vector<SymBlock>* all_blks = tl_blks;
+    auto blocks = [&](int which = 0) -> std::vector<SymBlock>& {
+        std::vector<SymBlock>& v = all_blks[which];
+        if ((int64_t)v.size() > 4 * nblk + 1024) v.clear();      // a much larger problem's
+        v.resize(nblk);
+        for (SymBlock& b : v) b.clear();
+        return v;
     };
     // the most one item may cost, from the symmetric pairs' kernel values
     auto cost_cap = [&](const std::vector<int64_t>& tc, const std::vector<int64_t>& sc, auto&& values) {
@@ -990,16 +992,29 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
         const double cap = cost_cap(L.tc[PC], L.sc[PC], [&](int64_t e, int64_t a, int64_t) {
             return (double)T.count[a] * (double)cube(L.deg[PC].empty() ? degree : (int)L.deg[PC][e]);
         });
+        // the share of its lanes' time that a tile's targets use: whole tiles of 256
+        // at four per lane, and a tail at two per lane (128 lanes' worth, a tenth
+        // slower) or one (64, half as fast: a source read per pair)
+        auto lane_use = [](int64_t n) {
+            const int64_t tail = n % 256;
+            const double lanes = (double)(n - tail) + (tail == 0 ? 0.0 : (tail <= 64 ? 100.0 : (tail <= 128 ? 140.0 : 256.0)));
+            return (double)n / lanes;
+        };
+        double grid_use[kMaxDegree + 1];
+        for (int d = 0; d <= kMaxDegree; ++d) grid_use[d] = cut.proxy_tiles ? lane_use(cube(d)) : 0.0;
+        auto by_proxies = [&](int64_t a, int d) { return lane_use(T.count[a]) < grid_use[d]; };
         // per (cluster A, degree d): the partners B whose PC and CP pairs with A
-        // are both listed at d, as proxy entries; tiles of A's particles
-        std::vector<SymBlock>& blks = blocks();
+        // are both listed at d, as proxy entries; tiles of A's particles.  Then
+        // per (cluster B, degree d) the partners A of the other pairs, as merged
+        // particle ranges cut into chunks; tiles of B's proxies.
+        std::vector<SymBlock>&blks = blocks(), &cblks = blocks(1);
         parallel_run(nblk, [&](int64_t bi) {
             SymBlock& B = blks[bi];
             for (int64_t a = bi * kBlk; a < std::min(nc, (bi + 1) * kBlk); ++a) {
                 uint32_t used = 0;
                 for (int64_t q = ipc.off[a]; q < ipc.off[a + 1]; ++q) used |= ipc.both[q] ? 1u << ipc.part[q].deg() : 0u;
                 for (int d = 0; d <= kMaxDegree; ++d) {
-                    if (!(used >> d & 1)) continue;
+                    if (!(used >> d & 1) || by_proxies(a, d)) continue;
                     const int64_t eb = (int64_t)B.entries.size();
                     for (int64_t q = ipc.off[a]; q < ipc.off[a + 1]; ++q) {
                         const int64_t b = ipc.part[q].sc();
@@ -1023,8 +1038,41 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
                     }
                 }
             }
+            if (!cut.proxy_tiles) return;
+            SymBlock& C = cblks[bi];
+            std::vector<std::pair<int64_t, int64_t>> rp, none;
+            std::vector<int32_t> first;
+            for (int64_t b = bi * kBlk; b < std::min(nc, (bi + 1) * kBlk); ++b) {
+                uint32_t used = 0;
+                for (int64_t q = icp.off[b]; q < icp.off[b + 1]; ++q) used |= icp.both[q] ? 1u << icp.part[q].deg() : 0u;
+                for (int d = 0; d <= kMaxDegree; ++d) {
+                    if (!(used >> d & 1)) continue;
+                    int64_t src = 0;
+                    for (int64_t q = icp.off[b]; q < icp.off[b + 1]; ++q) {
+                        const int64_t a = icp.part[q].sc();
+                        if (icp.part[q].deg() != d || !icp.both[q] || !by_proxies(a, d)) continue;
+                        rp.emplace_back(T.begin[a], T.count[a]);       // separated: never r = 0
+                        src += T.count[a];
+                    }
+                    if (rp.empty()) continue;
+                    const int64_t eb = (int64_t)C.entries.size(), np = cube(d);
+                    emit_ranges(rp, none, C.entries);
+                    const int64_t chunk = chunk_sources(std::min<int64_t>(256, np), cap, std::max<int64_t>(1, cut.min_src));
+                    if (src > chunk) chunk_ranges(C.entries, eb, chunk, first);
+                    else first = {(int32_t)eb, (int32_t)C.entries.size()};
+                    C.evals += 2.0 * (double)np * (double)src;
+                    for (int64_t lb = 0; lb < np; lb += 256) {
+                        const int64_t ln = std::min<int64_t>(256, np - lb);
+                        for (size_t c = 0; c + 1 < first.size(); ++c)
+                            C.items.push_back({(double)ln * (double)std::min(chunk, src - (int64_t)c * chunk),
+                                               Item{(int32_t)lb, (int32_t)ln, first[c], first[c + 1], (int32_t)b,
+                                                    (int32_t)d, (int32_t)b}});
+                    }
+                }
+            }
         });
         gather(blks, sw.pc_entries, sw.pc_items, sw.pc_evaluations);
+        if (cut.proxy_tiles) gather(cblks, sw.cp_entries, sw.cp_items, sw.pc_evaluations);
     }
 }
 
@@ -1039,8 +1087,8 @@ namespace {
 // Slots of one item of a fold group: its targets, its sources, or both.
 int64_t group_item_slots(const FoldGroup& g, const Item& it) {
     int64_t n = 0;
-    if (g.kind != FoldGroup::kProxySources) n += it.tn;
-    if (g.kind == FoldGroup::kParticleTargets) return n;
+    if (g.kind != FoldGroup::kProxySources && g.kind != FoldGroup::kParticleSources) n += it.tn;
+    if (g.kind == FoldGroup::kParticleTargets || g.kind == FoldGroup::kProxyTargets) return n;
     if (g.kind == FoldGroup::kProxyBoth || g.kind == FoldGroup::kProxySources)
         return n + cube(it.degree) * (int64_t)(it.ee - it.eb);
     for (int32_t e = it.eb; e < it.ee; ++e) n += (int64_t)((*g.entries)[e].b & kCountMask);
@@ -1086,8 +1134,9 @@ void fold_group_parts(const Tree& T, bool proxies, const std::vector<FoldGroup>&
         std::vector<uint8_t> used(nc * D, 0);
         for (const FoldGroup& g : groups)
             for (const Item& it : *g.items) {
-                if (g.kind == FoldGroup::kProxyBoth) used[it.degree * nc + it.cluster] = 1;
-                for (int32_t e = it.eb; e < it.ee; ++e) used[it.degree * nc + (*g.entries)[e].a] = 1;
+                if (g.kind == FoldGroup::kProxyBoth || g.kind == FoldGroup::kProxyTargets)
+                    used[it.degree * nc + it.cluster] = 1;
+                for (int32_t e = it.eb; e < it.ee && g.kind != FoldGroup::kProxyTargets; ++e) used[it.degree * nc + (*g.entries)[e].a] = 1;
             }
         seg_of.assign(nc * D, -1);
         for (int d = 0; d < D; ++d)
@@ -1098,13 +1147,13 @@ void fold_group_parts(const Tree& T, bool proxies, const std::vector<FoldGroup>&
                 }
     }
     auto leaf_at = [&](int64_t pos) {
-        const size_t k = (size_t)(std::upper_bound(leaf_begin.begin(), leaf_begin.end(), pos) - leaf_begin.begin()) - 1;
-        return leaf_id[k];
+        return (size_t)(std::upper_bound(leaf_begin.begin(), leaf_begin.end(), pos) - leaf_begin.begin()) - 1;
     };
     // parts of a particle range [a, a + len) whose slots start at o, split at leaf boundaries
     auto range_parts = [&](int64_t a, int64_t len, int64_t o, auto&& put) {
-        for (int64_t pos = a; pos < a + len;) {
-            const int64_t L = leaf_at(pos);
+        size_t k = leaf_at(a);
+        for (int64_t pos = a; pos < a + len; ++k) {
+            const int64_t L = leaf_id[k];
             const int64_t end = std::min(a + len, T.begin[L] + T.count[L]);
             put(seg_of[L], FoldPart{o + (pos - a), (int32_t)(pos - T.begin[L]), (int32_t)(end - pos)});
             pos = end;
@@ -1136,9 +1185,14 @@ void fold_group_parts(const Tree& T, bool proxies, const std::vector<FoldGroup>&
         case FoldGroup::kParticleTargets:
             range_parts(it.t0, it.tn, o, put);
             return;
+        case FoldGroup::kProxyTargets:
+            put(seg_of[it.degree * nc + it.cluster], FoldPart{o, it.t0, it.tn});
+            return;
         default:
-            put(seg_of[it.cluster], FoldPart{o, (int32_t)(it.t0 - T.begin[it.cluster]), it.tn});
-            o += it.tn;
+            if (G.kind == FoldGroup::kParticleBoth) {
+                put(seg_of[it.cluster], FoldPart{o, (int32_t)(it.t0 - T.begin[it.cluster]), it.tn});
+                o += it.tn;
+            }
             for (int32_t e = it.eb; e < it.ee; ++e) {
                 const int64_t len = entries[e].b & kCountMask;
                 range_parts(entries[e].a, len, o, put);
@@ -1149,7 +1203,9 @@ void fold_group_parts(const Tree& T, bool proxies, const std::vector<FoldGroup>&
     // parts grouped by segment, chunks of items in order (a parallel counting
     // sort: chunk k's parts of a segment follow those of chunks < k)
     const int64_t ns = (int64_t)f.segs.size();
-    const int64_t nch = std::max<int64_t>(1, std::min<int64_t>(num_threads(), ni / 256 + 1));
+    int64_t work = ni;
+    for (const FoldGroup& g : groups) work += (int64_t)g.entries->size();
+    const int64_t nch = std::max<int64_t>(1, std::min<int64_t>(num_threads(), work / 512 + 1));
     const int64_t per = (ni + nch - 1) / nch;
     std::vector<int32_t> cnt(nch * ns, 0);
     parallel_run(nch, [&](int64_t k) {
@@ -1176,9 +1232,11 @@ void fold_group_parts(const Tree& T, bool proxies, const std::vector<FoldGroup>&
 
 void build_pc_folds(const Tree& T, SymWork& sw) {
     std::vector<std::vector<int64_t>> pb, cb;
-    const std::vector<FoldGroup> pg{{&sw.pc_items, &sw.pc_entries, FoldGroup::kParticleTargets}};
+    const std::vector<FoldGroup> pg{{&sw.pc_items, &sw.pc_entries, FoldGroup::kParticleTargets},
+                                    {&sw.cp_items, &sw.cp_entries, FoldGroup::kParticleSources}};
     const std::vector<FoldGroup> cg{{&sw.cc_items, &sw.cc_entries, FoldGroup::kProxyBoth},
-                                    {&sw.pc_items, &sw.pc_entries, FoldGroup::kProxySources}};
+                                    {&sw.pc_items, &sw.pc_entries, FoldGroup::kProxySources},
+                                    {&sw.cp_items, &sw.cp_entries, FoldGroup::kProxyTargets}};
     sw.pc_fold.clear();
     sw.cc_fold.clear();
     sw.pc_fold.nslots = fold_group_bases(pg, pb);
@@ -1186,8 +1244,10 @@ void build_pc_folds(const Tree& T, SymWork& sw) {
     fold_group_parts(T, false, pg, pb, sw.pc_fold);
     fold_group_parts(T, true, cg, cb, sw.cc_fold);
     sw.pc_fold.ibase = std::move(pb[0]);
+    sw.cp_sbase = std::move(pb[1]);
     sw.cc_fold.ibase = std::move(cb[0]);
     sw.pc_sbase = std::move(cb[1]);
+    sw.cp_tbase = std::move(cb[2]);
 }
 
 double pc_source_slots(const Tree& T, const Lists& L, int degree, int tile) {

@@ -180,9 +180,107 @@ void run_one_way(int64_t m, int64_t n, int64_t leaf, int degree, double theta, i
     }
 }
 
+// PC/CP pairs once for both: with proxy_tiles some become items over proxy tiles
+// with particle ranges.  Through their slots and the two folds, every particle
+// must meet the same proxies and every proxy the same particles as without, and
+// no pair may come twice.
+void run_pc(int64_t n, int64_t leaf, int degree, double theta, ItemCut cut) {
+    std::mt19937_64 rng(n * 13 + leaf);
+    std::normal_distribution<double> g(0.0, 0.25);
+    std::vector<double> x[3], s[3];
+    for (auto& v : x) {
+        v.resize(n);
+        for (double& a : v) a = g(rng);
+    }
+    Tree T;
+    build_tree(n, x[0].data(), x[1].data(), x[2].data(), leaf, T, s[0], s[1], s[2]);
+    Lists L;
+    traverse(T, T, theta, degree, kSchemeDtt, L);
+    const int64_t P = cube3(degree);
+    std::vector<double> pout[2], cout[2];
+    double evals[2];
+    int64_t rest[2];
+    size_t cp = 0, pc = 0;
+    for (int k = 0; k < 2; ++k) {
+        Lists r;
+        SymWork w;
+        cut.proxy_tiles = k == 1;
+        split_symmetric(T, L, degree, true, true, r, w, {}, false, true, 256, cut);
+        build_pc_folds(T, w);
+        rest[k] = (int64_t)(r.tc[PC].size() + r.tc[CP].size());
+        evals[k] = w.pc_evaluations;
+        if (k == 0) check(w.cp_items.empty() && w.cp_entries.empty(), "no proxy tiles unless asked for");
+        cp = w.cp_items.size();
+        pc = w.pc_items.size();
+        std::vector<double> ps(w.pc_fold.nslots, 0.0), cs(w.cc_fold.nslots, 0.0);
+        std::vector<int> pw(ps.size(), 0), cw(cs.size(), 0);
+        // the CC items' own slots are not under test: no values, marked as written
+        const int64_t c0 = w.pc_items.empty() ? (w.cp_items.empty() ? w.cc_fold.nslots : w.cp_tbase[0]) : w.pc_sbase[0];
+        for (int64_t i = 0; i < c0; ++i) cw[i] = 1;
+        auto span = [&](int64_t a, int64_t c) {
+            double v = 0.0;
+            for (int64_t i = 0; i < c; ++i) v += weight(a + i);
+            return v;
+        };
+        auto put = [&](std::vector<double>& sl, std::vector<int>& wr, int64_t o, int64_t c, double v) {
+            for (int64_t i = o; i < o + c; ++i) {
+                sl[i] = v;
+                wr[i]++;
+            }
+        };
+        for (size_t i = 0; i < w.pc_items.size(); ++i) {
+            const Item& it = w.pc_items[i];
+            double src = 0.0;
+            for (int32_t e = it.eb; e < it.ee; ++e) {
+                const int64_t b = w.pc_entries[e].a;
+                src += span(b * P, P);
+                put(cs, cw, w.pc_sbase[i] + (e - it.eb) * P, P, span(it.t0, it.tn));
+            }
+            put(ps, pw, w.pc_fold.ibase[i], it.tn, src);
+        }
+        for (size_t i = 0; i < w.cp_items.size(); ++i) {
+            const Item& it = w.cp_items[i];
+            const double tgt = span(it.cluster * P + it.t0, it.tn);
+            double src = 0.0;
+            int64_t o = w.cp_sbase[i];
+            check(it.ee > it.eb && it.tn > 0 && it.tn <= 256 && it.t0 + it.tn <= P, "proxy tile", (long long)i);
+            for (int32_t e = it.eb; e < it.ee; ++e) {
+                const int64_t c = w.cp_entries[e].b & kCountMask;
+                src += span(w.cp_entries[e].a, c);
+                put(ps, pw, o, c, tgt);
+                o += c;
+            }
+            put(cs, cw, w.cp_tbase[i], it.tn, src);
+        }
+        for (size_t i = 0; i < pw.size(); ++i) check(pw[i] == 1, "particle slot written once", (long long)i, pw[i]);
+        for (size_t i = 0; i < cw.size(); ++i) check(cw[i] == 1, "proxy slot written once", (long long)i, cw[i]);
+        auto fold = [](const SymFold& f, const std::vector<double>& sl, std::vector<double>& out) {
+            for (const FoldSeg& sg : f.segs)
+                for (int32_t q = sg.pb; q < sg.pe; ++q)
+                    for (int32_t i = 0; i < f.parts[q].len; ++i)
+                        out[sg.off + f.parts[q].lo + i] += sl[f.parts[q].slot + i];
+        };
+        pout[k].assign(n, 0.0);
+        cout[k].assign(T.size() * P, 0.0);
+        fold(w.pc_fold, ps, pout[k]);
+        fold(w.cc_fold, cs, cout[k]);
+    }
+    check(evals[0] == evals[1] && rest[0] == rest[1], "PC/CP terms");
+    check(pout[0] == pout[1], "particle sums of the PC/CP items");
+    check(cout[0] == cout[1], "proxy sums of the PC/CP items");
+    std::printf("PC/CP n %lld leaf %lld degree %d: %zu particle items, %zu proxy items\n", (long long)n, (long long)leaf,
+                degree, pc, cp);
+}
+
 }  // namespace
 
 int main() {
+    run_pc(4000, 40, 3, 0.8, ItemCut{4096, 256});
+    run_pc(6000, 100, 5, 0.8, ItemCut{2048, 256});
+    run_pc(9000, 70, 6, 0.8, ItemCut{0, 1});
+    run_pc(9000, 300, 8, 0.9, ItemCut{1000000, 1});
+    run_pc(30000, 1500, 9, 0.9, ItemCut{4096, 256});
+    run_pc(300, 500, 3, 0.7, ItemCut{4096, 256});
     run_one_way(3000, 9000, 200, 3, 0.7, kSchemeDtt, ItemCut{4096, 256});
     run_one_way(700, 20000, 1000, 5, 0.8, kSchemeBltc, ItemCut{4096, 256});
     run_one_way(20000, 700, 300, 4, 0.8, kSchemeCpBltc, ItemCut{4096, 256});
