@@ -99,7 +99,7 @@ PMC_PASSES = {
 # the symmetric passes of the two timed forms, by kernel; where one kernel runs
 # two passes, its dispatch groups (by grid) are told apart by duration, longest first
 PMC_PASS_NAMES = {
-    "plain": {"k_sym<false, false>": ("pp_sym", "pp_self"), "k_sym<false, true>": ("cc_sym",)},
+    "plain": {"k_sym<0, false, false>": ("pp_sym", "pp_self"), "k_sym<0, false, true>": ("cc_sym",)},
     "tuned": {"k_sym_mfma<false, false>": ("pp_sym",), "k_sym_mfma<false, true>": ("pp_sym", "pp_self"),
               "k_sym_mfma<true, false>": ("cc_sym",)},
     "batch": {},                # the configuration of the last k_batch dispatch (the timed one)

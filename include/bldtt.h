@@ -84,17 +84,19 @@ enum {
                                       peaks are equal and 16x16 tiles pad n+1 rows)     */
     BLDTT_ONE_SIDED_PP = 1u << 8,  /* evaluate every PP and CC pair one-sided.  By
                                       default, for targets = sources with the Coulomb
-                                      kernel, a pair of distinct leaves listed as PP in
-                                      both directions, or of clusters listed as CC in
-                                      both directions at one degree, is evaluated once
-                                      for both (G is symmetric; a cluster's proxy grid
-                                      is the same as target and as source); its sums
-                                      go to per-item slots that a fold adds in a stored
-                                      order, so every compute gives the same bits.
-                                      FP64 batches of such problems evaluate their PP
-                                      and CC pairs once for both too, folded the same
-                                      way inside the batch kernel, unless this flag is
-                                      set                                                */
+                                      kernel (in FP64 also Yukawa with param >= 0,
+                                      oscillatory and regularized Coulomb), a pair of
+                                      distinct leaves listed as PP in both directions,
+                                      of clusters listed as CC in both directions at
+                                      one degree, or (FP64) as PC one way and CP the
+                                      other, is evaluated once for both (G is
+                                      symmetric; a cluster's proxy grid is the same as
+                                      target and as source); its sums go to per-item
+                                      slots that a fold adds in a stored order, so
+                                      every compute gives the same bits.  FP64 Coulomb
+                                      batches of such problems evaluate these pairs
+                                      once for both too, folded the same way inside
+                                      the batch kernel, unless this flag is set         */
     BLDTT_BLTC = 1u << 9,          /* build the lists of the particle-cluster treecode
                                       (BLTC, Sec. 2.8) instead of Algorithm 2: every
                                       target leaf (a batch) walks the source tree from
@@ -362,9 +364,8 @@ int bldtt_mlp_loss_grad(const float *model, const float *features, const float *
 /* bldtt_mlp_loss_grad for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * allocation): the same kernels and results, with the work memory in a static
- * device array of the library (4.25 MiB, one copy per GPU, held until the
- * process ends) instead of a fresh allocation, and the count of valid targets
- * taken on the device instead of on the host.  Enqueued on hip_stream without
+ * device array of the library (4.1 MiB, one copy per GPU, held until the
+ * process ends) instead of a fresh allocation.  Enqueued on hip_stream without
  * any synchronization; nothing is allocated, freed or copied to the host.
  * n is limited to 1..4096 samples.  Every call on one GPU shares that GPU's
  * array: calls that overlap on one GPU (other streams or threads) race and
@@ -418,7 +419,7 @@ int bldtt_autotune(bldtt_plan *plan, double *scratch, int32_t reps, void *hip_st
  * kernel (work groups take tasks from a counter; dependencies are device
  * counters with bounded waits) captured once in a hipGraph.  The per-problem
  * results equal those of bldtt_setup + bldtt_compute with the same arguments
- * (the same sums in the same order).  Supported: Coulomb and Yukawa (FP64 or
+ * (the same sums; the order of their terms may differ).  Supported: Coulomb and Yukawa (FP64 or
  * BLDTT_FP32_EVAL), POLY_TEST (FP64); degree 1..10; a fixed degree (no
  * BLDTT_LEARNED_DEGREE).
  * ------------------------------------------------------------------------ */

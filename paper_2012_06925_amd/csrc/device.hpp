@@ -6,7 +6,8 @@
 //
 //   interact_body       PP/PC sums into particles, CP/CC sums into proxies
 //   up_leaf_body        proxy charges of a source leaf, Eq. (proxy-charges)
-//   up_transfer_body    parent proxy charges from the children (Sec. 2.5, Appendix B)
+//   up_transfer_body    parent proxy charges from the children (Sec. 2.5, Appendix B);
+//                       up_transfer_mfma_body: on the matrix cores, a wave per child
 //   fold_body           fixed-order sums of the symmetric passes' slots (fold.hpp)
 //   down_transfer_body  parent-to-child interpolation of proxy potentials (Sec. 2.7, Appendix C)
 //   down_leaf_body      leaf proxies to targets plus the PP/PC part, caller order
@@ -1064,11 +1065,10 @@ __device__ __forceinline__ void down_leaf_mfma_body(const DevItem& it, bool far,
 // mod 64 over the targets of its wave.  The wave partials are summed in LDS
 // and written to the source's slot of the entry, each target's sum to its
 // slot at the end (fold.hpp): a fold adds the slots to the outputs in a fixed
-// order, so the result is the same bits every run.  PP ranges flagged SRC_RANGE_GUARD (a leaf
-// with itself, or leaf boxes within 2^-20 of their extent) skip r^2 == 0
-// (coincident points; FP32 relative coordinates of two close points may round
-// together); elsewhere the gap between the boxes keeps r^2 > 0.  CC pairs are
-// separated, so their proxies never meet.
+// order, so the result is the same bits every run.  PP ranges flagged SRC_RANGE_GUARD
+// (a leaf with itself, or near leaf boxes) skip r^2 == 0 (coincident points; FP32
+// relative coordinates of two close points may round together); elsewhere the gap
+// between the boxes keeps r^2 > 0.  CC and PC/CP pairs are separated: never r = 0.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ double rol1(double v) {
     const uint64_t u = __builtin_bit_cast(uint64_t, v);
@@ -1094,7 +1094,8 @@ constexpr int sym_lds_bytes() {
 // partial of the item's g-th source (its entries' sources one after another)
 // goes to sslots[sbase + g].  PROXY: the targets are proxies (of degree
 // it.degree), else particles; SPROXY: the same for the sources (PP: neither,
-// CC: both, the PC/CP pairs of a particle tile with proxy grids: sources).
+// CC: both; PC/CP pairs: the sources of a particle tile, or the targets where the
+// tile is of the grid).
 // A tile of at most 64 targets gets one slab and four copies with H = 1 or 2,
 // and the same bits (a lane's second row is padding with charge 0), so the
 // particle passes give such tiles H = 1 and no lane slot idles; tiles of 129

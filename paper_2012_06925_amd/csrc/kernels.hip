@@ -149,9 +149,10 @@ __global__ __launch_bounds__(kBlock) void k_sym(const DevItem* __restrict__ item
 // against the particles of small partners; the sums of the two sides go to slots
 // of two folds.  A cluster of a few particles as the tile leaves most lanes idle,
 // and at one target per lane each pair reads its source from LDS (the limit), so
-// the grid is the tile there: 1E5 Gaussian particles (leaf 300, n 8; PC clusters
-// of 40..300) 2.73 -> 2.29 ms, 3E5 Yukawa 9.84 -> 9.58.  One launch, because
-// either part may be a few blocks (1E4 particles, leaf 500: 4 and 18).
+// the grid is the tile there: 1E5 Gaussian particles (leaf 2000, n 8) this kernel
+// 590 -> 257 us, the summation 2.74 -> 2.36 ms; 3E5 Yukawa 10.0 -> 9.8 ms.  One
+// launch, because either part may be a few blocks (1E4 particles, leaf 500: 4 and
+// 18; in two launches 200 -> 209 us).
 template <int KIND>
 __global__ __launch_bounds__(kBlock) void k_sym_pc(SymPcPart pc, SymPcPart cp, DevParticles p, DevTree T,
                                                    const double* __restrict__ tab, DegPtrs qhat, double param,
