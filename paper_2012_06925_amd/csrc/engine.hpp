@@ -46,6 +46,10 @@ struct Tree {
     bool is_leaf(int64_t c) const { return nchild[c] == 0; }
 };
 
+// Setups of up to this many particles keep their host work arrays per calling
+// thread (at most 14 arrays of 2 MiB).
+constexpr int64_t kHostScratch = 1 << 18;
+
 // Build the tree of n particles (caller order x, y, z) with at most `leaf`
 // particles per leaf.  On return xs, ys, zs hold the coordinates in tree order.
 void build_tree(int64_t n, const double* x, const double* y, const double* z, int64_t leaf, Tree& t,

@@ -429,11 +429,20 @@ void build_tree(int64_t n, const double* x, const double* y, const double* z, in
     ys.assign(y, y + n);
     zs.assign(z, z + n);
     std::vector<int64_t> idx(n);
-    std::vector<double> s0(n), s1(n), s2(n);
-    std::vector<int64_t> sI(n);
+    // the other half of each partition: kept per thread for problems of up to
+    // kHostScratch particles (fresh pages cost a setup of 1E5 as much as its copies)
+    static thread_local std::vector<double> kept[3];
+    static thread_local std::vector<int64_t> kept_idx;
+    std::vector<double> own[3];
+    std::vector<int64_t> own_idx;
+    std::vector<double>* sX = n <= kHostScratch ? kept : own;
+    std::vector<int64_t>& sI = n <= kHostScratch ? kept_idx : own_idx;
+    for (int d = 0; d < 3; ++d)
+        if ((int64_t)sX[d].size() < n) sX[d].resize(n);
+    if ((int64_t)sI.size() < n) sI.resize(n);
     BuildBufs w;
     w.X[0] = xs.data(); w.X[1] = ys.data(); w.X[2] = zs.data();
-    w.tX[0] = s0.data(); w.tX[1] = s1.data(); w.tX[2] = s2.data();
+    for (int d = 0; d < 3; ++d) w.tX[d] = sX[d].data();
     w.I = idx.data();
     w.tI = sI.data();
     w.leaf = leaf;
