@@ -99,6 +99,23 @@ def test_mirrored_pc_cp_pairs_once_for_both(kernel, n, leaf, degree):
     _close(c, ref)
 
 
+@pytest.mark.parametrize("leaf,degree", [(20, 3), (30, 4), (60, 5), (200, 6), (300, 7)])
+def test_batch_pc_cp_pairs_tiled_over_the_grids(leaf, degree):
+    # grids of 64 (one target per lane), 125 (two), 216 and 343 (four, a tail of
+    # two), 512 (two full tiles), against clusters of fewer particles
+    from paper_2012_06925_amd import api
+    probs = [inputs.particles(n, "gaussian", seed=80 + k) for k, n in enumerate((900, 4001, 9000))]
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()        # noqa: E731
+    b = api.Batch([(None, [dev(a) for a in (p.x, p.y, p.z, p.q)]) for p in probs], kernel="coulomb", theta=0.8,
+                  degree=degree, leaf=leaf)
+    got = [[o.cpu().numpy() for o in b.compute()] for _ in range(2)]
+    assert b.stats()["n_entries"]["PC"] > 0
+    b.close()
+    for p, x, y in zip(probs, *got):
+        assert np.array_equal(x, y)
+        _close(x, core.bldtt(p, p, kernel="coulomb", theta=0.8, degree=degree, leaf=leaf))
+
+
 @pytest.mark.parametrize("kernel", ["coulomb", "yukawa", "oscillatory", "regcoulomb"])
 @pytest.mark.parametrize("nsel", [1, 255, 257, 513, 1030])
 def test_direct_sum_for_every_group_size(kernel, nsel):
