@@ -868,6 +868,13 @@ __device__ __forceinline__ void two_sum(double a, double b, double& s, double& e
     e = (a - (s - bb)) + (b - bb);
 }
 
+// r^2 of coincident points and of points whose squared distance exceeds the largest
+// double (beyond some 1E154 apart): neither contributes; the correction of
+// rsq_fix would give inf * 0.
+__device__ __forceinline__ bool zero_or_inf(double v) {
+    return __builtin_amdgcn_class(v, 0x260);       // +0, -0, +inf
+}
+
 // The kernel's value to the last bit or so (1/r by the cubic correction, not the
 // folded Newton step of the passes).
 template <int KIND>
@@ -879,11 +886,9 @@ __device__ __forceinline__ double g_ref(double tx, double ty, double tz, double 
     }
     const double dx = tx - sx, dy = ty - sy, dz = tz - sz;
     const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
-    if (KIND == K_COULOMB) {
-        double y = rsq_est(r2);
-        y = r2 > 0.0 ? y : 0.0;
-        return rsq_fix(r2, y);
-    }
+    if (KIND == K_COULOMB) return zero_or_inf(r2) ? 0.0 : rsq_fix(r2, rsq_est(r2));
+    if (KIND == K_REG && zero_or_inf(fma(param, param, r2))) return 0.0;
+    if ((KIND == K_YUKAWA || KIND == K_YUKAWA_ANY) && param > 0.0 && r2 == INFINITY) return 0.0;
     return G64<KIND>::template value<true>(r2, param);
 }
 

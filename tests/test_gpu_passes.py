@@ -130,3 +130,24 @@ def test_direct_sum_for_every_group_size(kernel, nsel):
         got = api.direct_sum(dev[:3], dev, kernel=kernel, sel=torch.from_numpy(sel).cuda()).cpu().numpy()
         ref = core.direct_sum(p, p, kernel=kernel)[sel]
         assert np.abs(got - ref).max() <= 1e-13 * max(np.abs(ref).max(), 1e-300)
+
+
+@pytest.mark.parametrize("kernel,param", [("coulomb", None), ("yukawa", 0.5), ("yukawa", -0.5), ("regcoulomb", 0.005),
+                                          ("regcoulomb", 1e160)])
+def test_direct_sum_at_the_ends_of_the_range(kernel, param):
+    # squared distances (and param^2) beyond the largest double give 1/inf = 0, not
+    # inf * 0; points 1E-150 apart, whose squares are near the smallest double, count
+    from paper_2012_06925_amd import api
+    rng = np.random.default_rng(5)
+    p = inputs.particles(700, "uniform", seed=75)
+    p.x[:50], p.y[:50], p.z[:50] = 1e-150 * rng.random((3, 50))
+    far = param is None or param > 0                       # exp(inf)/inf has no value
+    if far:
+        p.x[600:] = 1e200 * rng.choice([-3.0, -2.0, 1.0, 2.0], 100) + 1e198 * rng.random(100)
+    dev = [torch.from_numpy(a).cuda() for a in (p.x, p.y, p.z, p.q)]
+    got = api.direct_sum(dev[:3], dev, kernel=kernel, param=param).cpu().numpy()
+    ref = core.direct_sum(p, p, kernel=kernel, param=param)
+    p.q = np.abs(p.q)
+    scale = core.direct_sum(p, p, kernel=kernel, param=param)      # each term to a few roundings
+    assert np.all(np.isfinite(ref)) and np.all(np.isfinite(got))
+    assert np.all(np.abs(got - ref) <= 1e-14 * scale), np.max(np.abs(got - ref) / np.maximum(scale, 1e-300))
