@@ -151,3 +151,26 @@ def test_direct_sum_at_the_ends_of_the_range(kernel, param):
     scale = core.direct_sum(p, p, kernel=kernel, param=param)      # each term to a few roundings
     assert np.all(np.isfinite(ref)) and np.all(np.isfinite(got))
     assert np.all(np.abs(got - ref) <= 1e-14 * scale), np.max(np.abs(got - ref) / np.maximum(scale, 1e-300))
+
+
+@pytest.mark.parametrize("kernel,param,scale", [("yukawa", 0.0, 1.0), ("yukawa", 1e-3, 1.0), ("yukawa", 20.0, 1.0),
+                                                ("yukawa", 300.0, 1.0), ("yukawa", 1000.0, 1.0), ("yukawa", -0.5, 1.0),
+                                                ("regcoulomb", 3.0, 1.0), ("oscillatory", None, 60.0)])
+def test_values_over_the_parameters_range(kernel, param, scale):
+    # exponents from nothing to far below the smallest double (r up to 3.4), a
+    # growing exponential, distances of up to 100 wavelengths: the symmetric
+    # passes, the one-sided ones and the direct sum, each against the oracle
+    from paper_2012_06925_amd import api
+    p = inputs.particles(4001, "uniform", seed=76)
+    for a in (p.x, p.y, p.z):
+        a *= scale
+    kw = dict(kernel=kernel, param=param, theta=0.7, degree=3, leaf=60)
+    ref = core.bldtt(p, p, **kw)
+    for flags in (0, _lib.ONE_SIDED_PP):
+        plan = _plan(p, flags=flags, **kw)
+        got = _computes(plan, 1)[0]
+        plan.close()
+        _close(got, ref)
+    dev = [torch.from_numpy(a).cuda() for a in (p.x, p.y, p.z, p.q)]
+    _close(api.direct_sum(dev[:3], dev, kernel=kernel, param=param).cpu().numpy(),
+           core.direct_sum(p, p, kernel=kernel, param=param))
