@@ -27,7 +27,7 @@ constexpr int kBlock = 256;
 constexpr int kChunk = 512;                  // sources staged in LDS per round
 
 // K_YUKAWA_ANY: Yukawa in FP64 with the library's exp, for a param the fast form does
-// not take (negative, infinite or NaN) and for the batch kernel
+// not take (negative, above kYukawaParamMax or NaN) and for the batch kernel
 enum { K_COULOMB = 0, K_YUKAWA = 1, K_OSC = 2, K_REG = 3, K_YUKAWA_ANY = 4, K_POLY = 100 };
 
 // ---------------------------------------------------------------------------
@@ -118,7 +118,8 @@ __device__ __forceinline__ double osc_value(double r2, double y0) {
     return copysign(fma(m, 0x1.921fb54442d18p+1, m * q), f) * y;
 }
 
-// exp(-param r) / r of the Yukawa kernel, 0 <= param < inf.  r is r2 times the
+// exp(-param r) / r of the Yukawa kernel, 0 <= param <= kYukawaParamMax (param times
+// log2(e) must stay finite).  r is r2 times the
 // rounded 1/r, whose error partly cancels between the two factors.
 // exp(-param r) = 2^n e^t with n = rint(-param r / ln2): t = (-param r - n ln2_hi) -
 // n ln2_lo has param r inside an FMA and n ln2_hi exact, so -param r is never
@@ -129,6 +130,7 @@ __device__ __forceinline__ double osc_value(double r2, double y0) {
 // range checks: the one-sided passes of 2E6 targets and 1E7 sources 77 -> 69 ms
 // (bound by FP64 issue), the value's rms error 8.5e-17 as before for param 0.5,
 // r < 3.5, and smaller where param r is larger.
+constexpr double kYukawaParamMax = 1e300;
 __device__ __forceinline__ double yukawa_value(double r2, double y0, double param) {
     const double y = rsq_fix(r2, y0);
     const double r = fmin(r2 * y, 2000.0 / param);                // the quotient is the same for every pair

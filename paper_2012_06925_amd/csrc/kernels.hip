@@ -1122,7 +1122,7 @@ void launch_interact(KernelSpec k, bool fp32, bool proxy_targets, int tpt, const
     if (fp32) {
         if (proxy_targets) { DISPATCH_KIND(k.kind, LAUNCH_ONE(true, true)); }
         else { DISPATCH_KIND(k.kind, LAUNCH_ONE(true, false)); }
-    } else if (k.kind == K_YUKAWA && !(k.param >= 0.0 && k.param < INFINITY)) {
+    } else if (k.kind == K_YUKAWA && !(k.param >= 0.0 && k.param <= kYukawaParamMax)) {
         constexpr int KK = K_YUKAWA_ANY;
         if (proxy_targets) LAUNCH_ONE(false, true);
         else LAUNCH_ONE(false, false);

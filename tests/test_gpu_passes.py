@@ -174,3 +174,13 @@ def test_values_over_the_parameters_range(kernel, param, scale):
     dev = [torch.from_numpy(a).cuda() for a in (p.x, p.y, p.z, p.q)]
     _close(api.direct_sum(dev[:3], dev, kernel=kernel, param=param).cpu().numpy(),
            core.direct_sum(p, p, kernel=kernel, param=param))
+
+
+@pytest.mark.parametrize("param", [1e300, 1.2e308, 1.79e308])
+def test_yukawa_with_a_param_near_the_largest_double(param):
+    # param * log2(e) is infinite from 1.25E308 on; every value underflows to 0
+    p = inputs.particles(3000, "uniform", seed=77)
+    plan = _plan(p, kernel="yukawa", param=param, theta=0.7, degree=3, leaf=60)
+    got = _computes(plan, 1)[0]
+    plan.close()
+    assert not np.any(got)
