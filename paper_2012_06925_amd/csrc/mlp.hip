@@ -201,11 +201,13 @@ __global__ __launch_bounds__(kBlock) void k_grad_part(const float* __restrict__ 
     for (int64_t b = (int64_t)blockIdx.x * S; b < n; b += (int64_t)gridDim.x * S) {
         __syncthreads();                                   // the last round's readers are done
         if (t < S) {
-            float f[kNIn] = {0.f, 0.f, 0.f, 0.f}, x[kNIn];
-            if (b + t < n)
+            float x[kNIn] = {0.f, 0.f, 0.f, 0.f};          // past the last sample: any finite value
+            if (b + t < n) {
+                float f[kNIn];
 #pragma unroll
                 for (int k = 0; k < kNIn; ++k) f[k] = feats[kNIn * (b + t) + k];
-            normalise(M, f, x);
+                normalise(M, f, x);
+            }
 #pragma unroll
             for (int k = 0; k < kNIn; ++k) X[t][k] = x[k];
         }
