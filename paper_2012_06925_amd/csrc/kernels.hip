@@ -854,13 +854,13 @@ __global__ __launch_bounds__(kBlock) void k_pair_error(const int32_t* __restrict
 }
 
 // ---------------------------------------------------------------------------
-// Direct sum with compensated accumulation.  A work group of 16 waves takes T
-// targets; its threads share the sources, each source read once for the T
-// targets, and the threads' sums are added pairwise with their errors.  Bound by
-// FP64 issue (25 operations a term, 7 of them the compensation) once a source
-// read from the shared caches serves several targets: one target per group of
-// four waves, with a square root and a division per term, read 32 bytes a term
-// and took 2.80 ms for 1000 targets and 1E6 sources, now 1.03 ms.
+// Direct sum with compensated accumulation.  A work group takes T targets; its
+// threads share the sources, each source read once for the T targets, and the
+// threads' sums are added pairwise with their errors.  Bound by FP64 issue (25
+// operations a term, 7 of them the compensation) once a source read from the
+// shared caches serves several targets: one target per group of four waves, with
+// a square root and a division per term, read 32 bytes a term and took 2.80 ms
+// for 1000 targets and 1E6 sources, groups of 16 waves and four targets 0.91 ms.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void two_sum(double a, double b, double& s, double& e) {
     s = a + b;
@@ -915,16 +915,14 @@ __device__ __forceinline__ double g_ref(double tx, double ty, double tz, double 
     return r2 == 0.0 ? 0.0 : g;
 }
 
-constexpr int kDirectBlock = 1024;
-
-template <int KIND, int T>
-__global__ __launch_bounds__(kDirectBlock) void k_direct(int64_t nsel, const int64_t* __restrict__ sel,
+template <int KIND, int T, int NT>
+__global__ __launch_bounds__(NT) void k_direct(int64_t nsel, const int64_t* __restrict__ sel,
                                                          const double* __restrict__ tx, const double* __restrict__ ty,
                                                          const double* __restrict__ tz, int64_t N,
                                                          const double* __restrict__ sx, const double* __restrict__ sy,
                                                          const double* __restrict__ sz, const double* __restrict__ q,
                                                          double param, double* __restrict__ out) {
-    __shared__ double rs[kDirectBlock], rc[kDirectBlock];
+    __shared__ double rs[NT], rc[NT];
     const int64_t a0 = (int64_t)blockIdx.x * T;
     double x[T], y[T], z[T], s[T], c[T];
 #pragma unroll
@@ -935,7 +933,7 @@ __global__ __launch_bounds__(kDirectBlock) void k_direct(int64_t nsel, const int
         z[k] = tz[i];
         s[k] = c[k] = 0.0;
     }
-    for (int64_t j = threadIdx.x; j < N; j += kDirectBlock) {
+    for (int64_t j = threadIdx.x; j < N; j += NT) {
         const double jx = sx[j], jy = sy[j], jz = sz[j], jq = q[j];
 #pragma unroll
         for (int k = 0; k < T; ++k) {
@@ -952,7 +950,7 @@ __global__ __launch_bounds__(kDirectBlock) void k_direct(int64_t nsel, const int
         rs[threadIdx.x] = s[k];
         rc[threadIdx.x] = c[k];
         __syncthreads();
-        for (int w = kDirectBlock / 2; w > 0; w >>= 1) {
+        for (int w = NT / 2; w > 0; w >>= 1) {
             if ((int)threadIdx.x < w) {
                 double u, e;
                 two_sum(rs[threadIdx.x], rs[threadIdx.x + w], u, e);
@@ -1244,10 +1242,27 @@ void launch_prolong(const DevItem* items, int n_items, DevTree T, const double* 
 }
 
 namespace {
-// Targets per work group: as many as still give about a group per CU (256).  1E6
-// sources: 100 targets 0.44 / 0.56 / 0.91 ms with 1 / 2 / 4; 500: 1.00 / 0.66 /
-// 0.93; 1000: 2.01 / 1.20 / 1.03; 8 no faster than 4 from 2000 on (1.89 ms both).
-int direct_targets(int64_t nsel) { return nsel > 512 ? 4 : (nsel > 256 ? 2 : 1); }
+// Targets per work group: one while the targets are no more than the CUs (256), two
+// up to twice as many, then four, where fewer reads of the sources outweigh the CUs
+// left over (at 513 targets half of them).  1E6 sources, 1 / 2 / 4 targets per group:
+// 100 targets 0.43 / 0.54 / 0.91 ms; 300: 0.88 / 0.54 / 0.90; 513: 1.39 / 1.00 /
+// 0.90; 900: 1.91 / 1.03 / 0.91; 1100: 2.33 / 1.52 / 1.67; 1600: 3.14 / 2.04 / 1.67;
+// 8 no faster than 4 from 2000 on.
+int direct_targets(int64_t nsel) {
+    static thread_local int dev = -1, cus = 256;
+    int d = 0;
+    if (hipGetDevice(&d) == hipSuccess && d != dev) {
+        (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, d);
+        dev = d;
+    }
+    return nsel > 2 * (int64_t)cus ? 4 : (nsel > cus ? 2 : 1);
+}
+
+// Sources below which a group has 4 waves instead of 16: with a few sources per
+// thread the pairwise sum of its threads is most of the work.  1E6 targets, 4 / 16
+// waves: 300 sources 0.67 / 3.13 ms, 1000 1.02 / 3.42, 3000 2.68 / 4.13, 10000 8.56
+// / 9.08; but 700 targets of 10000 sources 17.8 / 15.8 us.
+constexpr int64_t kDirectFewSources = 8192;
 }  // namespace
 
 void launch_direct(KernelSpec k, int64_t nsel, const int64_t* sel, const double* tx, const double* ty,
@@ -1256,12 +1271,15 @@ void launch_direct(KernelSpec k, int64_t nsel, const int64_t* sel, const double*
     if (nsel <= 0) return;
     const int t = direct_targets(nsel);
     const dim3 grid((unsigned)((nsel + t - 1) / t));
-#define LAUNCH_T(T) hipLaunchKernelGGL((k_direct<KK, T>), grid, dim3(kDirectBlock), 0, st, nsel, sel, tx, ty, tz, N, sx, sy, \
-                                       sz, q, k.param, out)
+    const bool few = N < kDirectFewSources;
+#define LAUNCH_NT(T, NT) hipLaunchKernelGGL((k_direct<KK, T, NT>), grid, dim3(NT), 0, st, nsel, sel, tx, ty, tz, N, sx, sy, \
+                                            sz, q, k.param, out)
+#define LAUNCH_T(T) do { if (few) LAUNCH_NT(T, 256); else LAUNCH_NT(T, 1024); } while (0)
 #define LAUNCH_DIRECT switch (t) { case 1: LAUNCH_T(1); break; case 2: LAUNCH_T(2); break; default: LAUNCH_T(4); break; }
     DISPATCH_KIND(k.kind, LAUNCH_DIRECT);
 #undef LAUNCH_DIRECT
 #undef LAUNCH_T
+#undef LAUNCH_NT
     CHECK_LAUNCH();
 }
 

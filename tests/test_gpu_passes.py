@@ -184,3 +184,17 @@ def test_yukawa_with_a_param_near_the_largest_double(param):
     got = _computes(plan, 1)[0]
     plan.close()
     assert not np.any(got)
+
+
+@pytest.mark.parametrize("n", [1, 63, 300, 8191, 8192])
+@pytest.mark.parametrize("nsel", [1, 300, 1030])
+def test_direct_sum_for_few_and_many_sources(n, nsel):
+    # groups of 4 waves below 8192 sources and of 16 from there on, also with
+    # fewer sources than threads, for one, two and four targets per group
+    from paper_2012_06925_amd import api
+    t, s = inputs.particles(nsel, "gaussian", seed=78), inputs.particles(n, "uniform", seed=79)
+    dev = lambda *v: [torch.from_numpy(a).cuda() for a in v]                 # noqa: E731
+    got = api.direct_sum(dev(t.x, t.y, t.z), dev(s.x, s.y, s.z, s.q)).cpu().numpy()
+    ref = core.direct_sum(t, s)
+    s.q = np.abs(s.q)
+    assert np.all(np.abs(got - ref) <= 1e-14 * core.direct_sum(t, s))
