@@ -11,6 +11,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <memory>
 #include <string>
@@ -65,7 +66,7 @@ struct bldtt_batch {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     int tpt = 2, groups_per_cu = 0, grid = 0, spin_limit = 1 << 22;
-    int cus = 0;
+    int cus = 256;                           // of the MI355X; device batches read their device's
     bool packed_tpt_valid = false;
     int packed_tpt = 0;
 
@@ -304,23 +305,59 @@ void upload_folds(bldtt_batch* b) {
     upload(b->cseg, cseg);
 }
 
+int64_t count_tasks(const bldtt_batch* b) {
+    const Work& w = b->work;
+    const SymWork& sw = b->sym;
+    return (int64_t)b->n_leaves + b->n_parents + (int64_t)w.qitems.size() + 2 * (int64_t)w.pitems.size() +
+           (int64_t)(sw.pp_items.size() + sw.cc_items.size() + sw.pc_items.size() + sw.cp_items.size()) + b->n_kids;
+}
+
+// The longest symmetric tasks cut along their sources.  A cut shortens the tail of
+// the queue by up to a task's length, and every piece costs the queue a task: its
+// number, a release and an acquire between the XCDs' caches, its part of a fold,
+// about 0.2 us of the launch while the queue of a small batch is what bounds it,
+// as much as 7 sources per wave and resident group.  With W the larger of the work
+// and of the tasks' own cost, tasks of cost `cap` add W / cap pieces, so the cap
+// grows with sqrt(W).  All kinds share one cap: they share the queue.  Cutting each
+// kind into 2048 had made 30 problems of 1E3..5E3 particles, leaf 300, 495 -> 591 us
+// (uncut 505, so 494); 20 of 1E3..2E4 1301 -> 1463 (1235, 1129), leaf 1000 935 -> 729
+// (876, 624); 8 556 -> 497 (471, 359); 40 of 1E3..1E5, where the work is the larger,
+// 8.05 -> 7.24 ms (7.70, 7.31).
+void cut_long_tasks(bldtt_batch* b) {
+    const Work& w = b->work;
+    SymWork& sw = b->sym;
+    double work = 0.0;
+    auto add = [&](const std::vector<Item>& items, const std::vector<Entry>& entries) {
+        for (const Item& it : items) work += item_cost(it, entries);
+    };
+    add(sw.pp_items, sw.pp_entries);
+    add(sw.cc_items, sw.cc_entries);
+    add(sw.pc_items, sw.pc_entries);
+    add(sw.cp_items, sw.cp_entries);
+    add(w.qitems, w.qentries);
+    add(w.pitems, w.pentries);
+    const double groups = 4.0 * b->cus;                       // resident at a time
+    const double cap = 4.0 * std::sqrt(std::max(work, 7.0 * (double)count_tasks(b) * groups));
+    cut_symmetric(sw.pp_items, sw.pp_entries, cap);
+    cut_symmetric(sw.cc_items, sw.cc_entries, cap);
+    cut_symmetric(sw.pc_items, sw.pc_entries, cap);
+    cut_symmetric(sw.cp_items, sw.cp_entries, cap);
+}
+
 // Work items for tile size tpt, their flags and the per-cluster counts.
 void pack(bldtt_batch* b, int tpt) {
     if (b->packed_tpt_valid && b->packed_tpt == tpt) return;
     Work& w = b->work;
     w.guard_near = (b->flags & BLDTT_FP32_EVAL) != 0;   // FP32 batches guard near particle ranges too
     if (b->symmetric()) {
-        // few tasks per resident work group: cut the longest (a task costs fences and
-        // counters, so not as finely as the single plans: 40 problems of up to 1E5
-        // particles 8.25 ms uncut, 7.97 with 2048, 8.41 with 8192; 20 of up to 2E4
-        // 0.97 / 0.83 / 1.05 ms)
-        split_symmetric(b->T(), b->lists, b->degree, true, true, b->rest, b->sym, {}, false, true, 256, ItemCut{2048, 256, true});
+        split_symmetric(b->T(), b->lists, b->degree, true, true, b->rest, b->sym, {}, false, true, 256, ItemCut{0, 1, true});
         const std::vector<uint32_t> extra = sym_cc_degrees(b->T(), b->sym);
         pack_work(b->T(), b->S, b->rest, b->degree, kThreads * tpt, kThreads * tpt, w, &extra);
     } else {
         b->sym.clear();
         pack_work(b->T(), b->S, b->lists, b->degree, kThreads * tpt, kThreads * tpt, w);
     }
+    if (b->symmetric()) cut_long_tasks(b);
     for (int k = 0; k < 4; ++k) b->stats.interactions[k] = w.interactions[k];
     b->stats.interactions[PP] += b->sym.pp_evaluations;
     b->stats.interactions[CC] += b->sym.cc_evaluations;
@@ -328,9 +365,7 @@ void pack(bldtt_batch* b, int tpt) {
     b->stats.interactions[CP] += 0.5 * b->sym.pc_evaluations;
     b->packed_tpt = tpt;
     b->packed_tpt_valid = true;
-    b->stats.n_tasks = (int64_t)b->n_leaves + b->n_parents + (int64_t)w.qitems.size() + 2 * (int64_t)w.pitems.size() +
-                       (int64_t)b->sym.pp_items.size() + (int64_t)b->sym.cc_items.size() +
-                       (int64_t)b->sym.pc_items.size() + (int64_t)b->sym.cp_items.size() + b->n_kids;
+    b->stats.n_tasks = count_tasks(b);
     if (b->host_only) return;
     auto needs = [](const std::vector<Item>& items, const std::vector<Entry>& entries) {
         std::vector<uint8_t> f(items.size(), 0);

@@ -267,6 +267,16 @@ struct CutItems {
 void cut_items(const std::vector<Item>& items, std::vector<Entry>& entries, bool proxies, const ItemCut& cut,
                CutItems& out);
 
+// Cost of an item: its sources times its targets in whole waves of 64.
+double item_cost(const Item& it, const std::vector<Entry>& entries);
+
+// The items of a symmetric pass that cost more than `cap` cut along their sources
+// into pieces of equal size (whole rounds of 256 sources, whole proxy grids), each
+// an item of its own; longest first.  The pieces' entries are appended to
+// `entries`.  For items whose slots are given out afterwards, with no guarded
+// ranges kept apart.
+void cut_symmetric(std::vector<Item>& items, std::vector<Entry>& entries, double cap);
+
 struct SymWork {
     std::vector<Entry> pp_entries, cc_entries, pc_entries, cp_entries;
     std::vector<Item> pp_items, cc_items, pc_items;

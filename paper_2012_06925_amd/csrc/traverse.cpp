@@ -530,19 +530,30 @@ void pack_work(const Tree& T, const Tree& S, const Lists& L, int degree, int til
     sort_items(items, w.qitems);
 }
 
+namespace {
+
+int64_t entry_sources(const Entry& e) {
+    const int low = e.b & kCountMask;
+    return (uint32_t)e.b >> 29 == SRC_PROXY ? cube(low) : (int64_t)low;
+}
+
+}  // namespace
+
+double item_cost(const Item& it, const std::vector<Entry>& entries) {
+    int64_t n = 0;
+    for (int32_t e = it.eb; e < it.ee; ++e) n += entry_sources(entries[e]);
+    return (double)n * (double)((it.tn + 63) / 64);
+}
+
 void cut_items(const std::vector<Item>& items, std::vector<Entry>& entries, bool proxies, const ItemCut& cut,
                CutItems& out) {
     out.clear();
-    auto sources_of = [](const Entry& e) {
-        const int low = e.b & kCountMask;
-        return (uint32_t)e.b >> 29 == SRC_PROXY ? cube(low) : (int64_t)low;
-    };
     // lanes of an item: its targets in whole waves
     auto lanes_of = [](const Item& it) { return (int64_t)(it.tn + 63) / 64 * 64; };
     std::vector<int64_t> src(items.size(), 0);
     double total = 0.0;
     for (size_t i = 0; i < items.size(); ++i) {
-        for (int32_t e = items[i].eb; e < items[i].ee; ++e) src[i] += sources_of(entries[e]);
+        for (int32_t e = items[i].eb; e < items[i].ee; ++e) src[i] += entry_sources(entries[e]);
         total += (double)src[i] * (double)lanes_of(items[i]);
     }
     const double cap = std::max(1.0, total / (double)std::max<int64_t>(1, cut.want));
@@ -590,7 +601,7 @@ void cut_items(const std::vector<Item>& items, std::vector<Entry>& entries, bool
             const Entry en = entries[e];                   // by value: entries grows below
             if ((uint32_t)en.b >> 29 == SRC_PROXY) {       // a grid stays whole
                 entries.push_back(en);
-                have += sources_of(en);
+                have += entry_sources(en);
                 if (have >= each) close();
                 continue;
             }
@@ -619,6 +630,54 @@ void cut_items(const std::vector<Item>& items, std::vector<Entry>& entries, bool
         out.items.push_back(cost[k].second);
         out.fold.ibase.push_back(base[k]);
     }
+}
+
+void cut_symmetric(std::vector<Item>& items, std::vector<Entry>& entries, double cap) {
+    bool any = false;
+    for (const Item& it : items) any = any || item_cost(it, entries) > cap;
+    if (!any) return;
+    std::vector<std::pair<double, Item>> cost;
+    cost.reserve(items.size());
+    for (const Item& it : items) {
+        const double c = item_cost(it, entries), lanes = (double)((it.tn + 63) / 64);
+        // pieces of equal size, in whole rounds of the symmetric kernels (a grid stays whole)
+        const int64_t pieces = c > cap ? (int64_t)std::ceil(c / cap) : 1;
+        const int64_t each = ((int64_t)(c / lanes) / pieces + 256) / 256 * 256;
+        if (pieces == 1 || (double)each * lanes >= c) {
+            cost.push_back({c, it});
+            continue;
+        }
+        Item piece = it;
+        piece.eb = (int32_t)entries.size();
+        int64_t have = 0;
+        auto close = [&] {
+            piece.ee = (int32_t)entries.size();
+            cost.push_back({(double)have * lanes, piece});
+            piece.eb = piece.ee;
+            have = 0;
+        };
+        for (int32_t e = it.eb; e < it.ee; ++e) {
+            const Entry en = entries[e];                   // by value: entries grows below
+            if ((uint32_t)en.b >> 29 == SRC_PROXY) {
+                entries.push_back(en);
+                have += entry_sources(en);
+                if (have >= each) close();
+                continue;
+            }
+            const uint32_t kind = (uint32_t)en.b & ~(uint32_t)kCountMask;
+            for (int64_t a = en.a, n = en.b & kCountMask; n > 0;) {
+                const int64_t m = std::min(n, each - have);
+                entries.push_back(Entry{(int32_t)a, (int32_t)(kind | (uint32_t)m)});
+                a += m;
+                n -= m;
+                have += m;
+                if (have >= each) close();
+            }
+        }
+        if (have > 0) close();
+    }
+    items.clear();
+    sort_items(cost, items);
 }
 
 namespace {

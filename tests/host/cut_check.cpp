@@ -272,9 +272,75 @@ void run_pc(int64_t n, int64_t leaf, int degree, double theta, ItemCut cut) {
                 degree, pc, cp);
 }
 
+// Symmetric items (pairs of particles, of proxies, and both kinds of PC/CP items)
+// cut by cost: every target and every source meets what it met before, no piece is
+// empty, and a piece costs at most the cap, rounded up to whole rounds and grids.
+void run_cut_symmetric(int64_t n, int64_t leaf, int degree, double theta, double cap) {
+    std::mt19937_64 rng(n * 17 + leaf);
+    std::normal_distribution<double> g(0.0, 0.25);
+    std::vector<double> x[3], s[3];
+    for (auto& v : x) {
+        v.resize(n);
+        for (double& a : v) a = g(rng);
+    }
+    Tree T;
+    build_tree(n, x[0].data(), x[1].data(), x[2].data(), leaf, T, s[0], s[1], s[2]);
+    Lists L, r;
+    traverse(T, T, theta, degree, kSchemeDtt, L);
+    SymWork w;
+    split_symmetric(T, L, degree, true, true, r, w, {}, false, true, 256, ItemCut{0, 1, true});
+    const int64_t P = cube3(degree);
+    struct Kind {
+        std::vector<Item>* items;
+        std::vector<Entry>* entries;
+        bool proxy_tgt, proxy_src;
+    };
+    for (const Kind& k : {Kind{&w.pp_items, &w.pp_entries, false, false}, Kind{&w.cc_items, &w.cc_entries, true, true},
+                          Kind{&w.pc_items, &w.pc_entries, false, true}, Kind{&w.cp_items, &w.cp_entries, true, false}}) {
+        auto sums = [&] {
+            std::vector<double> out[2];            // what particles and proxies meet
+            out[0].assign(n, 0.0);
+            out[1].assign(T.size() * P, 0.0);
+            for (const Item& it : *k.items) {
+                const int64_t t0 = k.proxy_tgt ? it.cluster * P + it.t0 : it.t0;
+                double tgt = 0.0, src = 0.0;
+                for (int64_t i = 0; i < it.tn; ++i) tgt += weight(t0 + i);
+                for (int32_t e = it.eb; e < it.ee; ++e) {
+                    const Entry& en = (*k.entries)[e];
+                    const int64_t c = k.proxy_src ? P : (en.b & kCountMask), a = k.proxy_src ? en.a * P : en.a;
+                    for (int64_t i = a; i < a + c; ++i) {
+                        src += weight(i);
+                        out[k.proxy_src][i] += tgt;
+                    }
+                }
+                for (int64_t i = 0; i < it.tn; ++i) out[k.proxy_tgt][t0 + i] += src;
+            }
+            return std::make_pair(out[0], out[1]);
+        };
+        const auto want = sums();
+        const size_t before = k.items->size();
+        size_t most = 0;
+        for (const Item& it : *k.items) most += (size_t)(item_cost(it, *k.entries) / cap) + 1;
+        cut_symmetric(*k.items, *k.entries, cap);
+        check(sums() == want, "sums of the pieces", k.proxy_tgt, k.proxy_src);
+        check(k.items->size() >= before && k.items->size() <= most, "pieces", (long long)k.items->size(), (long long)most);
+        for (const Item& it : *k.items) {
+            const double lanes = (it.tn + 63) / 64, c = item_cost(it, *k.entries);
+            check(it.ee > it.eb, "a piece holds sources");
+            check(c <= cap + lanes * (256 + (k.proxy_src ? P : 0)), "cost of a piece", (long long)c, (long long)cap);
+        }
+        std::printf("cut %d%d n %lld cap %g: %zu -> %zu items\n", k.proxy_tgt, k.proxy_src, (long long)n, cap, before,
+                    k.items->size());
+    }
+}
+
 }  // namespace
 
 int main() {
+    run_cut_symmetric(6000, 100, 5, 0.8, 3000.0);
+    run_cut_symmetric(9000, 300, 4, 0.9, 1.0);
+    run_cut_symmetric(20000, 70, 3, 0.8, 700.0);
+    run_cut_symmetric(30000, 1500, 6, 0.9, 1e9);
     run_pc(4000, 40, 3, 0.8, ItemCut{4096, 256});
     run_pc(6000, 100, 5, 0.8, ItemCut{2048, 256});
     run_pc(9000, 70, 6, 0.8, ItemCut{0, 1});

@@ -118,3 +118,21 @@ def test_host_batch_refuses_device_calls_and_bad_arguments():
     with pytest.raises(_lib.BldttError) as e:
         api.HostBatch([], theta=0.7)
     assert e.value.code == _lib.EINVAL
+
+
+@pytest.mark.parametrize("leaf", [300, 1000])
+def test_small_batches_are_not_cut_into_many_tasks(leaf):
+    # every task costs the queue: problems of a few thousand particles keep about
+    # the tasks of the one-way form's leaves and tiles (cut into 2048 pieces the
+    # second had 2.4 times as many)
+    rng = np.random.default_rng(6)
+    probs = []
+    for i, n in enumerate(np.exp(rng.uniform(np.log(1e3), np.log(5e3), 30)).astype(int)):
+        p = inputs.particles(int(n), ("uniform", "gaussian", "sphere")[i % 3], seed=i)
+        probs.append((None, (p.x, p.y, p.z, p.q)))
+    with api.HostBatch(probs, theta=0.7, degree=6, leaf=leaf) as b:
+        st, tree = b.stats(), b.tree()
+    with api.HostBatch(probs, theta=0.7, degree=6, leaf=leaf, flags=_lib.ONE_SIDED_PP) as one:
+        n1 = one.stats()["n_tasks"]
+    tiles = int(np.sum((tree["count"][tree["nchild"] == 0] + 255) // 256))     # symmetric items, uncut
+    assert st["n_tasks"] <= 1.15 * (n1 + tiles), (st["n_tasks"], n1, tiles)
