@@ -383,12 +383,13 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
     // particles 2.85 -> 1.7 ms; at 1E6 and more one item per tile is as good.
     const ItemCut sym_cut{16 * (int64_t)std::max(1, pl->cus), 256, true};
     // PC pairs listed with their mirror CP pair are evaluated once for both as
-    // well (FP64), while their source slots, a proxy grid per pair and tile, stay
+    // well (FP64), while their slots, above all a proxy grid per pair and tile, stay
     // below 4 GiB; beyond that (or where there are none) they stay one-way.  1E5
     // Gaussian particles, n 8, leaf 2000: 1.6 + 1.0 ms one-way, 0.6 ms both ways.
     auto pc_both_ways = [&](const Lists& L) {
         return !fp32 && !L.tc[PC].empty() && !L.tc[CP].empty() &&
-               pc_source_slots(T, L, pl->degree, sym_tile) <= (double)((int64_t)4 << 30) / sizeof(double);
+               pc_slots_bound(T, L, pl->degree, sym_tile, sym_cut.proxy_tiles) <=
+                   (double)((int64_t)4 << 30) / sizeof(double);
     };
     auto particle_pass = [&](const DevBuf& items, int n, const DevBuf& entries, bool add, hipStream_t s,
                              SymSlots cut = {}) {

@@ -314,8 +314,9 @@ struct SymWork {
 // The folds of a SymWork with PC/CP items: cc_fold holds the CC items, then the
 // proxy side of the PC/CP items; pc_fold their particle side.
 void build_pc_folds(const Tree& T, SymWork& sw);
-// At most how many slots the sources of the PC/CP items of L's pairs take.
-double pc_source_slots(const Tree& T, const Lists& L, int degree, int tile);
+// At most how many slots the PC/CP items of L's pairs take, sources and targets, in
+// both folds (split_symmetric with this tile, and with or without proxy tiles).
+double pc_slots_bound(const Tree& T, const Lists& L, int degree, int tile, bool proxy_tiles);
 // pp_ready, when given, is called as soon as the PP items and their slot bases
 // are complete (before `rest` and the CC items are formed), so their pass can
 // start early.  The PP fold's parts are left to the caller (fold_parts: the

@@ -805,6 +805,20 @@ int64_t chunk_sources(int64_t targets, double cap, int64_t min_src) {
     return (std::max((int64_t)by_cost, min_src) + 255) / 256 * 256;
 }
 
+// The share of its lanes' time that a tile's targets use: whole tiles of 256 at four
+// per lane, and a tail at two per lane (128 lanes' worth, a tenth slower) or one
+// (64, half as fast: a source read per pair).
+double lane_use(int64_t n) {
+    const int64_t tail = n % 256;
+    const double lanes = (double)(n - tail) + (tail == 0 ? 0.0 : (tail <= 64 ? 100.0 : (tail <= 128 ? 140.0 : 256.0)));
+    return (double)n / lanes;
+}
+
+// A PC/CP pair of a cluster of `count` particles is tiled over the proxy grid of
+// degree d (in tiles of kGridTile) where that fills the lanes better.
+constexpr int64_t kGridTile = 256;
+bool tiles_the_grid(int64_t count, int d) { return lane_use(count) < lane_use(cube(d)); }
+
 // The blocks' entries concatenated; their items sorted longest first, those
 // without guarded ranges ahead of those with (n_plain of them).
 void gather(std::vector<SymBlock>& blks, std::vector<Entry>& entries, std::vector<Item>& out, double& evals,
@@ -1051,17 +1065,7 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
         const double cap = cost_cap(L.tc[PC], L.sc[PC], [&](int64_t e, int64_t a, int64_t) {
             return (double)T.count[a] * (double)cube(L.deg[PC].empty() ? degree : (int)L.deg[PC][e]);
         });
-        // the share of its lanes' time that a tile's targets use: whole tiles of 256
-        // at four per lane, and a tail at two per lane (128 lanes' worth, a tenth
-        // slower) or one (64, half as fast: a source read per pair)
-        auto lane_use = [](int64_t n) {
-            const int64_t tail = n % 256;
-            const double lanes = (double)(n - tail) + (tail == 0 ? 0.0 : (tail <= 64 ? 100.0 : (tail <= 128 ? 140.0 : 256.0)));
-            return (double)n / lanes;
-        };
-        double grid_use[kMaxDegree + 1];
-        for (int d = 0; d <= kMaxDegree; ++d) grid_use[d] = cut.proxy_tiles ? lane_use(cube(d)) : 0.0;
-        auto by_proxies = [&](int64_t a, int d) { return lane_use(T.count[a]) < grid_use[d]; };
+        auto by_proxies = [&](int64_t a, int d) { return cut.proxy_tiles && tiles_the_grid(T.count[a], d); };
         // per (cluster A, degree d): the partners B whose PC and CP pairs with A
         // are both listed at d, as proxy entries; tiles of A's particles.  Then
         // per (cluster B, degree d) the partners A of the other pairs, as merged
@@ -1116,12 +1120,12 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
                     if (rp.empty()) continue;
                     const int64_t eb = (int64_t)C.entries.size(), np = cube(d);
                     emit_ranges(rp, none, C.entries);
-                    const int64_t chunk = chunk_sources(std::min<int64_t>(256, np), cap, std::max<int64_t>(1, cut.min_src));
+                    const int64_t chunk = chunk_sources(std::min(kGridTile, np), cap, std::max<int64_t>(1, cut.min_src));
                     if (src > chunk) chunk_ranges(C.entries, eb, chunk, first);
                     else first = {(int32_t)eb, (int32_t)C.entries.size()};
                     C.evals += 2.0 * (double)np * (double)src;
-                    for (int64_t lb = 0; lb < np; lb += 256) {
-                        const int64_t ln = std::min<int64_t>(256, np - lb);
+                    for (int64_t lb = 0; lb < np; lb += kGridTile) {
+                        const int64_t ln = std::min(kGridTile, np - lb);
                         for (size_t c = 0; c + 1 < first.size(); ++c)
                             C.items.push_back({(double)ln * (double)std::min(chunk, src - (int64_t)c * chunk),
                                                Item{(int32_t)lb, (int32_t)ln, first[c], first[c + 1], (int32_t)b,
@@ -1309,12 +1313,23 @@ void build_pc_folds(const Tree& T, SymWork& sw) {
     sw.cp_tbase = std::move(cb[2]);
 }
 
-double pc_source_slots(const Tree& T, const Lists& L, int degree, int tile) {
+double pc_slots_bound(const Tree& T, const Lists& L, int degree, int tile, bool proxy_tiles) {
+    // pairs tiled over the grid: their particles per (grid, degree), whose chunks of at
+    // least 256 each take the grid's target slots
+    std::vector<int64_t> by_grid(proxy_tiles ? T.size() * (kMaxDegree + 1) : 0, 0);
     double n = 0.0;
     for (size_t e = 0; e < L.tc[PC].size(); ++e) {
-        const double P = (double)cube(L.deg[PC].empty() ? degree : (int)L.deg[PC][e]);
-        n += P * (double)((T.count[L.tc[PC][e]] + tile - 1) / tile);
+        const int d = L.deg[PC].empty() ? degree : (int)L.deg[PC][e];
+        const int64_t P = cube(d), c = T.count[L.tc[PC][e]];
+        if (proxy_tiles && tiles_the_grid(c, d)) {
+            n += (double)(c * ((P + kGridTile - 1) / kGridTile));
+            by_grid[L.sc[PC][e] * (kMaxDegree + 1) + d] += c;
+        } else {
+            n += (double)(P * ((c + tile - 1) / tile) + c);
+        }
     }
+    for (size_t k = 0; k < by_grid.size(); ++k)
+        n += (double)(cube((int)(k % (kMaxDegree + 1))) * ((by_grid[k] + 255) / 256));
     return n;
 }
 

@@ -334,9 +334,43 @@ void run_cut_symmetric(int64_t n, int64_t leaf, int degree, double theta, double
     }
 }
 
+// pc_slots_bound covers what the PC/CP items take, for every tile.
+void run_pc_bound(int64_t n, int64_t leaf, int degree, double theta, ItemCut cut) {
+    std::mt19937_64 rng(n * 19 + leaf);
+    std::normal_distribution<double> g(0.0, 0.25);
+    std::vector<double> x[3], s[3];
+    for (auto& v : x) {
+        v.resize(n);
+        for (double& a : v) a = g(rng);
+    }
+    Tree T;
+    build_tree(n, x[0].data(), x[1].data(), x[2].data(), leaf, T, s[0], s[1], s[2]);
+    Lists L;
+    traverse(T, T, theta, degree, kSchemeDtt, L);
+    for (bool proxy_tiles : {false, true})
+        for (int tile : {256, 512, 1024}) {
+            Lists r;
+            SymWork w;
+            cut.proxy_tiles = proxy_tiles;
+            split_symmetric(T, L, degree, true, true, r, w, {}, false, true, tile, cut);
+            build_pc_folds(T, w);
+            std::vector<std::vector<int64_t>> b;
+            const int64_t cc = fold_group_bases({{&w.cc_items, &w.cc_entries, FoldGroup::kProxyBoth}}, b);
+            const double took = (double)(w.pc_fold.nslots + w.cc_fold.nslots - cc);
+            const double bound = pc_slots_bound(T, L, degree, tile, proxy_tiles);
+            check(took > 0 && took <= bound, "slots within the bound", (long long)took, (long long)bound);
+            std::printf("PC/CP n %lld degree %d tile %d grids %d: %.0f slots, bound %.0f\n", (long long)n, degree, tile,
+                        proxy_tiles, took, bound);
+        }
+}
+
 }  // namespace
 
 int main() {
+    run_pc_bound(30000, 300, 6, 0.8, ItemCut{4096, 256});
+    run_pc_bound(40000, 700, 8, 0.9, ItemCut{4096, 256});
+    run_pc_bound(60000, 1500, 12, 0.9, ItemCut{100, 256});
+    run_pc_bound(9000, 70, 5, 0.8, ItemCut{1000000, 1});
     run_cut_symmetric(6000, 100, 5, 0.8, 3000.0);
     run_cut_symmetric(9000, 300, 4, 0.9, 1.0);
     run_cut_symmetric(20000, 70, 3, 0.8, 700.0);
