@@ -197,8 +197,10 @@ const char *bldtt_last_error(void);
  * synchronization (as hipFree implies), so the callbacks and ctx must stay
  * valid until the plans and batches using them are destroyed.  Pinned host
  * staging memory is not affected.  A NULL from alloc makes the calling entry
- * point fail with BLDTT_ENOMEM, every buffer it allocated released; memory not
- * aligned to 256 bytes makes it fail with BLDTT_EINVAL.
+ * point fail with BLDTT_ENOMEM, every buffer it allocated released, unless the
+ * memory was for sums kept apart to save time only: then a plan or batch goes on
+ * without, for the rest of its life; memory not aligned to 256 bytes makes the
+ * call fail with BLDTT_EINVAL.
  * Errors: EINVAL when exactly one callback is NULL. */
 int bldtt_set_allocator(void *(*alloc)(size_t bytes, void *ctx), void (*release)(void *ptr, void *ctx), void *ctx);
 

@@ -68,6 +68,7 @@ struct bldtt_batch {
     int tpt = 2, groups_per_cu = 0, grid = 0, spin_limit = 1 << 22;
     int cus = 256;                           // of the MI355X; device batches read their device's
     bool packed_tpt_valid = false;
+    bool lean = false;                       // symmetric tasks uncut, PC/CP pairs over particle tiles only: fewer slots
     int packed_tpt = 0;
 
     int P() const { return (degree + 1) * (degree + 1) * (degree + 1); }
@@ -345,26 +346,24 @@ void cut_long_tasks(bldtt_batch* b) {
 }
 
 // Work items for tile size tpt, their flags and the per-cluster counts.
-void pack(bldtt_batch* b, int tpt) {
-    if (b->packed_tpt_valid && b->packed_tpt == tpt) return;
+void pack_items(bldtt_batch* b, int tpt) {
     Work& w = b->work;
     w.guard_near = (b->flags & BLDTT_FP32_EVAL) != 0;   // FP32 batches guard near particle ranges too
     if (b->symmetric()) {
-        split_symmetric(b->T(), b->lists, b->degree, true, true, b->rest, b->sym, {}, false, true, 256, ItemCut{0, 1, true});
+        split_symmetric(b->T(), b->lists, b->degree, true, true, b->rest, b->sym, {}, false, true, 256,
+                        ItemCut{0, 1, !b->lean});
         const std::vector<uint32_t> extra = sym_cc_degrees(b->T(), b->sym);
         pack_work(b->T(), b->S, b->rest, b->degree, kThreads * tpt, kThreads * tpt, w, &extra);
     } else {
         b->sym.clear();
         pack_work(b->T(), b->S, b->lists, b->degree, kThreads * tpt, kThreads * tpt, w);
     }
-    if (b->symmetric()) cut_long_tasks(b);
+    if (b->symmetric() && !b->lean) cut_long_tasks(b);
     for (int k = 0; k < 4; ++k) b->stats.interactions[k] = w.interactions[k];
     b->stats.interactions[PP] += b->sym.pp_evaluations;
     b->stats.interactions[CC] += b->sym.cc_evaluations;
     b->stats.interactions[PC] += 0.5 * b->sym.pc_evaluations;     // each value serves one PC and one CP term
     b->stats.interactions[CP] += 0.5 * b->sym.pc_evaluations;
-    b->packed_tpt = tpt;
-    b->packed_tpt_valid = true;
     b->stats.n_tasks = count_tasks(b);
     if (b->host_only) return;
     auto needs = [](const std::vector<Item>& items, const std::vector<Entry>& entries) {
@@ -414,6 +413,25 @@ void pack(bldtt_batch* b, int tpt) {
     if (b->symmetric()) upload_folds(b);
     b->n_counters = kGlobalCounters + b->S.size() + b->T().size() + (int64_t)w.pitems.size() + b->count;
     b->counters.alloc(sizeof(int32_t) * b->n_counters);
+}
+
+// The same once per tile size; where the device memory for slots cannot be had,
+// again with tasks that take fewer.
+void pack(bldtt_batch* b, int tpt) {
+    if (b->packed_tpt_valid && b->packed_tpt == tpt) return;
+    b->packed_tpt_valid = false;
+    try {
+        pack_items(b, tpt);
+    } catch (const Error& e) {
+        if (e.code != BLDTT_ENOMEM || !b->symmetric() || b->lean) throw;
+        (void)hipGetLastError();             // a failed hipMalloc is not a failed launch
+        b->lean = true;
+        b->sslots.release();
+        b->cslots.release();
+        pack_items(b, tpt);
+    }
+    b->packed_tpt = tpt;
+    b->packed_tpt_valid = true;
 }
 
 BatchDev device_args(const bldtt_batch* b) {

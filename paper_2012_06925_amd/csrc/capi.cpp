@@ -306,14 +306,14 @@ void ensure_self_work(bldtt_plan* pl, SetupUpload& up) {
     std::vector<Item> sym;
     sym.reserve(si.size());
     for (auto& x : si) sym.push_back(x.second);
-    up.add(pl->self_items, di);
-    up.add(pl->self_entries, de);
-    up.add(pl->self_sym_items, sym);
-    up.add(pl->self_sym_entries, se);
     SymFold fold;
     build_fold(T, sym, se, false, fold);
     DevFold& f = pl->fold_self;
     f.slots.alloc(sizeof(double) * (size_t)std::max<int64_t>(fold.nslots, 1));
+    up.add(pl->self_items, di);
+    up.add(pl->self_entries, de);
+    up.add(pl->self_sym_items, sym);
+    up.add(pl->self_sym_entries, se);
     up.add(f.ibase, fold.ibase);
     up.add(f.segs, fold.segs);
     up.add(f.parts, fold.parts);
@@ -341,7 +341,7 @@ void drop_self_pairs(Lists& L) {
     if (!dg.empty()) dg.resize(o);
 }
 
-void compute(bldtt_plan* pl, double* out, hipStream_t st) {
+void compute_once(bldtt_plan* pl, double* out, hipStream_t st) {
     const Tree& T = pl->T();
     const Tree& S = pl->S;
     const DevTree dS = pl->dS.view(), dT = pl->dT().view();
@@ -381,13 +381,13 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
     // tiles and many partners, and one item per tile left the GPU idle: the pass of
     // 1E4 particles (leaf 500) 345 us with 62 items, 37 us with 1023; 1E5 Gaussian
     // particles 2.85 -> 1.7 ms; at 1E6 and more one item per tile is as good.
-    const ItemCut sym_cut{16 * (int64_t)std::max(1, pl->cus), 256, true};
+    const ItemCut sym_cut = pl->lean ? ItemCut{} : ItemCut{16 * (int64_t)std::max(1, pl->cus), 256, true};
     // PC pairs listed with their mirror CP pair are evaluated once for both as
     // well (FP64), while their slots, above all a proxy grid per pair and tile, stay
     // below 4 GiB; beyond that (or where there are none) they stay one-way.  1E5
     // Gaussian particles, n 8, leaf 2000: 1.6 + 1.0 ms one-way, 0.6 ms both ways.
     auto pc_both_ways = [&](const Lists& L) {
-        return !fp32 && !L.tc[PC].empty() && !L.tc[CP].empty() &&
+        return !fp32 && !pl->lean && !L.tc[PC].empty() && !L.tc[CP].empty() &&
                pc_slots_bound(T, L, pl->degree, sym_tile, sym_cut.proxy_tiles) <=
                    (double)((int64_t)4 << 30) / sizeof(double);
     };
@@ -755,6 +755,30 @@ void compute(bldtt_plan* pl, double* out, hipStream_t st) {
     mark_host(3);
 }
 
+// Whether an allocation failed that the plan can do without (bldtt_plan::lean); if
+// so its slots are given back, with nothing left on the streams that may use them.
+bool go_lean(bldtt_plan* pl, const Error& e, hipStream_t st) {
+    if (e.code != BLDTT_ENOMEM || pl->lean) return false;
+    (void)hipGetLastError();                 // a failed hipMalloc is not a failed launch
+    HIPCHK(hipStreamSynchronize(st));
+    if (pl->side) HIPCHK(hipStreamSynchronize(pl->side));
+    pl->lean = true;
+    for (DevFold* f : {&pl->fold_pp, &pl->fold_cc, &pl->fold_pc, &pl->fold_cut_near, &pl->fold_cut_part, &pl->fold_cut_prox})
+        f->slots.release();
+    if (!pl->symmetric_pp()) pl->fold_self.slots.release();
+    return true;
+}
+
+// One summation; where the device memory for slots cannot be had, again without.
+void compute(bldtt_plan* pl, double* out, hipStream_t st) {
+    try {
+        compute_once(pl, out, st);
+    } catch (const Error& e) {
+        if (!go_lean(pl, e, st)) throw;
+        compute_once(pl, out, st);
+    }
+}
+
 // Trees built on the host: the particles copied down, the trees built, the
 // permuted particles copied up.
 void setup_host_tree(bldtt_plan* pl, const bldtt_particles* p, hipStream_t st, SetupUpload& up) {
@@ -867,7 +891,13 @@ void setup_device(bldtt_plan* pl, const bldtt_particles* p, hipStream_t st) {
         for (auto& set : pl->prof_ev)
             for (auto& e : set) HIPCHK(hipEventCreate(&e));
     HIPCHK(hipEventRecord(pl->staging_free, st));
-    if (pl->symmetric_pp()) ensure_self_work(pl, up);
+    if (pl->symmetric_pp()) {
+        try {
+            ensure_self_work(pl, up);
+        } catch (const Error& e) {
+            if (pl->kind == BLDTT_COULOMB || !go_lean(pl, e, st)) throw;
+        }
+    }
     up.flush(pl->arena_setup);
     if (pl->device_walk()) walk_upload(pl->walk, T, pl->S, pl->aliased);
     fill_stats_tree(pl);

@@ -336,7 +336,7 @@ struct bldtt_plan {
     bool symmetric_pp() const {
         if (!aliased || (flags & BLDTT_ONE_SIDED_PP) != 0) return false;
         if (kind == BLDTT_COULOMB) return true;
-        return kind != BLDTT_POLY_TEST && (flags & BLDTT_FP32_EVAL) == 0 && padding_safe();
+        return !lean && kind != BLDTT_POLY_TEST && (flags & BLDTT_FP32_EVAL) == 0 && padding_safe();
     }
     bool padding_safe() const {
         for (int d = 0; d < 3; ++d)
@@ -345,6 +345,10 @@ struct bldtt_plan {
         return kind != BLDTT_REGCOULOMB || std::fabs(param) < 1e100;
     }
 
+    // Set when device memory for slots could not be had: from then on the plan makes
+    // do without cut items, PC/CP pairs both ways and the symmetric passes of
+    // kernels other than Coulomb, which save time only.
+    bool lean = false;
     int tpt = 2, tpt_proxy = 2;              // targets per thread in the interaction kernels
     int cus = 256;                           // compute units of the plan's device (set at setup)
     uint32_t up_degrees_last = 0;            // source degrees of the last per-pair degree compute

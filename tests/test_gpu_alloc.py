@@ -127,3 +127,75 @@ def test_failing_allocator_during_compute_and_batch_setup():
         assert not cnt2.live and cnt2.n_release == cnt2.n_alloc == 12
     finally:
         api.use_torch_allocator()
+
+
+class RefuseOne(Counting):
+    """Refuses one allocation only, the k-th."""
+
+    def __init__(self, k):
+        super().__init__()
+        self.k = k
+
+    def alloc(self, n):
+        if self.n_alloc == self.k and self.n_refused == 0:
+            self.n_refused = 1
+            return 0
+        return super().alloc(n)
+
+
+@pytest.mark.parametrize("form", ["coulomb", "yukawa", "treecode", "tuned", "batch"])
+def test_memory_that_only_saves_time_is_not_needed(form):
+    # every allocation of a setup and a compute refused in turn: the call fails with
+    # ENOMEM and releases all, or the plan goes on without and the results are right;
+    # slots (yukawa: of the self pairs, at setup, and of the passes) are of that kind
+    api = _api()
+    from paper_2012_06925_amd import _lib, train_degree_model
+    kw = dict(theta=0.8, degree=4, leaf=60)
+    p, src = _src(4000, 94)
+    tgt = None
+    if form == "yukawa":
+        kw["kernel"] = "yukawa"
+    if form == "treecode":
+        t = inputs.particles(300, "gaussian", seed=95, charges=False)
+        tgt = [torch.from_numpy(a).cuda() for a in (t.x, t.y, t.z)]
+        kw["flags"] = _lib.BLTC
+    if form == "tuned":
+        kw["flags"] = _lib.FP32_EVAL | _lib.LEARNED_DEGREE
+
+    def run():
+        if form == "batch":
+            b = api.Batch([(None, src)], **kw)
+            try:
+                return b.compute()[0].cpu().numpy()
+            finally:
+                b.close()
+        plan = api.Plan(tgt, src, **kw)
+        try:
+            if form == "tuned":
+                plan.set_degree_model(train_degree_model.load_model(), fallback=4)
+            a = plan.compute().cpu().numpy()
+            assert (plan.compute().cpu().numpy() == a).all()
+            return a
+        finally:
+            plan.close()
+
+    probe = Counting()
+    api.set_allocator(probe.alloc, probe.release)
+    try:
+        ref = run()
+        assert probe.n_alloc > 10 and not probe.live
+        went_on = 0
+        for k in range(probe.n_alloc):
+            one = RefuseOne(k)
+            api.set_allocator(one.alloc, one.release)
+            try:
+                got = run()
+            except _lib.BldttError as e:
+                assert e.code == _lib.ENOMEM, (k, e)
+            else:
+                went_on += one.n_refused
+                assert core.rel_l2(got, ref) < (1e-6 if form == "tuned" else 1e-12), k
+            assert not one.live and one.n_release == one.n_alloc, k
+    finally:
+        api.use_torch_allocator()
+    assert went_on >= {"yukawa": 3, "batch": 2}.get(form, 1), went_on
