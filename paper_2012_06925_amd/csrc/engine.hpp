@@ -334,6 +334,10 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
                      const std::function<void()>& pp_ready = {}, bool separate_guarded = false, bool pc = false,
                      int tile = 256, const ItemCut& cut = {});
 
+// Bytes that the walk and the packing keep for this calling thread after their
+// calls (bounded: a large problem's are given back).
+size_t kept_host_bytes();
+
 // Per-cluster degree masks of the proxy potentials the symmetric passes add
 // to: both clusters of each CC pair, the proxy side of each PC/CP pair.
 std::vector<uint32_t> sym_cc_degrees(const Tree& T, const SymWork& sw);

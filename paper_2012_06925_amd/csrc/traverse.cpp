@@ -155,6 +155,28 @@ int64_t append_tree(Tree& f, const Tree& t, int64_t pos0, int64_t caller0) {
     return c0;
 }
 
+namespace {
+
+// What a calling thread keeps between computes, so that a plan repacked every
+// compute touches no fresh pages: at most kKeptBytes each for the walk's lists and
+// for the packing's (1E7 particles in the cube: 24 and 26 MB).
+constexpr size_t kKeptBytes = (size_t)128 << 20;
+thread_local std::vector<Lists> kept_walk;
+
+template <class V>
+size_t held(const V& v) { return v.capacity() * sizeof(v[0]); }
+
+size_t walk_bytes() {
+    size_t n = held(kept_walk);
+    for (const Lists& p : kept_walk) {
+        for (int k = 0; k < 4; ++k) n += held(p.tc[k]) + held(p.sc[k]) + held(p.deg[k]);
+        n += held(p.sep_tc) + held(p.sep_sc);
+    }
+    return n;
+}
+
+}  // namespace
+
 void traverse_roots(const Tree& T, const Tree& S, const std::vector<std::pair<int64_t, int64_t>>& roots,
                     double theta, int degree, int scheme, Lists& out, bool defer_separated) {
     Ctx x{T, S, theta, degree, scheme, defer_separated};
@@ -176,8 +198,7 @@ void traverse_roots(const Tree& T, const Tree& S, const std::vector<std::pair<in
         cur.swap(nxt);
     }
     const int64_t runs = small ? 1 : std::min<int64_t>((int64_t)cur.size(), (int64_t)8 * num_threads());
-    static thread_local std::vector<Lists> tl_part;
-    std::vector<Lists>& part = tl_part;
+    std::vector<Lists>& part = kept_walk;
     if ((int64_t)part.size() < runs) part.resize(runs);
     parallel_run(runs, [&](int64_t r) {
         part[r].clear();
@@ -209,9 +230,7 @@ void traverse_roots(const Tree& T, const Tree& S, const std::vector<std::pair<in
         std::copy(p.sep_tc.begin(), p.sep_tc.end(), out.sep_tc.begin() + at[r][4]);
         std::copy(p.sep_sc.begin(), p.sep_sc.end(), out.sep_sc.begin() + at[r][4]);
     });
-    // a large problem's lists are not kept beside the plan's own
-    for (int64_t r = 0; r < runs; ++r)
-        if (at[runs][0] + at[runs][3] + at[runs][4] > ((size_t)1 << 22)) part[r] = Lists();
+    if (walk_bytes() > kKeptBytes) std::vector<Lists>().swap(part);      // a large problem's lists are not kept
 }
 
 namespace {
@@ -819,11 +838,30 @@ double lane_use(int64_t n) {
 constexpr int64_t kGridTile = 256;
 bool tiles_the_grid(int64_t count, int d) { return lane_use(count) < lane_use(cube(d)); }
 
+// What split_symmetric keeps per calling thread (see kKeptBytes).
+struct KeptPack {
+    PairIndex ipp, icc, ipc, icp;
+    std::vector<uint8_t> keep[4];
+    std::vector<SymBlock> blks[2];
+    std::vector<std::pair<double, Item>> items, gitems;
+    size_t bytes() const {
+        size_t n = held(items) + held(gitems);
+        for (const PairIndex* x : {&ipp, &icc, &ipc, &icp}) n += held(x->off) + held(x->cnt) + held(x->part) + held(x->both);
+        for (const auto& k : keep) n += held(k);
+        for (const auto& v : blks) {
+            n += held(v);
+            for (const SymBlock& b : v) n += held(b.entries) + held(b.items) + held(b.gitems);
+        }
+        return n;
+    }
+};
+thread_local KeptPack kept_pack;
+
 // The blocks' entries concatenated; their items sorted longest first, those
 // without guarded ranges ahead of those with (n_plain of them).
 void gather(std::vector<SymBlock>& blks, std::vector<Entry>& entries, std::vector<Item>& out, double& evals,
             int64_t* n_plain = nullptr) {
-    static thread_local std::vector<std::pair<double, Item>> items, gitems;   // kept: no fresh pages per call
+    auto &items = kept_pack.items, &gitems = kept_pack.gitems;
     items.clear();
     gitems.clear();
     for (auto& B : blks) {
@@ -864,12 +902,14 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
     const int64_t kBlk = listed < 4096 ? std::max<int64_t>(1, nc) : 32;
     const int64_t kTile = tile;
     const int64_t nblk = (nc + kBlk - 1) / kBlk;
-    // kept per calling thread, so a plan repacked every compute touches no fresh
-    // pages; the workers reach the caller's copies through these references
-    static thread_local PairIndex tl_ipp, tl_icc, tl_ipc, tl_icp;
-    static thread_local std::vector<uint8_t> tl_keep[4];
-    PairIndex &ipp = tl_ipp, &icc = tl_icc, &ipc = tl_ipc, &icp = tl_icp;
-    std::vector<uint8_t>* keep = tl_keep;        // per entry: not one of a pair evaluated once for both
+    // the workers reach the caller's copies through these references
+    PairIndex &ipp = kept_pack.ipp, &icc = kept_pack.icc, &ipc = kept_pack.ipc, &icp = kept_pack.icp;
+    std::vector<uint8_t>* keep = kept_pack.keep; // per entry: not one of a pair evaluated once for both
+    struct Trim {
+        ~Trim() {
+            if (kept_pack.bytes() > kKeptBytes) kept_pack = KeptPack();
+        }
+    } trim;
     for (int k = 0; k < 4; ++k) keep[k].assign(L.tc[k].size(), 1);
     const std::vector<int8_t> no_degrees;        // PP pairs are matched without their degree
     if (pp) {
@@ -879,8 +919,7 @@ void split_symmetric(const Tree& T, const Lists& L, int degree, bool pp, bool cc
     }
     // the indexes of CC, PC and CP pairs are formed after pp_ready, below
     // the blocks of one list type at a time, kept like the indexes
-    static thread_local std::vector<SymBlock> tl_blks[2];
-    std::vector<SymBlock>* all_blks = tl_blks;
+    std::vector<SymBlock>* all_blks = kept_pack.blks;
     auto blocks = [&](int which = 0) -> std::vector<SymBlock>& {
         std::vector<SymBlock>& v = all_blks[which];
         if ((int64_t)v.size() > 4 * nblk + 1024) v.clear();      // a much larger problem's
@@ -1332,6 +1371,8 @@ double pc_slots_bound(const Tree& T, const Lists& L, int degree, int tile, bool 
         n += (double)(cube((int)(k % (kMaxDegree + 1))) * ((by_grid[k] + 255) / 256));
     return n;
 }
+
+size_t kept_host_bytes() { return walk_bytes() + kept_pack.bytes(); }
 
 void fold_bases(const std::vector<Item>& items, const std::vector<Entry>& entries, bool proxies, SymFold& f) {
     f.clear();

@@ -364,9 +364,47 @@ void run_pc_bound(int64_t n, int64_t leaf, int degree, double theta, ItemCut cut
         }
 }
 
+// A large problem's lists do not stay with the thread, whatever their types (a
+// particle-cluster treecode lists PC pairs, a cluster-particle one CP pairs); a
+// small one's do.
+void run_kept(int scheme, int64_t m, int64_t n, int64_t leaf, double theta, bool symmetric) {
+    std::mt19937_64 rng(11);
+    std::uniform_real_distribution<double> u(-1.0, 1.0);
+    std::vector<double> x[3], y[3], sx[3], sy[3];
+    for (int d = 0; d < 3; ++d) {
+        x[d].resize(m);
+        y[d].resize(n);
+        for (double& a : x[d]) a = u(rng);
+        for (double& a : y[d]) a = u(rng);
+    }
+    Tree T, S;
+    build_tree(m, x[0].data(), x[1].data(), x[2].data(), leaf, T, sx[0], sx[1], sx[2]);
+    build_tree(n, y[0].data(), y[1].data(), y[2].data(), leaf, S, sy[0], sy[1], sy[2]);
+    Lists L;
+    size_t listed = 0;
+    if (symmetric) {
+        Lists r;
+        SymWork w;
+        traverse(T, T, theta, 1, scheme, L);
+        split_symmetric(T, L, 1, true, true, r, w, {}, false, true, 256, ItemCut{4096, 256, true});
+    } else {
+        traverse(T, S, theta, 1, scheme, L);
+    }
+    for (int k = 0; k < 4; ++k) listed += L.tc[k].size();
+    const size_t kept = kept_host_bytes();
+    check(kept <= (size_t)256 << 20, "kept lists are bounded", (long long)kept, (long long)listed);
+    check(listed < 100000 || listed > 8000000, "sizes of the check", (long long)listed);
+    check(listed > 8000000 ? kept < 17 * listed / 2 : kept > 0, "a large problem's lists are given back", (long long)kept, (long long)listed);
+    std::printf("kept: %zu pairs listed, %zu bytes\n", listed, kept);
+}
+
 }  // namespace
 
 int main() {
+    run_kept(kSchemeDtt, 2000, 2000, 100, 0.8, true);
+    run_kept(kSchemeBltc, 100000, 100000, 4, 0.6, false);
+    run_kept(kSchemeCpBltc, 100000, 100000, 4, 0.6, false);
+    run_kept(kSchemeDtt, 60000, 10, 4, 0.4, true);
     run_pc_bound(30000, 300, 6, 0.8, ItemCut{4096, 256});
     run_pc_bound(40000, 700, 8, 0.9, ItemCut{4096, 256});
     run_pc_bound(60000, 1500, 12, 0.9, ItemCut{100, 256});
