@@ -143,8 +143,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 
     // the symmetric PP items right after the upward pass: they need nothing
     // before them, and keep the SIMDs busy while the upward pass completes
-    constexpr bool SYM = !F32 && KIND == K_COULOMB;      // (other kinds keep no registers for those ranges)
-    const int n_s = SYM ? a.n_s : 0, n_c = SYM ? a.n_c : 0, n_m = SYM ? a.n_m : 0, n_r = SYM ? a.n_r : 0;
+    constexpr bool SYM = !F32 && KIND == K_COULOMB;
+    // Other kinds keep no registers for those (empty) ranges, but for FP32 Yukawa:
+    // there the compiler then runs the pair loop's two targets one after the other
+    // (degree 6: 146 instructions with 12 waits instead of 134; 8 problems of
+    // 1E3..5E3, leaf 1000, 645 instead of 600 us).
+    constexpr bool RANGES = SYM || (F32 && KIND == K_YUKAWA);
+    const int n_s = RANGES ? a.n_s : 0, n_c = RANGES ? a.n_c : 0, n_m = RANGES ? a.n_m : 0, n_r = RANGES ? a.n_r : 0;
     const int e0 = a.n_leaves, e1 = e0 + a.n_parents, ev = e1 + n_s, eq = ev + a.n_q, e2 = eq + n_c,
               er = e2 + n_m, em = er + n_r, e3 = em + a.n_p, e4 = e3 + a.n_kids;
     const int n_up = e1;
@@ -271,7 +276,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             // potentials (the same thread later adds the transfer to each
             // output it folded)
             down_transfer_stage<M>(c, a.T, a.tab, a.phihat, dl);
-            if (SYM && a.cslots && a.cseg[c] >= 0) {
+            if (RANGES && a.cslots && a.cseg[c] >= 0) {
                 const FoldSeg sg = a.csegs[a.cseg[c]];
                 fold_body(sg, a.cparts, a.cslots, a.phihat + sg.off, 0, sg.n,
                           reinterpret_cast<FoldPart*>(reinterpret_cast<char*>(pool) + kXferFold));
@@ -286,7 +291,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             const int prob = a.prob[c];
             if (n_s + n_m + n_r > 0) wait2(a, a.sdone + prob, a.s_need[prob], nullptr, 0);
             wait2(a, a.pdone + i, 1, a.dn + c, a.nq[c] + (a.T.parent[c] >= 0 ? 1 : 0));
-            if (SYM && a.sslots && a.pseg[i] >= 0) {
+            if (RANGES && a.sslots && a.pseg[i] >= 0) {
                 const FoldSeg sg = a.psegs[a.pseg[i]];
                 const int k0 = it.t0 - (int)sg.off;
                 fold_body(sg, a.pparts, a.sslots, a.phi_tree + sg.off, k0, k0 + it.tn,
