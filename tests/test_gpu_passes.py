@@ -198,3 +198,36 @@ def test_direct_sum_for_few_and_many_sources(n, nsel):
     ref = core.direct_sum(t, s)
     s.q = np.abs(s.q)
     assert np.all(np.abs(got - ref) <= 1e-14 * core.direct_sum(t, s))
+
+
+@pytest.mark.parametrize("kernel", ["coulomb", "yukawa"])
+def test_mirrored_pc_cp_pairs_in_tiles_of_several_slabs(kernel):
+    # more than 8192 leaves: particle tiles of whole leaves of up to 600, in two and
+    # four slabs of the work group, against grids of 1000 and the other way round
+    p = inputs.particles(5_000_000, "gaussian", seed=96)
+    kw = dict(kernel=kernel, theta=0.8, degree=9, leaf=600)
+    phi = []
+    for flags in (0, _lib.ONE_SIDED_PP):
+        plan = _plan(p, flags=flags | _lib.DEVICE_TREE, **kw)
+        phi += _computes(plan, 2 - (flags != 0))
+        n, st = plan.tree()["count"], plan.stats()
+        lists = plan.lists()["PC"]
+        plan.close()
+    assert np.array_equal(phi[0], phi[1])
+    assert st["n_entries"]["PC"] > 0 and np.any(n[lists[0]] > 256)
+    _close(phi[0], phi[2])
+
+
+def test_particles_beyond_the_padding_against_the_oracle():
+    # 2E17 away, where coordinates are 32 apart: proxy points of boxes of 1E15 round to
+    # 3e-14 of their size, which 3000 charges of both signs may bring to 1e-12 and more
+    p = inputs.particles(3000, "uniform", seed=72)
+    for a in (p.x, p.y, p.z):
+        a *= 1e16
+        a += 2e17
+    kw = dict(kernel="regcoulomb", param=0.01, theta=0.7, degree=3, leaf=100)
+    plan = _plan(p, **kw)
+    got = _computes(plan, 1)[0]
+    plan.close()
+    ref = core.bldtt(p, p, **kw)
+    assert core.rel_l2(got, ref) < 1e-10 and core.max_rel(got, ref) < 1e-10
