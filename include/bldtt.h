@@ -421,9 +421,10 @@ int bldtt_autotune(bldtt_plan *plan, double *scratch, int32_t reps, void *hip_st
  * kernel (work groups take tasks from a counter; dependencies are device
  * counters with bounded waits) captured once in a hipGraph.  The per-problem
  * results equal those of bldtt_setup + bldtt_compute with the same arguments
- * (the same sums; the order of their terms may differ).  Supported: Coulomb and Yukawa (FP64 or
- * BLDTT_FP32_EVAL), POLY_TEST (FP64); degree 1..10; a fixed degree (no
- * BLDTT_LEARNED_DEGREE).
+ * to rounding (the order of the terms differs, and FP64 Yukawa values come from
+ * the library's exponential here, from the passes' own in a plan).  Supported:
+ * Coulomb and Yukawa (FP64 or BLDTT_FP32_EVAL), POLY_TEST (FP64); degree 1..10;
+ * a fixed degree (no BLDTT_LEARNED_DEGREE).
  * ------------------------------------------------------------------------ */
 typedef struct bldtt_batch bldtt_batch;
 

@@ -403,9 +403,9 @@ void compute_once(bldtt_plan* pl, double* out, hipStream_t st) {
     };
     // The one-way items of small problems, and of few clusters with long lists,
     // are cut like the symmetric ones: `cut` holds the pieces (empty: nothing to
-    // cut), and the pass is followed by the fold of its pieces.  1E5 Gaussian
-    // targets, 2E6 Yukawa sources on a sphere: 70 -> 61 ms; treecodes of a few
-    // thousand targets, one item of few waves before, 2 to 14 times as fast.
+    // cut), and the pass is followed by the fold of its pieces.  2E6
+    // targets on a sphere, 1E7 Gaussian Yukawa sources: 70 -> 61 ms; treecodes of a
+    // few thousand targets, one item of few waves before, 2 to 14 times as fast.
     auto particle_pass_cut = [&](const DevBuf& items, int n, const DevBuf& entries, bool add, hipStream_t s,
                                  const CutItems& cut, const DevBuf& cut_items, const DevFold& f) {
         if (cut.items.empty()) {

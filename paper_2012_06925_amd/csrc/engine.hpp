@@ -47,7 +47,7 @@ struct Tree {
 };
 
 // Setups of up to this many particles keep their host work arrays per calling
-// thread (at most 14 arrays of 2 MiB).
+// thread (at most 18 arrays of 2 MiB: 14 of the setup, 4 of the tree build).
 constexpr int64_t kHostScratch = 1 << 18;
 
 // Build the tree of n particles (caller order x, y, z) with at most `leaf`

@@ -226,7 +226,7 @@ __global__ __launch_bounds__(kBlock) void k_sym_fold64(const FoldSeg* __restrict
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const bool real = q0 + u < sg.pe;
-                const FoldPart pt = parts[real ? q0 + u : q0];   // uniform: scalar loads
+                const FoldPart pt = parts[real ? q0 + u : q0];   // one address for the whole wave
                 const unsigned d = (unsigned)(k - pt.lo);
                 in[u] = real && d < (unsigned)pt.len;
                 s[u] = slots[pt.slot + (in[u] ? d : 0u)];

@@ -155,7 +155,7 @@ __global__ __launch_bounds__(kBlock) void k_mlp_forward(const float* __restrict_
 //
 // k_grad_part: a work group runs forward and backward of kGradSamples samples at
 // a time with the weights and every activation in LDS, and adds the samples'
-// contributions to the 5131 parameters' gradients in its registers (thread
+// contributions to the 5195 parameters' gradients in its registers (thread
 // (wave w, lane i) owns dW2[16 w .. 16 w + 15][i]), which it writes once at its
 // end.  Wave w holds samples 2 w, 2 w + 1, lane j the hidden unit j; W2 rows are
 // padded to 65 floats, so a row read across lanes and a column read both touch
